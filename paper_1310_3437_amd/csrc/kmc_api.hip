@@ -179,7 +179,7 @@ size_t layout(Plan& p, char* base, uint32_t nboxes, const kmc_config& cfg, const
     p.hist_np = (unsigned long long*)take(sizeof(unsigned long long) * H);
     p.hist_dig = (unsigned long long*)take(sizeof(unsigned long long) * H);
     p.acc = (StepAcc*)take(sizeof(StepAcc) * kAccLanes);
-    p.A = (double*)take(sizeof(double) * 6 * N);
+    p.A = (P64*)take(sizeof(P64) * N);
     p.B = (P64*)take(sizeof(P64) * N);
     const uint32_t blk = cfg.block_size ? (uint32_t)cfg.block_size : 256u;
     const uint32_t nblk_part = (uint32_t)((N + blk - 1) / blk);

@@ -256,8 +256,14 @@ __global__ void k_init_particles(Plan p, const double* __restrict__ in, const ui
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= p.N) return;
     const size_t N = p.N;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) p.A[k * N + i] = in[k * N + i];
+    P64 r;
+    r.x = in[i];
+    r.y = in[N + i];
+    r.z = in[2 * N + i];
+    r.vx = in[3 * N + i];
+    r.vy = in[4 * N + i];
+    r.vz = in[5 * N + i];
+    p.A[i] = r;
     p.idA[i] = i;
     if (p.spA) {
         // an invalid kind is counted by k_check_kinds (the context is then not
@@ -320,14 +326,44 @@ __global__ void k_read_partners(Plan p, int32_t* __restrict__ out)
     out[p.idB[i] & ~kGone] = q >= 0 ? (int32_t)p.idB[q] : -1;
 }
 
+__device__ __forceinline__ void store_columns(double* __restrict__ out, size_t N, size_t k, const P64& r)
+{
+    out[k] = r.x;
+    out[N + k] = r.y;
+    out[2 * N + k] = r.z;
+    out[3 * N + k] = r.vx;
+    out[4 * N + k] = r.vy;
+    out[5 * N + k] = r.vz;
+}
+
+// The state in id order, one launch: every record is read in order and its
+// six values go to six random places.
 __global__ void k_read_state(Plan p, double* __restrict__ out)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= p.N) return;
-    const size_t N = p.N;
-    const uint32_t id = p.idA[i] & ~kGone;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) out[k * N + id] = p.A[k * N + i];
+    store_columns(out, p.N, p.idA[i] & ~kGone, p.A[i]);
+}
+
+// The state in id order, two launches: the place of every id (one random
+// 4-byte write per particle, into the forward-best indices, which are free
+// between steps), then a gather of whole records written out in order.  Both
+// are bound by the random accesses: one 48-byte read and one 4-byte write per
+// particle instead of the six 8-byte writes of k_read_state, each of which
+// costs a memory sector (27.3 -> 6.1 ms at 1e8 particles; the records written
+// to their places and transposed from there, without the index, 7.4 to 9 ms).
+__global__ void k_state_places(Plan p)
+{
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= p.N) return;
+    p.fb_j[p.idA[i] & ~kGone] = (int32_t)i;
+}
+
+__global__ void k_state_gather(Plan p, double* __restrict__ out)
+{
+    const uint32_t id = blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= p.N) return;
+    store_columns(out, p.N, id, p.A[p.fb_j[id]]);
 }
 
 // --------------------------------------------------------------------------
@@ -382,10 +418,8 @@ __global__ void k_bin(Plan p)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     const bool valid = i < p.N;
-    const size_t N = p.N;
     const BoxDev& B = box_of(p, valid ? i : 0u);
-    bin_particle(p, i, valid, B, valid ? p.A[i] : 0.0, valid ? p.A[N + i] : 0.0, valid ? p.A[2 * N + i] : 0.0,
-                 false);
+    bin_particle(p, i, valid, B, valid ? p.A[i].x : 0.0, valid ? p.A[i].y : 0.0, valid ? p.A[i].z : 0.0, false);
 }
 
 // --------------------------------------------------------------------------
@@ -643,8 +677,7 @@ __global__ void k_leaf_count(Plan p)
         const uint32_t c = p.cell[i];
         const uint32_t lvl = p.level[c];
         if (lvl != 0u) {
-            const size_t N = p.N;
-            key = p.pool_base[c] + leaf_code(box_of(p, i), p.adapt_L, lvl, p.A[i], p.A[N + i], p.A[2 * N + i]);
+            key = p.pool_base[c] + leaf_code(box_of(p, i), p.adapt_L, lvl, p.A[i].x, p.A[i].y, p.A[i].z);
         }
     }
     const int lane = threadIdx.x & 63;
@@ -710,7 +743,6 @@ __global__ void k_scatter(Plan p)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     const bool valid = i < p.N;
-    const size_t N = p.N;
     float vm = 0.f;
     bool outside = false;
     double vx = 0.0, vy = 0.0, vz = 0.0;
@@ -718,10 +750,7 @@ __global__ void k_scatter(Plan p)
     // whole grid, read through scalar loads
     auto body = [&](const BoxDev& B) {
         const uint32_t id = p.idA[i];
-        P64 r;
-        r.x = p.A[i];
-        r.y = p.A[N + i];
-        r.z = p.A[2 * N + i];
+        const P64 r = p.A[i];
         const uint32_t c = p.adapt_L > 0 ? p.cell[i] : cell_of(B, r.x, r.y, r.z, (id & kGone) != 0u);
         uint32_t d = p.start[c] + p.slot[i];
         if (p.adapt_L > 0) {
@@ -732,9 +761,9 @@ __global__ void k_scatter(Plan p)
                 d = p.start[c] + p.pool[p.pool_base[c] + code] + p.leaf_slot[i];
             }
         }
-        r.vx = vx = p.A[3 * N + i];
-        r.vy = vy = p.A[4 * N + i];
-        r.vz = vz = p.A[5 * N + i];
+        vx = r.vx;
+        vy = r.vy;
+        vz = r.vz;
         p.B[d] = r;
         p.idB[d] = id;
         if (p.spA) p.spB[d] = p.spA[i];
@@ -2440,17 +2469,19 @@ __device__ __forceinline__ void apply_bc(const BoxDev& B, double x[3], double v[
 // default allocation (103 SGPRs) allowed seven; the few scalar values that
 // no longer fit go to vector-register lanes (measured 4.36 -> 3.92 ms at
 // N = 1e8).  With kinds, eight waves would spill vector registers.
+typedef uint32_t Chunk16 __attribute__((ext_vector_type(4), may_alias));   // 16 bytes of a record
+
 template <bool K>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(K ? 1 : 8))) void k_resolve(Plan p)
 {
     __shared__ uint64_t lds[32];
+    extern __shared__ P64 rec[];   // [blockDim.x]: the new records, on their way out
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     uint64_t my_np = 0, my_dig = 0;
     double nx = 0.0, ny = 0.0, nz = 0.0;
     bool gone = false, left = false;
     if (i < p.N) {
         const BoxDev& B = box_of(p, i);
-        const size_t N = p.N;
         const P64 me = p.B[i];
         double x[3] = {me.x, me.y, me.z}, v[3] = {me.vx, me.vy, me.vz};
         uint32_t id = p.idB[i];
@@ -2538,16 +2569,37 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(K ? 1 : 8)
                 gone = true;
             }
         }
-        // streaming (non-temporal) stores: the state is read again only by
-        // the next step's sorted copy (measured 4% faster than cached stores)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            __builtin_nontemporal_store(x[k], p.A + k * N + i);
-            __builtin_nontemporal_store(v[k], p.A + (3 + k) * N + i);
-        }
+        P64 w;
+        w.x = x[0];
+        w.y = x[1];
+        w.z = x[2];
+        w.vx = v[0];
+        w.vy = v[1];
+        w.vz = v[2];
+        rec[threadIdx.x] = w;
         __builtin_nontemporal_store(id, p.idA + i);
         if (K) p.spA[i] = p.spB[i];
         nx = x[0]; ny = x[1]; nz = x[2];
+    }
+    // The wave's 64 records leave through LDS, each store instruction writing
+    // 1 KiB of consecutive bytes: whole lines, so streaming (non-temporal)
+    // stores apply (the state is read again only by the next step's sorted
+    // copy).  At 1e8 particles 3.66 ms, against 4.12 with each lane storing its
+    // own record and 3.74 with the state in six columns (where the sorted copy,
+    // which reads the state back, took 3.43 ms instead of 3.04).
+    {
+        const uint32_t lane = threadIdx.x & 63u, w0 = threadIdx.x & ~63u;
+        const uint32_t i0 = blockIdx.x * blockDim.x + w0;   // the wave's first particle
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const Chunk16* src = reinterpret_cast<const Chunk16*>(rec + w0);
+        Chunk16* dst = reinterpret_cast<Chunk16*>(p.A + i0);
+        const uint32_t nc = i0 < p.N ? 3u * min(64u, p.N - i0) : 0u;
+#pragma unroll
+        for (uint32_t c = 0; c < 3u; ++c) {
+            const uint32_t t = c * 64u + lane;
+            if (t < nc) __builtin_nontemporal_store(src[t], dst + t);
+        }
     }
     // a1 of the next step: cell and slot of the new position
     bin_particle(p, i, i < p.N, box_of(p, i < p.N ? i : 0u), nx, ny, nz, gone);
@@ -2725,8 +2777,8 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
     }
     mark(KMC_PHASE_RESOLVE);
     if (p.N > 0) {
-        if (p.nspecies > 0) k_resolve<true><<<gN, b, 0, s>>>(p);
-        else k_resolve<false><<<gN, b, 0, s>>>(p);
+        if (p.nspecies > 0) k_resolve<true><<<gN, b, b * sizeof(P64), s>>>(p);
+        else k_resolve<false><<<gN, b, b * sizeof(P64), s>>>(p);
     }
     k_advance<<<1, kAdvanceThreads, 0, s>>>(p);
     mark(KMC_PHASE_COUNT);
@@ -2739,9 +2791,19 @@ hipError_t launch_read_partners(const Plan& p, int32_t* out, hipStream_t s)
     return hipGetLastError();
 }
 
+// Above this size the state is read out by the gather (two launches): direct
+// 4.1 us against 4.9 at 3e4 particles, 8.0 against 5.8 at 1e5, 76 against 42
+// at 1e6.
+constexpr uint32_t kStateGatherMin = 65536;
+
 hipError_t launch_read_state(const Plan& p, double* out, hipStream_t s)
 {
-    if (p.N > 0) k_read_state<<<blocks_for(p.N, 256), 256, 0, s>>>(p, out);
+    if (p.N > kStateGatherMin) {
+        k_state_places<<<blocks_for(p.N, 256), 256, 0, s>>>(p);
+        k_state_gather<<<blocks_for(p.N, 256), 256, 0, s>>>(p, out);
+    } else if (p.N > 0) {
+        k_read_state<<<blocks_for(p.N, 256), 256, 0, s>>>(p, out);
+    }
     return hipGetLastError();
 }
 

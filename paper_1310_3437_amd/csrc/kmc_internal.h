@@ -108,7 +108,7 @@ struct Plan {
     unsigned long long* hist_np;   // [history]: collision count of each step (a ring)
     unsigned long long* hist_dig;  // [history]: digest of each step
     StepAcc* acc;                  // [kAccLanes]: this step's partial sums
-    double* A;                     // current state, 6*N SoA (previous cell order)
+    P64* A;                        // current state (records in the previous step's cell order)
     P64* B;                        // cell-sorted copy of the current state (records)
     float* vmax_part;              // per scatter block: max |v_k| of its particles this step
     unsigned int* box_vmax;        // per box: max |fl32(v_k)| this step (FP32 bits)

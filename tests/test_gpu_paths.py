@@ -1,0 +1,22 @@
+"""GPU parity of the launch choices that depend on sizes: each kernel variant
+at the edges of its range, against the CPU oracle (bit for bit)."""
+import numpy as np
+import pytest
+
+from paper_1310_3437_amd import inputs as I
+from tests.test_gpu_parity import run_parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [63, 65536, 65537, 200_001])
+def test_state_read_out(kmc, n):
+    """Direct read-out up to 65536 particles, the gather above; on the initial
+    state (an exact copy) and on a state in cell order, a ragged last wave."""
+    w = I.c1_small(n=n, steps=2)
+    sim = kmc.Sim(w.boxes, w.state, device="cuda:0", seed=w.seed)
+    assert np.array_equal(sim.state().cpu().numpy(), w.state)
+    sim.close()
+    for block in (64, 1024):
+        _, exact = run_parity(kmc, w, 2, block_size=block)
+        assert exact
