@@ -346,8 +346,7 @@ __global__ void k_read_state(Plan p, double* __restrict__ out)
 }
 
 // The state in id order, two launches: the place of every id (one random
-// 4-byte write per particle, into the forward-best indices, which are free
-// between steps), then a gather of whole records written out in order.  Both
+// 4-byte write per particle), then a gather of whole records written out in order.  Both
 // are bound by the random accesses: one 48-byte read and one 4-byte write per
 // particle instead of the six 8-byte writes of k_read_state, each of which
 // costs a memory sector (27.3 -> 6.1 ms at 1e8 particles; the records written
@@ -356,14 +355,14 @@ __global__ void k_state_places(Plan p)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= p.N) return;
-    p.fb_j[p.idA[i] & ~kGone] = (int32_t)i;
+    p.place[p.idA[i] & ~kGone] = i;
 }
 
 __global__ void k_state_gather(Plan p, double* __restrict__ out)
 {
     const uint32_t id = blockIdx.x * blockDim.x + threadIdx.x;
     if (id >= p.N) return;
-    store_columns(out, p.N, id, p.A[p.fb_j[id]]);
+    store_columns(out, p.N, id, p.A[p.place[id]]);
 }
 
 // --------------------------------------------------------------------------
@@ -498,7 +497,6 @@ __global__ __launch_bounds__(1024) void k_scan_partials(Plan p)
     if (threadIdx.x == 0) {
         p.ctl->recheck_count = 0;
         p.ctl->overflow = 0;
-        p.ctl->ovf_count = 0;
         p.ctl->refined_count = 0;
         p.ctl->pool_used = 0;
     }
@@ -994,11 +992,26 @@ __device__ __forceinline__ bool exact_key(const Plan& p, const BoxDev& B, uint32
 
 // Pairs a lane found, kept until the end of the wave's search (the sorted
 // indices in LDS, the image shifts in a register: a global atomic or a
-// division inside the search loop would stall the whole wave); a lane that
-// finds more than kReg appends the excess to the step's overflow pair list
-// (one counter, handled by k_distribute_overflow), or raises the overflow
-// flag when that list is full (whole-step FP64 fallback).
+// division inside the search loop would stall the whole wave).  A lane that
+// finds more than kReg appends the excess to the wave's list of extra pairs
+// in LDS, which the wave decides and posts together at its end.  When that
+// list is full the lane remembers that it lost pairs, and after the chunk it
+// marks itself and every particle of its window for the full FP64 re-search.
+// In a Maxwellian gas at three particles per cell (about three acceptable
+// partners each) 1.4% of the lanes find more than four; when each of these
+// pairs took an atomic on one step-wide counter the search waited on it
+// (3e6 particles, FP64: 1320 us, now 420; eight slots per lane instead of the
+// wave's list: 437 us, but 8.57 ms against 8.27 on the 1e8 sphere, whose
+// registers they take).
 constexpr int kReg = 4;
+constexpr uint32_t kExtra = 96;
+constexpr uint32_t kMarked = 16;   // list count added by a mark (> kSlots)
+
+struct Extra {
+    uint32_t n;             // pairs offered (those beyond kExtra were lost)
+    uint32_t j[kExtra];     // sorted index of the partner
+    uint8_t lane[kExtra];   // the lane that found the pair
+};
 
 __device__ __forceinline__ uint32_t wcode(int wx, int wy, int wz)
 {
@@ -1007,31 +1020,36 @@ __device__ __forceinline__ uint32_t wcode(int wx, int wy, int wz)
 constexpr uint32_t kNoImage = 0x15u;   // wcode(0, 0, 0)
 
 struct Found {
+    Extra* extra; // the wave's extra pairs in LDS
     uint32_t* sj; // this lane's kept indices in LDS: pair k at sj[64 k] (one store per pair
                   // instead of a select over register slots)
     uint32_t w;   // image shift of pair k in bits 6k..6k+5: (wx+1) | (wy+1) << 2 | (wz+1) << 4;
-                  // bit 31: the overflow pair list was full, nothing more is recorded
-    uint32_t sh;  // 6 n
+                  // bit 31: the lane lost a pair in the current chunk
     int n;
-    __device__ __forceinline__ void add(const Plan& p, uint32_t i, uint32_t jj, uint32_t wcode)
+    __device__ __forceinline__ void add(uint32_t jj, uint32_t wcode)
     {
         if (n < kReg) {
             sj[64 * n] = jj;
-            w |= wcode << sh;
-            sh += 6u;
+            w |= wcode << (6 * n);
             ++n;
-        } else if (!(w >> 31)) {
-            const uint32_t idx = atomicAdd(&p.ctl->ovf_count, 1u);
-            if (idx < p.ovf_cap) {
-                p.ovf[idx] = make_uint2(i, jj);
-            } else {
-                // list full: the whole-step FP64 search decides this step, so
-                // the lane records nothing more (the top bit of w, which the
-                // image shifts of kReg pairs leave free, marks it)
-                atomicOr(&p.ctl->overflow, 1u);
-                w |= 0x80000000u;
-            }
+            return;
         }
+        const uint32_t t = atomicAdd(&extra->n, 1u);
+        if (t < kExtra) {
+            extra->j[t] = jj;
+            extra->lane[t] = (uint8_t)threadIdx.x;
+        } else {
+            w |= 0x80000000u;
+        }
+    }
+    // After a chunk in which the lane lost pairs: particle i and its window
+    // [j0, j1) of the chunk go to the full re-search.
+    __device__ __forceinline__ void mark_lost(const Plan& p, uint32_t i, uint32_t j0, uint32_t j1)
+    {
+        if (!(w >> 31)) return;
+        w &= 0x7FFFFFFFu;
+        (void)atomicAdd(&p.sl_cnt[i], kMarked);
+        for (uint32_t j = j0; j < j1; ++j) (void)atomicAdd(&p.sl_cnt[j], kMarked);
     }
     // Decide the kept pairs exactly in FP64 (the FP32 screen keeps pairs it
     // could not reject), write i's best among them (its forward best) and
@@ -1109,6 +1127,21 @@ struct Found {
         p.fb_key[i] = best_key;
         p.fb_j[i] = best;
         return (uint32_t)n;
+    }
+    // The wave's extra pairs: decided in FP64 and posted to both candidate
+    // lists (tile0: the wave's first particle).
+    __device__ __forceinline__ void flush_extra(const Plan& p, uint32_t tile0, uint32_t lane)
+    {
+        const uint32_t m = min(extra->n, kExtra);
+        for (uint32_t t = lane; t < m; t += 64u) {
+            const uint32_t a = tile0 + extra->lane[t], j = extra->j[t];
+            const P64 me = p.B[a];
+            double key;
+            if (exact_key(p, box_of(p, a), a, me, j, key)) {
+                post_candidate(p, a, j, key);
+                post_candidate(p, j, a, key);
+            }
+        }
     }
 };
 
@@ -1219,7 +1252,7 @@ struct PolF64 {
             if (SH) { rx = rx + sx; ry = ry + sy; rz = rz + sz; }
             const PairQ pq = pair_q(rx, ry, rz, q.vx - o.me.vx, q.vy - o.me.vy, q.vz - o.me.vz);
             const double d2 = K ? l.d2[o.row + l.kind[j - c0]] : D2;
-            if (accept(pq, d2, dt)) f.add(p, i, j, wcode(wx, wy, wz));
+            if (accept(pq, d2, dt)) f.add(j, wcode(wx, wy, wz));
         }
     }
     // full neighbourhood: running (key, id) minimum over the acceptable pairs
@@ -1566,13 +1599,13 @@ struct PolF32 {
             const float4 qa0 = rp[0], qb0 = rp[W], qa1 = rp[1], qb1 = rp[W + 1];
             const bool k0 = test(qa0, qb0), k1 = test(qa1, qb1);
             if (k0 | k1) {
-                if (k0) f.add(p, i, __float_as_uint(qb0.w), wcode(wx, wy, wz));
-                if (k1) f.add(p, i, __float_as_uint(qb1.w), wcode(wx, wy, wz));
+                if (k0) f.add(__float_as_uint(qb0.w), wcode(wx, wy, wz));
+                if (k1) f.add(__float_as_uint(qb1.w), wcode(wx, wy, wz));
             }
         }
         if (rp < re) {
             const float4 qa = rp[0], qb = rp[W];
-            if (test(qa, qb)) f.add(p, i, __float_as_uint(qb.w), wcode(wx, wy, wz));
+            if (test(qa, qb)) f.add(__float_as_uint(qb.w), wcode(wx, wy, wz));
         }
     }
     // full neighbourhood: every pair the screen cannot reject is decided in
@@ -1662,21 +1695,31 @@ void k_search_half(Plan p)
     int cx = 0, cy = 0, cz = 0;
     typename Pol::Own own{};
     if (alive) {
-        bidx = p.boxidx ? p.boxidx[i] : 0u;
-        const BoxDev& B = p.boxes[bidx];
         double x, y, z;
         Pol::load_own(p, i, own, x, y, z);
-        cx = cell1(x, B.lo[0], B.inv_h[0], B.nc[0]);
-        cy = cell1(y, B.lo[1], B.inv_h[1], B.nc[1]);
-        cz = cell1(z, B.lo[2], B.inv_h[2], B.nc[2]);
-        rowkey = B.coff + (uint32_t)B.nc[0] * ((uint32_t)cy + (uint32_t)B.nc[1] * (uint32_t)cz);
+        // (one box: its parameters are the same for every lane and come
+        // through scalar loads, which keeps them out of the vector registers)
+        auto locate = [&](const BoxDev& B) {
+            cx = cell1(x, B.lo[0], B.inv_h[0], B.nc[0]);
+            cy = cell1(y, B.lo[1], B.inv_h[1], B.nc[1]);
+            cz = cell1(z, B.lo[2], B.inv_h[2], B.nc[2]);
+            rowkey = B.coff + (uint32_t)B.nc[0] * ((uint32_t)cy + (uint32_t)B.nc[1] * (uint32_t)cz);
+        };
+        if (p.boxidx) {
+            bidx = p.boxidx[i];
+            locate(p.boxes[bidx]);
+        } else {
+            locate(p.boxes[0]);
+        }
     }
     __shared__ uint32_t found_j[kReg * 64];
+    __shared__ Extra extra;
+    if (lane == 0) extra.n = 0u;   // (a barrier follows before the first pair is tested)
     Found found;
+    found.extra = &extra;
     found.sj = found_j + lane;
     found.n = 0;
     found.w = 0u;
-    found.sh = 0u;
     uint64_t remaining = __ballot(alive);
     while (remaining) {
         const int lead = __ffsll((unsigned long long)remaining) - 1;
@@ -1711,8 +1754,10 @@ void k_search_half(Plan p)
                     Pol::stage(lds, t, p, c0 + t, B, gctx, wx, wy, wz, dy, dz);
                 __syncthreads();
                 const uint32_t j0 = max(ls, c0), j1 = min(le, c0 + n);
-                if (sh) Pol::template scan<true>(p, lds, c0, j0, j1, i, own, B, gctx, wx, wy, wz, dy, dz, found);
+                // (the screen's records are staged with their image shift)
+                if (!Pol::kScreen && sh) Pol::template scan<true>(p, lds, c0, j0, j1, i, own, B, gctx, wx, wy, wz, dy, dz, found);
                 else Pol::template scan<false>(p, lds, c0, j0, j1, i, own, B, gctx, wx, wy, wz, dy, dz, found);
+                found.mark_lost(p, i, j0, j1);
                 __syncthreads();
             }
         };
@@ -1753,9 +1798,12 @@ void k_search_half(Plan p)
             }
         }
     }
-    uint64_t c = valid ? found.template flush<Pol::kFlushBatch, Pol::kFlushSkipEmpty, Pol::kKinds>(p, i, Pol::self64(p, i, own),
+    uint32_t c = valid ? found.template flush<Pol::kFlushBatch, Pol::kFlushSkipEmpty, Pol::kKinds>(p, i, Pol::self64(p, i, own),
                                                                                        p.boxes[bidx])
                        : 0u;
+    __syncthreads();   // every lane's extra pairs are in LDS
+    if (lane == 0) c += extra.n;
+    found.flush_extra(p, xcd_tile(blockIdx.x, gridDim.x) * 64u, (uint32_t)lane);
     // statistics: pairs the search kept, counted at both particles
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
@@ -1896,11 +1944,26 @@ void k_search_full(Plan p)
     search_full_tile<Pol, true>(p, xcd_tile(blockIdx.x, gridDim.x), lds, lid, dslots);
 }
 
-// Whole-step FP64 search, by the full-neighbourhood organisation, when a
-// list overflowed (recheck list or overflow pair list) or, under the FP32
-// screen, a particle lies outside its box's grid or a box's scales leave the
-// screen's safe range.  A fixed grid of waves that exits at once unless the
-// step's flag is set, and otherwise takes the tiles in turn.
+// The re-search of single particles: its blocks of four waves, and the share
+// of the particles (one in kRecheckShare) above which the whole-step search is
+// the faster way to the same partners (measured on 1e6 particles of one speed,
+// three per cell: 1.5 ns a particle re-searched, 0.24 ns a particle of the
+// whole step; the crossing is at one in six).
+constexpr uint32_t kRecheckBlocks = 1024;
+constexpr uint32_t kRecheckShare = 6;
+
+// Whether this step's partners come from the whole-step search: its flag is
+// set, or the re-search has too many particles.
+__device__ __forceinline__ bool whole_step(const Plan& p)
+{
+    return p.ctl->overflow != 0u || p.ctl->recheck_count > p.N / kRecheckShare + 4u * kRecheckBlocks;
+}
+
+// Whole-step FP64 search, by the full-neighbourhood organisation, when the
+// recheck list overflowed or holds a large share of the particles or, under
+// the FP32 screen, a particle lies outside its box's grid or a box's scales
+// leave the screen's safe range.  A fixed grid of waves that exits at once
+// unless the step needs it, and otherwise takes the tiles in turn.
 constexpr uint32_t kFallbackBlocks = 4096;
 // Waves that walk the list of split cells (adaptive bins).
 constexpr uint32_t kAdaptPrepBlocks = 4096;
@@ -1911,7 +1974,7 @@ void k_fallback_full(Plan p)
 {
     __shared__ typename Pol::Lds lds;
     __shared__ uint32_t lid[Pol::W];
-    if (p.ctl->overflow == 0u) return;
+    if (!whole_step(p)) return;
     const uint32_t ntiles = (p.N + 63u) / 64u;
     for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) search_full_tile<Pol, false>(p, t, lds, lid, nullptr);
 }
@@ -2283,28 +2346,9 @@ void k_fallback_adapt(Plan p)
 {
     __shared__ typename Pol::Lds lds;
     __shared__ AdaptLds<Pol::W> al;
-    if (p.ctl->overflow == 0u) return;
+    if (!whole_step(p)) return;
     const uint32_t ntiles = (p.N + 63u) / 64u;
     for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) search_adapt_tile<Pol, false>(p, t, lds, al);
-}
-
-// Pairs beyond a search lane's register slots: decided in FP64 and posted to
-// both candidate lists.
-__global__ void k_distribute_overflow(Plan p)
-{
-    const uint32_t cnt = p.ctl->ovf_count;
-    const uint32_t n = cnt < p.ovf_cap ? cnt : p.ovf_cap;
-    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
-        const uint2 e = p.ovf[k];
-        const P64 me = p.B[e.x];
-        double key;
-        if (exact_key(p, box_of(p, e.x), e.x, me, e.y, key)) {
-            post_candidate(p, e.x, e.y, key);
-            post_candidate(p, e.y, e.x, key);
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && n)
-        atomicAdd(&p.acc[0].cand, 2ull * (unsigned long long)n);
 }
 
 // Wave-aggregated append of this lane's particle to the FP64 recheck list
@@ -2355,10 +2399,12 @@ __global__ __launch_bounds__(256) void k_finish(Plan p)
     if (valid) p.partner[i] = best;
 }
 
-// The FP64 search of one particle by a whole wave: the lanes share its
-// candidates and the wave takes the (key, id) minimum of their minima.  All
-// lanes of the wave must call it with the same i; returns the partner in
-// every lane.
+// The FP64 search of one particle by a whole wave: lanes 0..26 look up one
+// neighbouring cell each, the lanes share the candidates of all of them and
+// the wave takes the (key, id) minimum.  (Row by row, each row's cell starts
+// and records wait for the row before: 18 us for the few particles of a
+// 1e5-particle step, now 7.5.)  All lanes of the wave must call it with
+// the same i; returns the partner in every lane.
 __device__ int32_t search_one64_wave(const Plan& p, uint32_t i)
 {
     if (p.idB[i] & kGone) return -1;
@@ -2366,21 +2412,57 @@ __device__ int32_t search_one64_wave(const Plan& p, uint32_t i)
     const BoxDev& B = box_of(p, i);
     const P64* __restrict__ X = p.B;
     const P64 me = X[i];
-    const int cx = cell1(me.x, B.lo[0], B.inv_h[0], B.nc[0]);
-    const int cy = cell1(me.y, B.lo[1], B.inv_h[1], B.nc[1]);
-    const int cz = cell1(me.z, B.lo[2], B.inv_h[2], B.nc[2]);
     const double dt = B.dt;
     const uint32_t row = kind_row(p, i);
+    // this lane's neighbouring cell: its range of sorted particles and image
+    uint32_t s = 0, n = 0, code = kNoImage;
+    if (lane < 27) {
+        const double xs[3] = {me.x, me.y, me.z};
+        const int d[3] = {lane % 3 - 1, (lane / 3) % 3 - 1, lane / 9 - 1};
+        int q[3], w[3];
+        bool ok = true;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            q[a] = cell1(xs[a], B.lo[a], B.inv_h[a], B.nc[a]) + d[a];
+            w[a] = 0;
+            if (q[a] < 0) { ok = ok && B.periodic[a]; q[a] += B.nc[a]; w[a] = -1; }
+            else if (q[a] >= B.nc[a]) { ok = ok && B.periodic[a]; q[a] -= B.nc[a]; w[a] = 1; }
+        }
+        if (ok) {
+            const uint32_t c = B.coff + (uint32_t)q[0] + (uint32_t)B.nc[0] * ((uint32_t)q[1] + (uint32_t)B.nc[1] * (uint32_t)q[2]);
+            s = p.start[c];
+            n = p.start[c + 1] - s;
+            code = wcode(w[0], w[1], w[2]);
+        }
+    }
+    uint32_t off = n;   // becomes the exclusive prefix of the range sizes
+#pragma unroll
+    for (int sft = 1; sft < 64; sft <<= 1) {
+        const uint32_t y = __shfl_up(off, sft, 64);
+        if (lane >= sft) off += y;
+    }
+    const uint32_t total = (uint32_t)__shfl((int)off, 63, 64);
+    off -= n;
     double best_key = __builtin_inf();
     uint32_t best_id = 0xFFFFFFFFu;
     int32_t best = -1;
-    for_each_range(B, cx, cy, cz, p.start, [&](uint32_t s, uint32_t e, int wx, int wy, int wz) {
-        const bool shift = (wx | wy | wz) != 0;
-        const double sx = (double)wx * B.L[0], sy = (double)wy * B.L[1], sz = (double)wz * B.L[2];
-        for (uint32_t j = s + (uint32_t)lane; j < e; j += 64u) {
+    for (uint32_t f0 = 0; f0 < total; f0 += 64u) {
+        const uint32_t f = f0 + (uint32_t)lane;
+        uint32_t r = 0;   // the last range that starts at or before candidate f
+#pragma unroll
+        for (uint32_t step = 16; step > 0; step >>= 1) {
+            const uint32_t v = (uint32_t)__shfl((int)off, (int)(r + step), 64);
+            if (r + step < 27u && v <= f) r += step;
+        }
+        const uint32_t j = (uint32_t)__shfl((int)s, (int)r, 64) + f - (uint32_t)__shfl((int)off, (int)r, 64);
+        const uint32_t c = (uint32_t)__shfl((int)code, (int)r, 64);
+        if (f < total) {
             const P64 q = X[j];
+            const int wx = (int)(c & 3u) - 1, wy = (int)((c >> 2) & 3u) - 1, wz = (int)((c >> 4) & 3u) - 1;
             double rx = q.x - me.x, ry = q.y - me.y, rz = q.z - me.z;
-            if (shift) { rx = rx + sx; ry = ry + sy; rz = rz + sz; }
+            if (wx != 0) rx = rx + (double)wx * B.L[0];
+            if (wy != 0) ry = ry + (double)wy * B.L[1];
+            if (wz != 0) rz = rz + (double)wz * B.L[2];
             const PairQ pq = pair_q(rx, ry, rz, q.vx - me.vx, q.vy - me.vy, q.vz - me.vz);
             if (accept(pq, pair_D2(p, B, row, j), dt)) {
                 const double key = pq.c2 / pq.g2;
@@ -2392,12 +2474,12 @@ __device__ int32_t search_one64_wave(const Plan& p, uint32_t i)
                 }
             }
         }
-    });
+    }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double k2 = __shfl_xor(best_key, off, 64);
-        const uint32_t id2 = (uint32_t)__shfl_xor((int)best_id, off, 64);
-        const int32_t b2 = __shfl_xor(best, off, 64);
+    for (int sft = 32; sft > 0; sft >>= 1) {
+        const double k2 = __shfl_xor(best_key, sft, 64);
+        const uint32_t id2 = (uint32_t)__shfl_xor((int)best_id, sft, 64);
+        const int32_t b2 = __shfl_xor(best, sft, 64);
         if (k2 < best_key || (k2 == best_key && id2 < best_id)) {
             best_key = k2;
             best_id = id2;
@@ -2411,7 +2493,7 @@ __device__ int32_t search_one64_wave(const Plan& p, uint32_t i)
 // wave per particle.
 __global__ void k_recheck64(Plan p)
 {
-    if (p.ctl->overflow != 0u) return;   // the whole-step FP64 search follows
+    if (whole_step(p)) return;   // the whole-step FP64 search follows
     const uint32_t cnt = p.ctl->recheck_count;
     const uint32_t n = cnt < p.recheck_cap ? cnt : p.recheck_cap;
     const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
@@ -2761,11 +2843,10 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
     }
     mark(KMC_PHASE_FINISH);
     if (p.N > 0 && !full) {
-        k_distribute_overflow<<<256, 256, 0, s>>>(p);
         k_finish<<<blocks_for(p.N, 256), 256, 0, s>>>(p);
     }
     mark(KMC_PHASE_RECHECK);
-    if (p.N > 0 && !full) k_recheck64<<<128, 256, 0, s>>>(p);
+    if (p.N > 0 && !full) k_recheck64<<<kRecheckBlocks, 256, 0, s>>>(p);
     // (the full search raises no overflow; the FP32 sorted copy may)
     if (p.N > 0 && (!full || p.precision == KMC_FP32_SCREEN)) {
         if (p.nspecies > 0) k_fallback_full<PolF64<true>><<<kFallbackBlocks, 64, 0, s>>>(p);

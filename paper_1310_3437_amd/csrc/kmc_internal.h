@@ -84,10 +84,9 @@ struct Ctl {
     unsigned long long candidates_total;// pairs the search recorded, summed over steps
     unsigned int recheck_count;         // this step's recheck list length
     unsigned int overflow;              // this step's flag for the whole-step FP64 search
-    unsigned int ovf_count;             // this step's overflow pair list length
     unsigned int refined_count;         // adaptive bins: bins split this step
     unsigned int pool_used;             // adaptive bins: leaf-table entries claimed this step
-    unsigned int pad_;
+    unsigned int pad_[2];
 };
 
 // FP32 screen thresholds of one box for one step.  The bounds on the error
@@ -128,14 +127,13 @@ struct Plan {
     uint32_t* start;               // per cell + 1: exclusive prefix of count
     uint32_t* partial;             // scan block sums
     uint32_t* recheck;             // sorted indices to re-search in full FP64
-    uint2* ovf;                    // pairs a search lane found beyond its register slots
+    uint32_t* place;               // per id: its index in A (written by the read-out of the state)
     unsigned long long* v2_part;   // adaptive dt: per scatter block, max |v|^2 (FP64 bits) of
                                    // its particles in the box of its first particle
     unsigned long long* box_v2;    // adaptive dt: per box, max |v|^2 of the other particles
     uint32_t N, C, nboxes, H;
     uint32_t nblk_scan;
     uint32_t recheck_cap;
-    uint32_t ovf_cap;
     uint64_t seed;
     int32_t precision, kinematics, block;
     uint32_t nblk_part;            // scatter blocks (entries of vmax_part)
