@@ -1152,29 +1152,63 @@ struct NoGroup {
 // Running (key, id) minimum of one lane in the full-neighbourhood search.
 struct Best {
     double key;
+    float kcut;          // FP32 screen: folded constant of the m3 test for the best key so far
     uint32_t id;
     int32_t j;
     uint32_t accepted;   // acceptable pairs seen (statistics)
-    uint32_t screened;   // FP32 screen: pairs decided in FP64
+    uint32_t screened;   // FP32 screen: pairs it could not reject (statistics)
+    __device__ __forceinline__ void clear()
+    {
+        key = __builtin_inf();
+        kcut = __builtin_inff();
+        id = 0xFFFFFFFFu;
+        j = -1;
+        accepted = 0u;
+        screened = 0u;
+    }
     __device__ __forceinline__ void offer(double k, uint32_t idj, uint32_t jj)
     {
-        accepted += 1u;
         if (k < key || (k == key && idj < id)) {
             key = k;
             id = idj;
             j = (int32_t)jj;
         }
     }
+    // An acceptable pair: its key is divided out only if it can be the best
+    // (a particle with many acceptable partners improves on its best a few
+    // times, and every division stalls the whole wave).  c2 / g2 rounds to at
+    // most key only if c2 <= key (1 + 2^-53) g2, or key is subnormal; the
+    // comparison's own roundings are below its slack of 2^-50.
+    __device__ __forceinline__ void take(const PairQ& q, uint32_t idj, uint32_t jj)
+    {
+        accepted += 1u;
+        if (q.c2 * (1.0 - 0x1.0p-50) <= (key + 0x1.0p-1022) * q.g2) offer(q.c2 / q.g2, idj, jj);
+    }
 };
 
-// Pairs the FP32 screen keeps in the full-neighbourhood search, decided in
-// FP64 once the tile's rows are done (a record gather inside the pair loop
-// stalls the whole wave); a lane's pairs beyond kDefer are decided at once.
-constexpr int kDefer = 4;
+// Pairs of the full-neighbourhood search that the FP32 screen can neither
+// reject nor show to be worse than the particle's best: decided in FP64 once
+// the tile's rows are done (a record gather inside the pair loop stalls the
+// whole wave).  Each waits with a lower bound on its key: when the slots are
+// full, one that the best has overtaken makes room, and at the end only those
+// that may still win are decided, whatever the number of partners.  A particle
+// for which that is not enough (six pairs within the screen's error of each
+// other) is searched again in FP64 by the whole wave.  Against four unpruned
+// slots and an FP64 decision in the loop for every further pair: 1e7
+// particles of one speed (11 partners each) 4.65 -> 2.38 ms, 1e7 in blobs (up
+// to 180 partners) 15.9 -> 10.5 ms, 256 boxes (2.8 partners) 1.66 -> 1.53 ms,
+// and no spilled registers; eight slots without the lower bounds, the
+// overtaken pairs staying in them, took 18.9 ms on the blobs for the particles
+// searched again.
+constexpr int kDefer = 5;
+struct DeferLds {
+    uint32_t j[kDefer][64];      // sorted index
+    float lo[kDefer][64];        // lower bound of the key
+    uint8_t code[kDefer][64];    // image shift (wcode)
+};
 struct Deferred {
-    uint32_t* sj;   // this lane's slots in LDS: sorted index of pair k at sj[64 k],
-                    // its image shift (wcode) at sj[64 (kDefer + k)]
-    int n;
+    DeferLds* l;
+    int n;   // kDefer + 1: there were more
 };
 
 // Tile shape of a search kernel: W records staged per LDS chunk, and the
@@ -1270,7 +1304,7 @@ struct PolF64 {
             if (SH) { rx = rx + sx; ry = ry + sy; rz = rz + sz; }
             const PairQ pq = pair_q(rx, ry, rz, q.vx - o.me.vx, q.vy - o.me.vy, q.vz - o.me.vz);
             const double d2 = K ? l.d2[o.row + l.kind[j - c0]] : D2;
-            if (accept(pq, d2, dt)) best.offer(pq.c2 / pq.g2, lid[j - c0], j);
+            if (accept(pq, d2, dt)) best.take(pq, lid[j - c0], j);
         }
     }
     // adaptive bins: the staged candidates t = u, u + kk, ... (< n) against
@@ -1295,7 +1329,7 @@ struct PolF64 {
             }
             const PairQ pq = pair_q(rx, ry, rz, q.vx - o.me.vx, q.vy - o.me.vy, q.vz - o.me.vz);
             const double d2 = K ? l.d2[o.row + l.kind[t]] : D2;
-            if (accept(pq, d2, dt)) best.offer(pq.c2 / pq.g2, lid[t], j);
+            if (accept(pq, d2, dt)) best.take(pq, lid[t], j);
         }
     }
 };
@@ -1394,11 +1428,11 @@ __device__ __forceinline__ float fold_kD2(double D2_32, double tc1, double RRb)
     return tc1 > 0.0 ? (float)((D2_32 + tc1 + 2.0 * u * (RRb + D2_32 + tc1)) * (1.0 + 2e-6)) : (float)D2_32;
 }
 
-// Returns tc1 and RRb (for fold_kD2 with other D2 values of the box).  With
+// Returns the g2 slopes tt1 and tc1 and RRb (for fold_kD2 with other D2 values of the box).  With
 // particle kinds B.D2 is the largest pair value; every bound term grows with
 // D2, so the bounds hold for every pair of kinds.
 __device__ __forceinline__ void screen_thresholds(const BoxDev& B, const double P[3], double V, float guard,
-                                                  ScreenBounds& g, double& tc1, double& RRb)
+                                                  ScreenBounds& g, double& tt1, double& tc1, double& RRb)
 {
     const double u = 0x1.0p-24, u64 = 0x1.0p-53;
     const double eg = 4.0001 * u * V + 4.0 * u64 * V;
@@ -1416,9 +1450,7 @@ __device__ __forceinline__ void screen_thresholds(const BoxDev& B, const double 
     g.tb0 = (float)t[0];
     g.tb1 = (float)t[1];
     g.tt0 = (float)t[2];
-    g.tt1 = (float)t[3];
     g.tc0 = (float)t[4];
-    g.tc1 = (float)t[5];
     // Folded constants, rounded up (the factor 1 + 2e-6 exceeds every rounding
     // here).  m2: -b - kdt g2 <= -b - (dt + tt1) g2 for kdt >= dt + tt1, and the
     // screen's one rounding of the FMA is monotone.  m3: replacing the
@@ -1431,9 +1463,26 @@ __device__ __forceinline__ void screen_thresholds(const BoxDev& B, const double 
 #pragma unroll
     for (int k = 0; k < 3; ++k) RRb += (Rk[k] + er[k]) * (Rk[k] + er[k]);
     RRb *= 1.0 + 1e-5;
+    tt1 = t[3];
     tc1 = t[5];
     g.kdt = t[3] > 0.0 ? (float)((dt32 + t[3]) * (1.0 + 2e-6)) : B.dt_32;
     g.kD2 = fold_kD2((double)B.D2_32, t[5], RRb);
+    // Pruning by the best key of a particle (full search).  A pair whose key
+    // is at most K passes the m3 test with the constant folded for K, by the
+    // same argument as for D2 (the bounds grow with D2, and K < D2): kc is the
+    // part of that constant that does not depend on K; the factor 1 + 4e-6 on
+    // K and on kc exceeds the rounding of K to FP32 and of the sum.  A pair is
+    // certain to be acceptable when it passes the tests with the bounds on the
+    // other side (kdm <= dt - tt1, g2 above its own error), and its key is
+    // then at most |r|^2 + tc1 - (b^2 - tc0) / g2, which has to be below D2
+    // (taken from kD2: D2 >= (1 - 5e-6) kD2 - kc); the factor 1 + 1e-6 on
+    // |r|^2 exceeds the rounding of that expression (its terms are at most
+    // |r|^2, its other error tc1).  In the same way |r|^2 (1 - 1e-6) - (b^2 + tc0) / g2
+    // is no larger than the K at which the pair would fail the folded test.
+    g.kc = (float)((t[5] + 2.0 * u * (RRb + t[5])) * (1.0 + 4e-6));
+    g.tcu = (float)(2.0 * t[5]);
+    g.kdm = (float)((dt32 - t[3]) * (1.0 - 2e-6));
+    g.gmin = t[7] < 0.5 ? (float)(2.0 * t[6] * (1.0 + 2e-6)) : __builtin_inff();
 }
 
 __global__ void k_screen_bounds(Plan p)
@@ -1466,13 +1515,13 @@ __global__ void k_screen_bounds(Plan p)
 #pragma unroll
         for (int k = 0; k < 3; ++k)
             P[k] = 0.5 * cells[k] * B.h[k] * (1.0 + 1e-9) + 1e-12 * (fabs(B.lo[k]) + fabs(B.hi[k]) + 2.0 * B.L[k]);
-        double tc1, RRb;
+        double tt1, tc1, RRb;
         ScreenBounds g;
-        screen_thresholds(B, P, V, p.guard, g, tc1, RRb);
+        screen_thresholds(B, P, V, p.guard, g, tt1, tc1, RRb);
         p.box_sb[(size_t)b * kSpanClasses + c] = g;
-        const float th[8] = {g.tb0, g.tb1, g.tt0, g.tt1, g.tc0, g.tc1, g.kdt, g.kD2};
+        const float th[9] = {g.tb0, g.tb1, g.tt0, (float)tt1, g.tc0, (float)tc1, g.kdt, g.kD2, g.kc};
 #pragma unroll
-        for (int k = 0; k < 8; ++k) safe = safe && isfinite(th[k]) && (double)fabsf(th[k]) * g2max < big;
+        for (int k = 0; k < 9; ++k) safe = safe && isfinite(th[k]) && (double)fabsf(th[k]) * g2max < big;
         if (p.nspecies > 0) {
             // the folded constant of each pair of kinds, from the pair's own D2
             // rounded to FP32 (entries of absent kinds are never read)
@@ -1616,59 +1665,78 @@ struct PolF32 {
                                      int wx, int wy, int wz, int, int, Best& best, Deferred& d)
     {
         const float tb0 = g.t.tb0, tb1 = g.t.tb1, tt0 = g.t.tt0, kdt = g.t.kdt, tc0 = g.t.tc0, kD2 = g.t.kD2;
-        auto test = [&](uint32_t j) {
-            const float4 qa = l.a[j - c0];
-            const float4 qb = l.b[j - c0];
+        struct Q {
+            float b, g2, rr;
+        };
+        auto test = [&](const float4& qa, const float4& qb, Q& q) {
             const float rx = qa.x - o.x, ry = qa.y - o.y, rz = qa.z - o.z;
             const float gx = qa.w - o.vx, gy = qb.x - o.vy, gz = qb.y - o.vz;
-            const float b = fmaf(rz, gz, fmaf(ry, gy, rx * gx));
-            const float g2 = fmaf(gz, gz, fmaf(gy, gy, gx * gx));
-            const float rr = fmaf(rz, rz, fmaf(ry, ry, rx * rx));
+            q.b = fmaf(rz, gz, fmaf(ry, gy, rx * gx));
+            q.g2 = fmaf(gz, gz, fmaf(gy, gy, gx * gx));
+            q.rr = fmaf(rz, rz, fmaf(ry, ry, rx * rx));
             const float kd = K ? l.kd2[o.row + __float_as_uint(qb.z)] : kD2;
-            const float mb = fmaf(-tb1, g2, b);
-            const float m2 = fmaf(-kdt, g2, -b);
-            const float m3 = fmaf(rr - kd, g2, -(b * b));
-            return (mb <= tb0) & (m2 <= tt0) & (m3 <= tc0) & (j != i);
+            const float mb = fmaf(-tb1, q.g2, q.b);
+            const float m2 = fmaf(-kdt, q.g2, -q.b);
+            const float m3 = fmaf(q.rr - kd, q.g2, -(q.b * q.b));
+            return (mb <= tb0) & (m2 <= tt0) & (m3 <= tc0);
         };
-        // a kept pair: recorded for the end of the tile, or decided at once
-        auto take = [&](uint32_t j) {
-            if (d.n < kDefer) {
-                d.sj[64 * d.n] = j;
-                d.sj[64 * (kDefer + d.n)] = wcode(wx, wy, wz);
-                ++d.n;
-                return;
-            }
-            const P64 me = p.B[i], q = p.B[j];
-            double rx6 = q.x - me.x, ry6 = q.y - me.y, rz6 = q.z - me.z;
-            if (SH) {
-                rx6 = rx6 + (double)wx * B.L[0];
-                ry6 = ry6 + (double)wy * B.L[1];
-                rz6 = rz6 + (double)wz * B.L[2];
-            }
-            const PairQ pq = pair_q(rx6, ry6, rz6, q.vx - me.vx, q.vy - me.vy, q.vz - me.vz);
+        // a kept pair: dropped if its key is certain to exceed the best so
+        // far, else recorded for the end of the tile
+        auto take = [&](const float4& qb, const Q& q) {
+            const uint32_t j = __float_as_uint(qb.w);
+            if (j == i) return;   // (the particle itself passes the tests)
             best.screened += 1u;
-            if (accept(pq, pair_D2(p, B, o.row, j), B.dt)) best.offer(pq.c2 / pq.g2, lid[j - c0], j);
+            if (!(fmaf(q.rr - best.kcut, q.g2, -(q.b * q.b)) <= tc0)) return;
+            // certain to be acceptable: its key's upper bound prunes from here on
+            const float ig = __builtin_amdgcn_rcpf(q.g2), bb = q.b * q.b;
+            const float ku = fmaf(q.rr, 1.000001f, g.t.tcu) + (tc0 - bb) * ig;
+            const float kd = K ? l.kd2[o.row + __float_as_uint(qb.z)] : kD2;
+            if ((fmaf(tb1, q.g2, q.b) <= -tb0) & (fmaf(-g.t.kdm, q.g2, -q.b) <= -tt0) &
+                (ku < fmaf(kd, 0.999995f, -g.t.kc)) & (q.g2 > g.t.gmin))
+                best.kcut = fminf(best.kcut, fmaf(fmaxf(ku, 0.f), 1.000004f, g.t.kc));
+            int k = d.n;
+            if (k < kDefer) {
+                ++d.n;
+            } else {
+                k = -1;
+                for (int e = 0; e < kDefer; ++e)
+                    if (d.l->lo[e][threadIdx.x] > best.kcut) k = e;
+                if (k < 0) {
+                    d.n = kDefer + 1;
+                    return;
+                }
+            }
+            d.l->j[k][threadIdx.x] = j;
+            d.l->lo[k][threadIdx.x] = fmaf(q.rr, 0.999999f, -(bb + tc0) * ig);
+            d.l->code[k][threadIdx.x] = (uint8_t)wcode(wx, wy, wz);
         };
-        uint32_t j = j0;
-        for (; j + 1 < j1; j += 2) {   // two records per iteration, as in scan
-            const bool k0 = test(j), k1 = test(j + 1);
+        const float4* rp = l.a + (j0 - c0);
+        const float4* const re = rp + (j1 > j0 ? j1 - j0 : 0u);
+        Q q0, q1;
+        for (; rp + 1 < re; rp += 2) {   // two records per iteration, as in scan
+            const float4 qa0 = rp[0], qb0 = rp[W], qa1 = rp[1], qb1 = rp[W + 1];
+            const bool k0 = test(qa0, qb0, q0), k1 = test(qa1, qb1, q1);
             if (k0 | k1) {
-                if (k0) take(j);
-                if (k1) take(j + 1);
+                if (k0) take(qb0, q0);
+                if (k1) take(qb1, q1);
             }
         }
-        if (j < j1 && test(j)) take(j);
+        if (rp < re) {
+            const float4 qa = rp[0], qb = rp[W];
+            if (test(qa, qb, q0)) take(qb, q0);
+        }
     }
     // the deferred pairs of particle i, decided in FP64 with their image shifts
     __device__ static void decide_deferred(const Plan& p, uint32_t i, const Deferred& d, const BoxDev& B,
                                            Best& best)
     {
-        if (d.n == 0) return;
+        if (d.n == 0 || d.n > kDefer) return;
         const P64 me = p.B[i];
         const uint32_t row = kind_row(p, i);
         for (int k = 0; k < d.n; ++k) {
-            const uint32_t j = d.sj[64 * k];
-            const uint32_t c = d.sj[64 * (kDefer + k)];
+            if (d.l->lo[k][threadIdx.x] > best.kcut) continue;   // overtaken
+            const uint32_t j = d.l->j[k][threadIdx.x];
+            const uint32_t c = d.l->code[k][threadIdx.x];
             const int wx = (int)(c & 3u) - 1, wy = (int)((c >> 2) & 3u) - 1, wz = (int)((c >> 4) & 3u) - 1;
             const P64 q = p.B[j];
             double rx = q.x - me.x, ry = q.y - me.y, rz = q.z - me.z;
@@ -1676,8 +1744,7 @@ struct PolF32 {
             if (wy != 0) ry = ry + (double)wy * B.L[1];
             if (wz != 0) rz = rz + (double)wz * B.L[2];
             const PairQ pq = pair_q(rx, ry, rz, q.vx - me.vx, q.vy - me.vy, q.vz - me.vz);
-            best.screened += 1u;
-            if (accept(pq, pair_D2(p, B, row, j), B.dt)) best.offer(pq.c2 / pq.g2, p.idB[j], j);
+            if (accept(pq, pair_D2(p, B, row, j), B.dt)) best.take(pq, p.idB[j], j);
         }
     }
 };
@@ -1810,19 +1877,109 @@ void k_search_half(Plan p)
     if (lane == 0 && c) atomicAdd(&p.acc[blockIdx.x % kAccLanes].cand, 2ull * (unsigned long long)c);
 }
 
+// The FP64 search of one particle by a whole wave: lanes 0..26 look up one
+// neighbouring cell each, the lanes share the candidates of all of them and
+// the wave takes the (key, id) minimum.  (Row by row, each row's cell starts
+// and records wait for the row before: 18 us for the few particles of a
+// 1e5-particle step, now 7.5.)  All lanes of the wave must call it with
+// the same i; returns the partner in every lane.
+__device__ int32_t search_one64_wave(const Plan& p, uint32_t i)
+{
+    if (p.idB[i] & kGone) return -1;
+    const int lane = threadIdx.x & 63;
+    const BoxDev& B = box_of(p, i);
+    const P64* __restrict__ X = p.B;
+    const P64 me = X[i];
+    const double dt = B.dt;
+    const uint32_t row = kind_row(p, i);
+    // this lane's neighbouring cell: its range of sorted particles and image
+    uint32_t s = 0, n = 0, code = kNoImage;
+    if (lane < 27) {
+        const double xs[3] = {me.x, me.y, me.z};
+        const int d[3] = {lane % 3 - 1, (lane / 3) % 3 - 1, lane / 9 - 1};
+        int q[3], w[3];
+        bool ok = true;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            q[a] = cell1(xs[a], B.lo[a], B.inv_h[a], B.nc[a]) + d[a];
+            w[a] = 0;
+            if (q[a] < 0) { ok = ok && B.periodic[a]; q[a] += B.nc[a]; w[a] = -1; }
+            else if (q[a] >= B.nc[a]) { ok = ok && B.periodic[a]; q[a] -= B.nc[a]; w[a] = 1; }
+        }
+        if (ok) {
+            const uint32_t c = B.coff + (uint32_t)q[0] + (uint32_t)B.nc[0] * ((uint32_t)q[1] + (uint32_t)B.nc[1] * (uint32_t)q[2]);
+            s = p.start[c];
+            n = p.start[c + 1] - s;
+            code = wcode(w[0], w[1], w[2]);
+        }
+    }
+    uint32_t off = n;   // becomes the exclusive prefix of the range sizes
+#pragma unroll
+    for (int sft = 1; sft < 64; sft <<= 1) {
+        const uint32_t y = __shfl_up(off, sft, 64);
+        if (lane >= sft) off += y;
+    }
+    const uint32_t total = (uint32_t)__shfl((int)off, 63, 64);
+    off -= n;
+    double best_key = __builtin_inf();
+    uint32_t best_id = 0xFFFFFFFFu;
+    int32_t best = -1;
+    for (uint32_t f0 = 0; f0 < total; f0 += 64u) {
+        const uint32_t f = f0 + (uint32_t)lane;
+        uint32_t r = 0;   // the last range that starts at or before candidate f
+#pragma unroll
+        for (uint32_t step = 16; step > 0; step >>= 1) {
+            const uint32_t v = (uint32_t)__shfl((int)off, (int)(r + step), 64);
+            if (r + step < 27u && v <= f) r += step;
+        }
+        const uint32_t j = (uint32_t)__shfl((int)s, (int)r, 64) + f - (uint32_t)__shfl((int)off, (int)r, 64);
+        const uint32_t c = (uint32_t)__shfl((int)code, (int)r, 64);
+        if (f < total) {
+            const P64 q = X[j];
+            const int wx = (int)(c & 3u) - 1, wy = (int)((c >> 2) & 3u) - 1, wz = (int)((c >> 4) & 3u) - 1;
+            double rx = q.x - me.x, ry = q.y - me.y, rz = q.z - me.z;
+            if (wx != 0) rx = rx + (double)wx * B.L[0];
+            if (wy != 0) ry = ry + (double)wy * B.L[1];
+            if (wz != 0) rz = rz + (double)wz * B.L[2];
+            const PairQ pq = pair_q(rx, ry, rz, q.vx - me.vx, q.vy - me.vy, q.vz - me.vz);
+            if (accept(pq, pair_D2(p, B, row, j), dt)) {
+                const double key = pq.c2 / pq.g2;
+                const uint32_t idj = p.idB[j];
+                if (key < best_key || (key == best_key && idj < best_id)) {
+                    best_key = key;
+                    best_id = idj;
+                    best = (int32_t)j;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int sft = 32; sft > 0; sft >>= 1) {
+        const double k2 = __shfl_xor(best_key, sft, 64);
+        const uint32_t id2 = (uint32_t)__shfl_xor((int)best_id, sft, 64);
+        const int32_t b2 = __shfl_xor(best, sft, 64);
+        if (k2 < best_key || (k2 == best_key && id2 < best_id)) {
+            best_key = k2;
+            best_id = id2;
+            best = b2;
+        }
+    }
+    return best;
+}
+
 // Full-neighbourhood variant of the search (KMC_SEARCH_FULL): every
 // particle scans its own and all 26 neighbouring cells and keeps the running
 // (key, id) minimum in registers, writing its partner directly.  It tests
 // every pair twice but records nothing, so it suits dense cells with many
 // acceptable partners per particle, where the candidate lists of the
 // half-neighbourhood search overflow.  Rows and staging as in k_search_half.
-// Under the FP32 screen the kept pairs wait in LDS (Deferred) and are decided
-// in FP64 after the last row.  One tile of 64 cell-sorted particles (one
-// wave), writing their partners; dslots: kDefer * 2 * 64 words of LDS for
-// the FP32 screen (unused in FP64); STATS: count the pairs for the statistics.
+// Under the FP32 screen the kept pairs that may still be the best wait in LDS
+// (Deferred) and are decided in FP64 after the last row.  One tile of 64 cell-sorted particles (one
+// wave), writing their partners; lid: the staged candidates' ids (FP64), dslots:
+// the FP32 screen's deferred pairs, both in LDS; STATS: count the pairs for the statistics.
 template <class Pol, bool STATS>
 __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, typename Pol::Lds& lds, uint32_t* lid,
-                                                 uint32_t* dslots)
+                                                 DeferLds* dslots)
 {
     const int lane = threadIdx.x;
     const uint32_t i = tile * 64u + (uint32_t)lane;
@@ -1845,15 +2002,10 @@ __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, t
         if (p.adapt_L > 0 && p.mixed[rowkey + (uint32_t)cx]) alive = false;
     }
     Best best;
-    best.key = __builtin_inf();
-    best.id = 0xFFFFFFFFu;
-    best.j = -1;
-    best.accepted = 0u;
-    best.screened = 0u;
+    best.clear();
     Deferred dfr;
-    dfr.sj = nullptr;
+    dfr.l = dslots;
     dfr.n = 0;
-    if constexpr (Pol::kScreen) dfr.sj = dslots + lane;
     uint64_t remaining = __ballot(alive);
     while (remaining) {
         const int lead = __ffsll((unsigned long long)remaining) - 1;
@@ -1884,11 +2036,11 @@ __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, t
                 const uint32_t n = min((uint32_t)Pol::W, ge - c0);
                 for (uint32_t t = (uint32_t)lane; t < n; t += 64u) {
                     Pol::stage(lds, t, p, c0 + t, B, gctx, wx, wy, wz, dy, dz);
-                    lid[t] = p.idB[c0 + t];
+                    if constexpr (!Pol::kScreen) lid[t] = p.idB[c0 + t];
                 }
                 __syncthreads();
                 const uint32_t j0 = max(ls, c0), j1 = min(le, c0 + n);
-                if (sh)
+                if (!Pol::kScreen && sh)   // (the screen's records are staged with their image shift)
                     Pol::template scan_best<true>(p, lds, lid, c0, j0, j1, i, own, B, gctx, wx, wy, wz, dy, dz, best,
                                                   dfr);
                 else
@@ -1932,6 +2084,17 @@ __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, t
         for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
         if (lane == 0 && c) atomicAdd(&p.acc[blockIdx.x % kAccLanes].cand, (unsigned long long)c);
     }
+    if constexpr (Pol::kScreen) {
+        // particles with more deferred pairs than slots
+        uint64_t again = __ballot(dfr.n > kDefer);
+        while (again) {
+            const int l = __ffsll((unsigned long long)again) - 1;
+            again &= again - 1;
+            const uint32_t k = tile * 64u + (uint32_t)l;
+            const int32_t b = search_one64_wave(p, k);
+            if (lane == 0) p.partner[k] = b;
+        }
+    }
 }
 
 template <class Pol>
@@ -1939,9 +2102,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Pol::kFullWa
 void k_search_full(Plan p)
 {
     __shared__ typename Pol::Lds lds;
-    __shared__ uint32_t lid[Pol::W];
-    __shared__ uint32_t dslots[Pol::kScreen ? 2 * kDefer * 64 : 1];
-    search_full_tile<Pol, true>(p, xcd_tile(blockIdx.x, gridDim.x), lds, lid, dslots);
+    if constexpr (Pol::kScreen) {
+        __shared__ DeferLds dslots;
+        search_full_tile<Pol, true>(p, xcd_tile(blockIdx.x, gridDim.x), lds, nullptr, &dslots);
+    } else {
+        __shared__ uint32_t lid[Pol::W];
+        search_full_tile<Pol, true>(p, xcd_tile(blockIdx.x, gridDim.x), lds, lid, nullptr);
+    }
 }
 
 // The re-search of single particles: its blocks of four waves, and the share
@@ -2210,11 +2377,7 @@ __device__ __forceinline__ void search_adapt_tile(const Plan& p, uint32_t tile, 
         const uint32_t sbi = gb * (uint32_t)kSpanClasses;   // the neighbourhood spans 3 cells: class 0
         Pol::begin_group(p, B, own, gctx, gc[0], gc[0], gc[1], gc[2], (int)sbi, io, owner);
         Pol::group_lds(lds, p, sbi, lane);
-        best.key = __builtin_inf();
-        best.id = 0xFFFFFFFFu;
-        best.j = -1;
-        best.accepted = 0u;
-        best.screened = 0u;
+        best.clear();
         // ranges of the touching leaves: lanes 0..26 take one neighbour cell each
         if (gcell != nb_of) {
             if (lane < 27) nb_cell_load(p, B, gc, ndx, ndy, ndz, nbc);
@@ -2397,96 +2560,6 @@ __global__ __launch_bounds__(256) void k_finish(Plan p)
     }
     push_recheck(p, i, cnt > (uint32_t)kSlots);
     if (valid) p.partner[i] = best;
-}
-
-// The FP64 search of one particle by a whole wave: lanes 0..26 look up one
-// neighbouring cell each, the lanes share the candidates of all of them and
-// the wave takes the (key, id) minimum.  (Row by row, each row's cell starts
-// and records wait for the row before: 18 us for the few particles of a
-// 1e5-particle step, now 7.5.)  All lanes of the wave must call it with
-// the same i; returns the partner in every lane.
-__device__ int32_t search_one64_wave(const Plan& p, uint32_t i)
-{
-    if (p.idB[i] & kGone) return -1;
-    const int lane = threadIdx.x & 63;
-    const BoxDev& B = box_of(p, i);
-    const P64* __restrict__ X = p.B;
-    const P64 me = X[i];
-    const double dt = B.dt;
-    const uint32_t row = kind_row(p, i);
-    // this lane's neighbouring cell: its range of sorted particles and image
-    uint32_t s = 0, n = 0, code = kNoImage;
-    if (lane < 27) {
-        const double xs[3] = {me.x, me.y, me.z};
-        const int d[3] = {lane % 3 - 1, (lane / 3) % 3 - 1, lane / 9 - 1};
-        int q[3], w[3];
-        bool ok = true;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            q[a] = cell1(xs[a], B.lo[a], B.inv_h[a], B.nc[a]) + d[a];
-            w[a] = 0;
-            if (q[a] < 0) { ok = ok && B.periodic[a]; q[a] += B.nc[a]; w[a] = -1; }
-            else if (q[a] >= B.nc[a]) { ok = ok && B.periodic[a]; q[a] -= B.nc[a]; w[a] = 1; }
-        }
-        if (ok) {
-            const uint32_t c = B.coff + (uint32_t)q[0] + (uint32_t)B.nc[0] * ((uint32_t)q[1] + (uint32_t)B.nc[1] * (uint32_t)q[2]);
-            s = p.start[c];
-            n = p.start[c + 1] - s;
-            code = wcode(w[0], w[1], w[2]);
-        }
-    }
-    uint32_t off = n;   // becomes the exclusive prefix of the range sizes
-#pragma unroll
-    for (int sft = 1; sft < 64; sft <<= 1) {
-        const uint32_t y = __shfl_up(off, sft, 64);
-        if (lane >= sft) off += y;
-    }
-    const uint32_t total = (uint32_t)__shfl((int)off, 63, 64);
-    off -= n;
-    double best_key = __builtin_inf();
-    uint32_t best_id = 0xFFFFFFFFu;
-    int32_t best = -1;
-    for (uint32_t f0 = 0; f0 < total; f0 += 64u) {
-        const uint32_t f = f0 + (uint32_t)lane;
-        uint32_t r = 0;   // the last range that starts at or before candidate f
-#pragma unroll
-        for (uint32_t step = 16; step > 0; step >>= 1) {
-            const uint32_t v = (uint32_t)__shfl((int)off, (int)(r + step), 64);
-            if (r + step < 27u && v <= f) r += step;
-        }
-        const uint32_t j = (uint32_t)__shfl((int)s, (int)r, 64) + f - (uint32_t)__shfl((int)off, (int)r, 64);
-        const uint32_t c = (uint32_t)__shfl((int)code, (int)r, 64);
-        if (f < total) {
-            const P64 q = X[j];
-            const int wx = (int)(c & 3u) - 1, wy = (int)((c >> 2) & 3u) - 1, wz = (int)((c >> 4) & 3u) - 1;
-            double rx = q.x - me.x, ry = q.y - me.y, rz = q.z - me.z;
-            if (wx != 0) rx = rx + (double)wx * B.L[0];
-            if (wy != 0) ry = ry + (double)wy * B.L[1];
-            if (wz != 0) rz = rz + (double)wz * B.L[2];
-            const PairQ pq = pair_q(rx, ry, rz, q.vx - me.vx, q.vy - me.vy, q.vz - me.vz);
-            if (accept(pq, pair_D2(p, B, row, j), dt)) {
-                const double key = pq.c2 / pq.g2;
-                const uint32_t idj = p.idB[j];
-                if (key < best_key || (key == best_key && idj < best_id)) {
-                    best_key = key;
-                    best_id = idj;
-                    best = (int32_t)j;
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int sft = 32; sft > 0; sft >>= 1) {
-        const double k2 = __shfl_xor(best_key, sft, 64);
-        const uint32_t id2 = (uint32_t)__shfl_xor((int)best_id, sft, 64);
-        const int32_t b2 = __shfl_xor(best, sft, 64);
-        if (k2 < best_key || (k2 == best_key && id2 < best_id)) {
-            best_key = k2;
-            best_id = id2;
-            best = b2;
-        }
-    }
-    return best;
 }
 
 // FP64 re-search of the particles whose candidate lists overflowed, one

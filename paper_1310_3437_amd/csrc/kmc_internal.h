@@ -95,9 +95,10 @@ struct Ctl {
 // constants, so a pair is kept when
 //   b - tb1 g2 <= tb0,  -b - kdt g2 <= tt0,  (|r|^2 - kD2) g2 - b^2 <= tc0
 // with kdt >= dt + tt1 and kD2 >= D2 + tc1 plus the rounding of |r|^2 - kD2.
-// tt1 and tc1 are kept for reference.
+// The others serve the pruning by a particle's best key (full search).
 struct alignas(16) ScreenBounds {
-    float tb0, tb1, tt0, kdt, tc0, kD2, tt1, tc1;
+    float tb0, tb1, tt0, kdt, tc0, kD2;
+    float kc, tcu, kdm, gmin, pad_[2];
 };
 
 // Device pointers carved out of the caller's workspace plus launch scalars.
