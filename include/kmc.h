@@ -182,10 +182,11 @@ typedef struct kmc_config {
                                   with 0 < s = e1*e1 + e2*e2 < 1 of the same random
                                   numbers, n = ((e1*e1 - e2*e2) / s,
                                   ((2*e1)*e2) / s, 0)                                    */
-    int32_t tile;              /* tile shape of the partner-search kernel: 0 (default), 1
-                                  (small LDS chunks) or 2 (large chunks, fewer waves per
-                                  SIMD); the results do not depend on it (a launch
-                                  choice, see kmc_autotune)                              */
+    int32_t tile;              /* tile shape of the partner-search kernel: 0 (default; small
+                                  gases then take a search without tiles), 1 (small LDS
+                                  chunks) or 2 (large chunks, fewer waves per SIMD); the
+                                  results do not depend on it (a launch choice, see
+                                  kmc_autotune)                                          */
     int32_t reserved;          /* must be zero                                           */
     double guard_scale;        /* FP32 screen: factor applied to the derived rounding-error
                                   bounds; 0 = 4 (default), >= 1 otherwise.  -1 disables the

@@ -253,6 +253,7 @@ size_t layout(Plan& p, char* base, uint32_t nboxes, const kmc_config& cfg, const
     p.dt_rule = cfg.dt_rule;
     p.search_mode = cfg.search_mode;
     p.tile = cfg.tile;
+    p.direct = 0;   // chosen by kmc_init
     p.dims = cfg.dims == 2 ? 2 : 3;
     p.dt_factor = cfg.dt_factor != 0.0 ? cfg.dt_factor : 1.0;
     return off;
@@ -294,6 +295,35 @@ void fill_box_dev(BoxDev& d, const kmc_box& b, uint32_t coff, uint32_t poff)
     d.n = b.n;
     d.D2_32 = (float)b.D2;
     d.dt_32 = (float)b.dt;
+}
+
+// Lanes per particle of the direct search, or 0 for the staged searches.
+//
+// The direct search tests about twice the pairs without reusing a record, but
+// waits for nothing in between: it is the faster one while the staged search
+// leaves the chip idle.  The line lies by the pair tests a step is expected to
+// make (27 or 9 cells of the mean density): at three particles per cell a step
+// takes 54 us against 111 at 1e4 particles, 72 against 101 at 6e4 and 101
+// against 114 at 1.2e5 (10 M tests), and loses from there on; thinner gases
+// keep the gain longer (0.03 per cell, 1e5 particles: 72 against 153) until
+// 2^18 particles, above which 0.05 per cell is as fast staged (3e5: 105
+// against 102).  Gases in dense blobs gain as well, although they test far
+// more pairs than their mean density says (2.5e5 in 64 blobs: 166 against 248).
+// More lanes per particle shorten the chain of loads and leave more of them
+// without a candidate (16, 8 and 4 lanes: 52, 54, 61 us at 1e4 particles, 64,
+// 60, 65 at 3e4, 83, 75, 72 at 6e4).
+//
+// A tile shape that is asked for (kmc_config.tile) is one of the staged search.
+int32_t direct_lanes(const kmc_box* boxes, uint32_t nboxes, const kmc_config& cfg, uint64_t N)
+{
+    if (N == 0 || N > (1u << 18) || cfg.tile != 0 || cfg.adapt_levels > 0) return 0;
+    double tests = 0.0;
+    for (uint32_t b = 0; b < nboxes; ++b) {
+        const double cells = (double)boxes[b].ncell[0] * (double)boxes[b].ncell[1] * (double)boxes[b].ncell[2];
+        tests += (cfg.dims == 2 ? 9.0 : 27.0) * (double)boxes[b].n * (double)boxes[b].n / cells;
+    }
+    if (tests > 6e6) return 0;
+    return N <= 16384 ? 16 : (N <= 49152 ? 8 : 4);
 }
 
 int dev_err(hipError_t e) { return e == hipSuccess ? KMC_OK : KMC_EDEVICE; }
@@ -397,6 +427,7 @@ int kmc_init(const kmc_box* boxes, uint32_t nboxes, const kmc_config* cfg, const
     }
     c->boxes.assign(boxes, boxes + nboxes);
     layout(c->plan, (char*)d_workspace, nboxes, *cfg, t);
+    c->plan.direct = direct_lanes(boxes, nboxes, *cfg, t.N);
     if (hipGetDevice(&c->device) != hipSuccess) { delete c; return KMC_EDEVICE; }
 
     std::vector<BoxDev> bd(nboxes);

@@ -736,6 +736,25 @@ __global__ __launch_bounds__(64) void k_leaf_scan(Plan p)
 // which the screen's error bounds per box are made.
 // --------------------------------------------------------------------------
 
+// The screen's error bounds take every particle to lie inside the cell it is
+// binned in (up to a slack of 1e-9 of a cell edge).  A particle outside its
+// box's grid (placed there, or moved more than a box length in one step) is
+// binned in an end cell; the step's partners then come from the whole-step
+// FP64 search instead.  Rounding-level excursions (a sphere's mirror image
+// just past a face of a grid that fits it exactly) stay within the slack and
+// are ignored.
+__device__ __forceinline__ bool outside_grid(const BoxDev& B, const P64& r)
+{
+    bool out = !(r.x >= B.lo[0] && r.x <= B.hi[0] && r.y >= B.lo[1] && r.y <= B.hi[1] && r.z >= B.lo[2] &&
+                 r.z <= B.hi[2]);
+    if (out) {
+        const double t0 = 1e-11 * B.h[0], t1 = 1e-11 * B.h[1], t2 = 1e-11 * B.h[2];
+        out = !(r.x >= B.lo[0] - t0 && r.x <= B.hi[0] + t0 && r.y >= B.lo[1] - t1 && r.y <= B.hi[1] + t1 &&
+                r.z >= B.lo[2] - t2 && r.z <= B.hi[2] + t2);
+    }
+    return out;
+}
+
 template <bool F32>
 __global__ void k_scatter(Plan p)
 {
@@ -769,22 +788,8 @@ __global__ void k_scatter(Plan p)
         if (F32) {
             vm = fmaxf(fabsf((float)r.vx), fmaxf(fabsf((float)r.vy), fabsf((float)r.vz)));
 
-            // The screen's error bounds take every particle to lie inside the
-            // cell it is binned in (up to a slack of 1e-9 of a cell edge).  A
-            // particle outside its box's grid (placed there, or moved more
-            // than a box length in one step) is binned in an end cell; the
-            // step's partners then come from the whole-step FP64 search
-            // instead.  Rounding-level excursions (a sphere's mirror image
-            // just past a face of a grid that fits it exactly) stay within
-            // the slack and are ignored.
             if (!(id & kGone)) {
-                outside = !(r.x >= B.lo[0] && r.x <= B.hi[0] && r.y >= B.lo[1] && r.y <= B.hi[1] &&
-                            r.z >= B.lo[2] && r.z <= B.hi[2]);
-                if (outside) {
-                    const double t0 = 1e-11 * B.h[0], t1 = 1e-11 * B.h[1], t2 = 1e-11 * B.h[2];
-                    outside = !(r.x >= B.lo[0] - t0 && r.x <= B.hi[0] + t0 && r.y >= B.lo[1] - t1 &&
-                                r.y <= B.hi[1] + t1 && r.z >= B.lo[2] - t2 && r.z <= B.hi[2] + t2);
-                }
+                outside = outside_grid(B, r);
             }
         }
     };
@@ -841,6 +846,18 @@ __global__ void k_scatter(Plan p)
     }
 }
 
+// The adaptive rule's step from the bits of max |v|^2.
+__device__ __forceinline__ double adaptive_dt(const Plan& p, const BoxDev& B, unsigned long long v2_bits)
+{
+    const double v2 = __longlong_as_double((long long)v2_bits);
+    double dt = B.dt_cap;
+    if (v2 > 0.0) {
+        const double a = (p.dt_factor * B.dx) / sqrt(v2);
+        if (a < dt) dt = a;
+    }
+    return dt;
+}
+
 // This step's time step of every box (one block per box), from the maxima
 // k_scatter gathered: dt = min(cap, (C dx) / sqrt(max |v|^2)) under the
 // adaptive rule, the configured dt otherwise; also the simulated time.
@@ -870,12 +887,7 @@ __global__ __launch_bounds__(256) void k_adapt_dt(Plan p)
             const unsigned long long o = p.box_v2[b];
             const unsigned long long mm = o > red[0] ? o : red[0];
             p.box_v2[b] = 0ull;
-            const double v2 = __longlong_as_double((long long)mm);
-            double dt = B.dt_cap;
-            if (v2 > 0.0) {
-                const double a = (p.dt_factor * B.dx) / sqrt(v2);
-                if (a < dt) dt = a;
-            }
+            const double dt = adaptive_dt(p, B, mm);
             B.dt = dt;
             B.dt_32 = (float)dt;
         }
@@ -1485,18 +1497,19 @@ __device__ __forceinline__ void screen_thresholds(const BoxDev& B, const double 
     g.gmin = t[7] < 0.5 ? (float)(2.0 * t[6] * (1.0 + 2e-6)) : __builtin_inff();
 }
 
-__global__ void k_screen_bounds(Plan p)
+// The thresholds of span class c of box b for the largest speed V, computed by
+// a whole wave (with particle kinds each lane folds the constant of one pair
+// of kinds); true in every lane when the screen is safe to use.
+//
+// The bounds take FP32 arithmetic to neither overflow nor lose to underflow
+// more than a small fraction of them: cell edges in [2^-40, 2^40], the largest
+// speed 0 or in [2^-40, 2^40], the pair test's largest products (|r|^2 g2 <=
+// 144 h^2 V^2 and the folded thresholds times g2 <= 12 V^2) below 2^120, every
+// threshold finite.  Outside that range this step's partners come from the
+// whole-step FP64 search.
+__device__ __forceinline__ bool screen_class(const Plan& p, const BoxDev& B, uint32_t b, int c, double V, int lane,
+                                             bool store)
 {
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= p.nboxes) return;
-    const BoxDev& B = p.boxes[b];
-    const double V = (double)__uint_as_float(p.box_vmax[b]) * (1.0 + 3.0 * 0x1.0p-24);
-    // The bounds take FP32 arithmetic to neither overflow nor lose to
-    // underflow more than a small fraction of them: cell edges in
-    // [2^-40, 2^40], the largest speed 0 or in [2^-40, 2^40], the pair test's
-    // largest products (|r|^2 g2 <= 144 h^2 V^2 and the folded thresholds
-    // times g2 <= 12 V^2) below 2^120, every threshold finite.  Outside that
-    // range this step's partners come from the whole-step FP64 search.
     const double lo_s = 0x1.0p-40, hi_s = 0x1.0p40, big = 0x1.0p120;
     bool safe = V == 0.0 || (V >= lo_s && V <= hi_s);
     double hmax = 0.0;
@@ -1507,35 +1520,40 @@ __global__ void k_screen_bounds(Plan p)
     }
     const double g2max = 12.0 * V * V;
     safe = safe && 256.0 * hmax * hmax * g2max < big;
-    for (int c = 0; c < kSpanClasses; ++c) {
-        // neighbourhood of a group of this class in cells (its own cells and
-        // one on each side)
-        const double cells[3] = {(double)(span_cells(c) + 2), 3.0, 3.0};
-        double P[3];
+    // neighbourhood of a group of this class in cells (its own cells and one
+    // on each side)
+    const double cells[3] = {(double)(span_cells(c) + 2), 3.0, 3.0};
+    double P[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
-            P[k] = 0.5 * cells[k] * B.h[k] * (1.0 + 1e-9) + 1e-12 * (fabs(B.lo[k]) + fabs(B.hi[k]) + 2.0 * B.L[k]);
-        double tt1, tc1, RRb;
-        ScreenBounds g;
-        screen_thresholds(B, P, V, p.guard, g, tt1, tc1, RRb);
-        p.box_sb[(size_t)b * kSpanClasses + c] = g;
-        const float th[9] = {g.tb0, g.tb1, g.tt0, (float)tt1, g.tc0, (float)tc1, g.kdt, g.kD2, g.kc};
+    for (int k = 0; k < 3; ++k)
+        P[k] = 0.5 * cells[k] * B.h[k] * (1.0 + 1e-9) + 1e-12 * (fabs(B.lo[k]) + fabs(B.hi[k]) + 2.0 * B.L[k]);
+    double tt1, tc1, RRb;
+    ScreenBounds g;
+    screen_thresholds(B, P, V, p.guard, g, tt1, tc1, RRb);
+    if (store && lane == 0) p.box_sb[(size_t)b * kSpanClasses + c] = g;
+    const float th[9] = {g.tb0, g.tb1, g.tt0, (float)tt1, g.tc0, (float)tc1, g.kdt, g.kD2, g.kc};
 #pragma unroll
-        for (int k = 0; k < 9; ++k) safe = safe && isfinite(th[k]) && (double)fabsf(th[k]) * g2max < big;
-        if (p.nspecies > 0) {
-            // the folded constant of each pair of kinds, from the pair's own D2
-            // rounded to FP32 (entries of absent kinds are never read)
-            float* tab = p.box_kD2 + ((size_t)b * kSpanClasses + c) * (kMaxKinds * kMaxKinds);
-            for (int e = 0; e < kMaxKinds * kMaxKinds; ++e) {
-                tab[e] = fold_kD2((double)(float)p.sp_D2[e], tc1, RRb);
-                safe = safe && isfinite(tab[e]) && (double)tab[e] * g2max < big;
-            }
-        }
+    for (int k = 0; k < 9; ++k) safe = safe && isfinite(th[k]) && (double)fabsf(th[k]) * g2max < big;
+    if (p.nspecies > 0) {
+        // the folded constant of each pair of kinds, from the pair's own D2
+        // rounded to FP32 (entries of absent kinds are never read)
+        static_assert(kMaxKinds * kMaxKinds == 64, "one lane per pair of kinds");
+        const float kd = fold_kD2((double)(float)p.sp_D2[lane], tc1, RRb);
+        if (store) p.box_kD2[((size_t)b * kSpanClasses + c) * (kMaxKinds * kMaxKinds) + (uint32_t)lane] = kd;
+        safe = safe && isfinite(kd) && (double)kd * g2max < big;
     }
-    if (!safe) atomicOr(&p.ctl->overflow, 1u);
+    return __ballot(safe) == ~0ull;
 }
 
-
+// One block per box, one wave per span class.
+__global__ __launch_bounds__(64 * kSpanClasses) void k_screen_bounds(Plan p)
+{
+    const uint32_t b = blockIdx.x;
+    const double V = (double)__uint_as_float(p.box_vmax[b]) * (1.0 + 3.0 * 0x1.0p-24);
+    const int lane = threadIdx.x & 63;
+    const bool safe = screen_class(p, p.boxes[b], b, (int)(threadIdx.x >> 6), V, lane, true);
+    if (!safe && lane == 0) atomicOr(&p.ctl->overflow, 1u);
+}
 
 // K: particles of several kinds (the screen's folded D2 constant of each
 // pair of kinds from a per-box table in LDS); otherwise the box's constant.
@@ -2514,6 +2532,152 @@ void k_fallback_adapt(Plan p)
     for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) search_adapt_tile<Pol, false>(p, t, lds, al);
 }
 
+// --------------------------------------------------------------------------
+// Direct search: small gases.
+//
+// G lanes (a power of two) share a particle and read its candidates straight
+// from the sorted records: no staging, no barriers, no lists.  Every lane
+// holds the nine row windows of its particle (their starts are loaded
+// together) and takes each G-th candidate of every row, the three rows of a z
+// plane in flight together; the lanes' (key, id) minima are then folded.  It
+// tests every pair from both sides and gives up the reuse of records through
+// LDS, so it is for gases that leave the chip idle, where the staged
+// searches wait for one row after another (search, list merge and re-search
+// together: 4096 particles in 30^3 cells 88 -> 11 us, 1537 at three per cell
+// 83 -> 13, 2e4 in the planar mode 25 -> 10, 1e5 at three per cell 57 -> 56).
+// FP64: the definition's test.  FP32 screen: FP64 differences rounded to FP32
+// against the thresholds of the narrowest groups, which bound larger errors;
+// kept pairs are decided in FP64 from the same records.  In a step that breaks
+// the screen's assumptions (its flag is set) the screen lets every pair pass.
+// --------------------------------------------------------------------------
+template <int G, bool K, bool F32>
+__global__ __launch_bounds__(64) void k_search_direct(Plan p)
+{
+    const int lane = threadIdx.x;
+    const uint32_t u = (uint32_t)lane % (uint32_t)G;
+    const uint32_t i = blockIdx.x * (64u / (uint32_t)G) + (uint32_t)lane / (uint32_t)G;
+    const bool alive = i < p.N && !(p.idB[i] & kGone);
+    Best best;
+    best.clear();
+    if (alive) {
+        auto search = [&](const BoxDev& B, uint32_t bidx) {
+            const P64 me = p.B[i];
+            const uint32_t row = K ? kind_row(p, i) : 0u;
+            const int NX = B.nc[0], NY = B.nc[1], NZ = B.nc[2];
+            const int cx = cell1(me.x, B.lo[0], B.inv_h[0], NX);
+            const int cy = cell1(me.y, B.lo[1], B.inv_h[1], NY);
+            const int cz = cell1(me.z, B.lo[2], B.inv_h[2], NZ);
+            const double D2 = B.D2, dt = B.dt;
+            ScreenBounds t{};
+            const bool screen = F32 && p.ctl->overflow == 0u;
+            if (F32) t = p.box_sb[(size_t)bidx * kSpanClasses];
+            auto test = [&](const P64& q, uint32_t j, int wx, int wy, int wz) {
+                double rx = q.x - me.x, ry = q.y - me.y, rz = q.z - me.z;
+                if (wx != 0) rx = rx + (double)wx * B.L[0];
+                if (wy != 0) ry = ry + (double)wy * B.L[1];
+                if (wz != 0) rz = rz + (double)wz * B.L[2];
+                const double gx = q.vx - me.vx, gy = q.vy - me.vy, gz = q.vz - me.vz;
+                if (F32) {
+                    const float sx = (float)rx, sy = (float)ry, sz = (float)rz;
+                    const float hx = (float)gx, hy = (float)gy, hz = (float)gz;
+                    const float b = fmaf(sz, hz, fmaf(sy, hy, sx * hx));
+                    const float g2 = fmaf(hz, hz, fmaf(hy, hy, hx * hx));
+                    const float rr = fmaf(sz, sz, fmaf(sy, sy, sx * sx));
+                    const float kd = K ? p.box_kD2[(size_t)bidx * kSpanClasses * (kMaxKinds * kMaxKinds) + row + p.spB[j]]
+                                       : t.kD2;
+                    const bool keep = (fmaf(-t.tb1, g2, b) <= t.tb0) & (fmaf(-t.kdt, g2, -b) <= t.tt0) &
+                                      (fmaf(rr - kd, g2, -(b * b)) <= t.tc0);
+                    if (screen && !keep) return;
+                    if (j == i) return;
+                    best.screened += 1u;
+                }
+                const PairQ pq = pair_q(rx, ry, rz, gx, gy, gz);
+                // (the particle itself has g2 = 0 and is never accepted)
+                if (accept(pq, K ? pair_D2(p, B, row, j) : D2, dt)) best.take(pq, p.idB[j], j);
+            };
+            // the windows of the nine rows (empty where a row does not exist)
+            uint32_t rs[9], re[9];
+            int wys[3], wzs[3];
+            const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx + 1 < NX ? cx + 1 : NX - 1;
+            uint32_t rowbase[9];
+            uint32_t exist = 0;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                int ny = cy + a - 1, nz = cz + a - 1;
+                wys[a] = ny < 0 ? -1 : (ny >= NY ? 1 : 0);
+                wzs[a] = nz < 0 ? -1 : (nz >= NZ ? 1 : 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 9; ++r) {
+                const int wy = wys[r % 3], wz = wzs[r / 3];
+                const bool ok = (wy == 0 || B.periodic[1]) && (wz == 0 || B.periodic[2]);
+                const int ny = cy + r % 3 - 1 - wy * NY, nz = cz + r / 3 - 1 - wz * NZ;
+                rowbase[r] = B.coff + (uint32_t)NX * ((uint32_t)ny + (uint32_t)NY * (uint32_t)nz);
+                rs[r] = re[r] = 0u;
+                if (ok) {
+                    exist |= 1u << r;
+                    rs[r] = p.start[rowbase[r] + (uint32_t)x0];
+                    re[r] = p.start[rowbase[r] + (uint32_t)x1 + 1u];
+                }
+            }
+#pragma unroll
+            for (int z = 0; z < 3; ++z) {
+                uint32_t j0 = rs[3 * z] + u, j1 = rs[3 * z + 1] + u, j2 = rs[3 * z + 2] + u;
+                const uint32_t e0 = re[3 * z], e1 = re[3 * z + 1], e2 = re[3 * z + 2];
+                while (j0 < e0 || j1 < e1 || j2 < e2) {
+                    P64 q0, q1, q2;
+                    const bool h0 = j0 < e0, h1 = j1 < e1, h2 = j2 < e2;
+                    if (h0) q0 = p.B[j0];
+                    if (h1) q1 = p.B[j1];
+                    if (h2) q2 = p.B[j2];
+                    if (h0) test(q0, j0, 0, wys[0], wzs[z]);
+                    if (h1) test(q1, j1, 0, wys[1], wzs[z]);
+                    if (h2) test(q2, j2, 0, wys[2], wzs[z]);
+                    j0 += (uint32_t)G;
+                    j1 += (uint32_t)G;
+                    j2 += (uint32_t)G;
+                }
+            }
+            if (B.periodic[0] && (cx == 0 || cx == NX - 1)) {
+                // the wrapped end cell of every row
+                const int wx = cx == 0 ? -1 : 1, c = cx == 0 ? NX - 1 : 0;
+                for (int r = 0; r < 9; ++r) {
+                    if (!((exist >> r) & 1u)) continue;
+                    const int wy = wys[r % 3], wz = wzs[r / 3];
+                    const int ny = cy + r % 3 - 1 - wy * NY, nz = cz + r / 3 - 1 - wz * NZ;
+                    const uint32_t cell =
+                        B.coff + (uint32_t)c + (uint32_t)NX * ((uint32_t)ny + (uint32_t)NY * (uint32_t)nz);
+                    const uint32_t e = p.start[cell + 1u];
+                    for (uint32_t j = p.start[cell] + u; j < e; j += (uint32_t)G) test(p.B[j], j, wx, wy, wz);
+                }
+            }
+        };
+        // (one box: its parameters come through scalar loads)
+        if (p.boxidx) {
+            const uint32_t b = p.boxidx[i];
+            search(p.boxes[b], b);
+        } else {
+            search(p.boxes[0], 0u);
+        }
+    }
+    uint32_t c = F32 ? best.screened : best.accepted;
+#pragma unroll
+    for (int off = G / 2; off > 0; off >>= 1) {
+        const double k2 = __shfl_xor(best.key, off, 64);
+        const uint32_t id2 = (uint32_t)__shfl_xor((int)best.id, off, 64);
+        const int32_t j2 = __shfl_xor(best.j, off, 64);
+        if (k2 < best.key || (k2 == best.key && id2 < best.id)) {
+            best.key = k2;
+            best.id = id2;
+            best.j = j2;
+        }
+    }
+    if (i < p.N && u == 0) p.partner[i] = best.j;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+    if (lane == 0 && c) atomicAdd(&p.acc[blockIdx.x % kAccLanes].cand, (unsigned long long)c);
+}
+
 // Wave-aggregated append of this lane's particle to the FP64 recheck list
 // (all lanes of the wave must call it).
 __device__ __forceinline__ void push_recheck(const Plan& p, uint32_t i, bool need)
@@ -2618,7 +2782,116 @@ __device__ __forceinline__ void apply_bc(const BoxDev& B, double x[3], double v[
     }
 }
 
+// Step of sorted particle i: its new record to *out, its id and kind to their
+// places, its new position (nx, ny, nz); gone: absorbed earlier or now, left:
+// absorbed now; the member of a colliding pair with the smaller id counts the
+// collision in my_np and my_dig (all of these are cleared by the caller).
 // K: particles of several kinds (masses from the kind table).
+template <bool K>
+__device__ __forceinline__ void move_particle(const Plan& p, uint32_t i, P64* out, uint64_t& my_np, uint64_t& my_dig,
+                                              double& nx, double& ny, double& nz, bool& gone, bool& left)
+{
+    const BoxDev& B = box_of(p, i);
+    const P64 me = p.B[i];
+    double x[3] = {me.x, me.y, me.z}, v[3] = {me.vx, me.vy, me.vz};
+    uint32_t id = p.idB[i];
+    gone = (id & kGone) != 0u;   // absorbed earlier: keeps its state
+    const int32_t q = p.partner[i];
+    const double dt = B.dt;
+    bool hit = false;
+    if (q >= 0 && p.partner[q] == (int32_t)i) {
+        hit = true;
+        const uint32_t idq = p.idB[q];
+        const P64 o = p.B[q];
+        const double xq[3] = {o.x, o.y, o.z}, vq[3] = {o.vx, o.vy, o.vz};
+        const bool me_a = id < idq;   // a = the member with the smaller id
+        const double* xa = me_a ? x : xq;
+        const double* va = me_a ? v : vq;
+        const double* xb = me_a ? xq : x;
+        const double* vb = me_a ? vq : v;
+        const uint32_t ida = me_a ? id : idq, idb = me_a ? idq : id;
+        double r[3], g[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int ca = cell1(xa[k], B.lo[k], B.inv_h[k], B.nc[k]);
+            const int cb = cell1(xb[k], B.lo[k], B.inv_h[k], B.nc[k]);
+            const int w = wrap_of(ca, cb, B.nc[k], B.periodic[k]);
+            r[k] = xb[k] - xa[k];
+            if (w != 0) r[k] = r[k] + (double)w * B.L[k];
+            g[k] = vb[k] - va[k];
+        }
+        const PairQ pq = pair_q(r[0], r[1], r[2], g[0], g[1], g[2]);
+        const double tstar = (-pq.b) / pq.g2;
+        double nh[3];
+        direction(p.seed, p.ctl->step, ida, nh, p.dims);
+        // masses of a and b (particle kinds), equal otherwise
+        double ma = 1.0, mb = 1.0;
+        if (K) {
+            const uint32_t ki = p.spB[i], kq = p.spB[q];
+            ma = p.sp_mass[me_a ? ki : kq];
+            mb = p.sp_mass[me_a ? kq : ki];
+        }
+        double vn[3];
+        if (ma == mb) {
+            const double hg = 0.5 * sqrt(pq.g2);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const double vcm = 0.5 * (va[k] + vb[k]);
+                vn[k] = me_a ? vcm + hg * nh[k] : vcm - hg * nh[k];
+            }
+        } else {
+            // centre-of-mass velocity, |g| shared in inverse proportion to the masses
+            const double M = ma + mb, gm = sqrt(pq.g2);
+            const double wa = (mb / M) * gm, wb = (ma / M) * gm;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const double vcm = fma(ma, va[k], mb * vb[k]) / M;
+                vn[k] = me_a ? vcm + wa * nh[k] : vcm - wb * nh[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (p.kinematics == KMC_KIN_AT_TSTAR) {
+                const double xs = x[k] + v[k] * tstar;
+                x[k] = xs + vn[k] * (dt - tstar);
+            } else {
+                x[k] = x[k] + vn[k] * dt;
+            }
+            v[k] = vn[k];
+        }
+        if (me_a) {
+            my_np = 1;
+            my_dig = pair_hash(ida, idb);
+        }
+    }
+    if (!hit && !gone) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) x[k] = x[k] + v[k] * dt;
+    }
+    if (!gone) {
+        apply_bc(B, x, v);
+        // absorbing faces: beyond them the particle leaves the gas
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (B.absorb[k] && (x[k] < B.lo[k] || x[k] > B.hi[k])) left = true;
+        if (left) {
+            id |= kGone;
+            gone = true;
+        }
+    }
+    P64 w;
+    w.x = x[0];
+    w.y = x[1];
+    w.z = x[2];
+    w.vx = v[0];
+    w.vy = v[1];
+    w.vz = v[2];
+    *out = w;
+    __builtin_nontemporal_store(id, p.idA + i);
+    if (K) p.spA[i] = p.spB[i];
+    nx = x[0]; ny = x[1]; nz = x[2];
+}
+
 // One kind of particle: compiled for eight waves per SIMD.  The collision
 // path is bound by the latency of its partner-record gathers, and the
 // default allocation (103 SGPRs) allowed seven; the few scalar values that
@@ -2635,107 +2908,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(K ? 1 : 8)
     uint64_t my_np = 0, my_dig = 0;
     double nx = 0.0, ny = 0.0, nz = 0.0;
     bool gone = false, left = false;
-    if (i < p.N) {
-        const BoxDev& B = box_of(p, i);
-        const P64 me = p.B[i];
-        double x[3] = {me.x, me.y, me.z}, v[3] = {me.vx, me.vy, me.vz};
-        uint32_t id = p.idB[i];
-        gone = (id & kGone) != 0u;   // absorbed earlier: keeps its state
-        const int32_t q = p.partner[i];
-        const double dt = B.dt;
-        bool hit = false;
-        if (q >= 0 && p.partner[q] == (int32_t)i) {
-            hit = true;
-            const uint32_t idq = p.idB[q];
-            const P64 o = p.B[q];
-            const double xq[3] = {o.x, o.y, o.z}, vq[3] = {o.vx, o.vy, o.vz};
-            const bool me_a = id < idq;   // a = the member with the smaller id
-            const double* xa = me_a ? x : xq;
-            const double* va = me_a ? v : vq;
-            const double* xb = me_a ? xq : x;
-            const double* vb = me_a ? vq : v;
-            const uint32_t ida = me_a ? id : idq, idb = me_a ? idq : id;
-            double r[3], g[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const int ca = cell1(xa[k], B.lo[k], B.inv_h[k], B.nc[k]);
-                const int cb = cell1(xb[k], B.lo[k], B.inv_h[k], B.nc[k]);
-                const int w = wrap_of(ca, cb, B.nc[k], B.periodic[k]);
-                r[k] = xb[k] - xa[k];
-                if (w != 0) r[k] = r[k] + (double)w * B.L[k];
-                g[k] = vb[k] - va[k];
-            }
-            const PairQ pq = pair_q(r[0], r[1], r[2], g[0], g[1], g[2]);
-            const double tstar = (-pq.b) / pq.g2;
-            double nh[3];
-            direction(p.seed, p.ctl->step, ida, nh, p.dims);
-            // masses of a and b (particle kinds), equal otherwise
-            double ma = 1.0, mb = 1.0;
-            if (K) {
-                const uint32_t ki = p.spB[i], kq = p.spB[q];
-                ma = p.sp_mass[me_a ? ki : kq];
-                mb = p.sp_mass[me_a ? kq : ki];
-            }
-            double vn[3];
-            if (ma == mb) {
-                const double hg = 0.5 * sqrt(pq.g2);
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const double vcm = 0.5 * (va[k] + vb[k]);
-                    vn[k] = me_a ? vcm + hg * nh[k] : vcm - hg * nh[k];
-                }
-            } else {
-                // centre-of-mass velocity, |g| shared in inverse proportion to the masses
-                const double M = ma + mb, gm = sqrt(pq.g2);
-                const double wa = (mb / M) * gm, wb = (ma / M) * gm;
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const double vcm = fma(ma, va[k], mb * vb[k]) / M;
-                    vn[k] = me_a ? vcm + wa * nh[k] : vcm - wb * nh[k];
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                if (p.kinematics == KMC_KIN_AT_TSTAR) {
-                    const double xs = x[k] + v[k] * tstar;
-                    x[k] = xs + vn[k] * (dt - tstar);
-                } else {
-                    x[k] = x[k] + vn[k] * dt;
-                }
-                v[k] = vn[k];
-            }
-            if (me_a) {
-                my_np = 1;
-                my_dig = pair_hash(ida, idb);
-            }
-        }
-        if (!hit && !gone) {
-#pragma unroll
-            for (int k = 0; k < 3; ++k) x[k] = x[k] + v[k] * dt;
-        }
-        if (!gone) {
-            apply_bc(B, x, v);
-            // absorbing faces: beyond them the particle leaves the gas
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                if (B.absorb[k] && (x[k] < B.lo[k] || x[k] > B.hi[k])) left = true;
-            if (left) {
-                id |= kGone;
-                gone = true;
-            }
-        }
-        P64 w;
-        w.x = x[0];
-        w.y = x[1];
-        w.z = x[2];
-        w.vx = v[0];
-        w.vy = v[1];
-        w.vz = v[2];
-        rec[threadIdx.x] = w;
-        __builtin_nontemporal_store(id, p.idA + i);
-        if (K) p.spA[i] = p.spB[i];
-        nx = x[0]; ny = x[1]; nz = x[2];
-    }
+    if (i < p.N) move_particle<K>(p, i, rec + threadIdx.x, my_np, my_dig, nx, ny, nz, gone, left);
     // The wave's 64 records leave through LDS, each store instruction writing
     // 1 KiB of consecutive bytes: whole lines, so streaming (non-temporal)
     // stores apply (the state is read again only by the next step's sorted
@@ -2834,6 +3007,21 @@ __global__ __launch_bounds__(256) void k_count_tests(Plan p, unsigned long long*
 
 inline uint32_t blocks_for(uint32_t n, uint32_t b) { return (n + b - 1) / b; }
 
+// The direct search with G lanes per particle.
+template <int G>
+void launch_direct(hipStream_t s, const Plan& p)
+{
+    const uint32_t g = blocks_for(p.N, 64 / G);
+    const bool f32 = p.precision == KMC_FP32_SCREEN;
+    if (p.nspecies > 0) {
+        if (f32) k_search_direct<G, true, true><<<g, 64, 0, s>>>(p);
+        else k_search_direct<G, true, false><<<g, 64, 0, s>>>(p);
+    } else {
+        if (f32) k_search_direct<G, false, true><<<g, 64, 0, s>>>(p);
+        else k_search_direct<G, false, false><<<g, 64, 0, s>>>(p);
+    }
+}
+
 // The search kernel of one precision policy and tile shape.
 template <template <bool, class> class Pol, class T>
 void launch_search(bool kinds, bool full, uint32_t gW, hipStream_t s, const Plan& p)
@@ -2891,11 +3079,16 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
     const uint32_t gW = blocks_for(p.N, 64);
     if (p.precision == KMC_FP32_SCREEN) {
         k_vmax_reduce<<<p.nboxes * kVmaxSplit, 256, 0, s>>>(p);
-        k_screen_bounds<<<blocks_for(p.nboxes, 64), 64, 0, s>>>(p);
+        k_screen_bounds<<<p.nboxes, 64 * kSpanClasses, 0, s>>>(p);
     }
     if (ev) (void)hipEventRecord(ev[KMC_PHASE_COUNT + 1], s);   // search kernel alone
-    const bool full = p.search_mode == KMC_SEARCH_FULL;
-    if (p.N > 0) {
+    const int32_t dg = p.direct;
+    const bool full = p.search_mode == KMC_SEARCH_FULL || dg > 0;
+    if (dg > 0) {
+        if (dg == 4) launch_direct<4>(s, p);
+        else if (dg == 8) launch_direct<8>(s, p);
+        else launch_direct<16>(s, p);
+    } else if (p.N > 0) {
         const bool kinds = p.nspecies > 0;
         if (p.precision == KMC_FP32_SCREEN) {
             if (p.tile == 1) launch_search<PolF32, TileF32_1>(kinds, full, gW, s, p);
@@ -2921,7 +3114,7 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
     mark(KMC_PHASE_RECHECK);
     if (p.N > 0 && !full) k_recheck64<<<kRecheckBlocks, 256, 0, s>>>(p);
     // (the full search raises no overflow; the FP32 sorted copy may)
-    if (p.N > 0 && (!full || p.precision == KMC_FP32_SCREEN)) {
+    if (p.N > 0 && dg == 0 && (!full || p.precision == KMC_FP32_SCREEN)) {
         if (p.nspecies > 0) k_fallback_full<PolF64<true>><<<kFallbackBlocks, 64, 0, s>>>(p);
         else k_fallback_full<PolF64<false>><<<kFallbackBlocks, 64, 0, s>>>(p);
         if (p.adapt_L > 0) {

@@ -142,6 +142,7 @@ struct Plan {
     int32_t dt_rule;               // kmc_dt_rule
     int32_t search_mode;           // kmc_search_mode
     int32_t tile;                  // tile shape of the search kernel (0, 1, 2)
+    int32_t direct;                // lanes per particle of the direct search (0: a staged search)
     // density-adaptive bins (adapt_L == 0: the uniform grid)
     int32_t adapt_L;               // at most this many halvings of a bin
     uint32_t adapt_T;              // split while more than adapt_T * 8^level particles

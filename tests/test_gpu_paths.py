@@ -5,6 +5,7 @@ import pytest
 
 from paper_1310_3437_amd import inputs as I
 from tests.test_gpu_parity import run_parity
+from tests import test_gpu_screen as S
 from tests.test_gpu_screen import dense_gas
 
 pytestmark = pytest.mark.gpu
@@ -78,3 +79,65 @@ def test_full_search_equal_and_near_equal_keys(kmc, precision):
     for mode in (kmc.KMC_SEARCH_FULL, kmc.KMC_SEARCH_HALF):
         _, exact = run_parity(kmc, w, 1, precision=precision, search_mode=mode)
         assert exact
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n", [1, 5, 63, 16384, 16385, 49152, 49153, 60_000])
+def test_direct_search_sizes(kmc, n, precision):
+    """The direct search at the edges of its three widths (16, 8, 4 lanes per
+    particle), periodic and reflecting, thin and at three per cell."""
+    box, s = I.uniform_box(n, periodic=bool(n % 2), ic_seed=n, D=None if n > 200 else 0.3)
+    cases = [I.Workload("direct", [box], s, 2)]
+    if n > 1000:
+        cases.append(I.c1_small(n=n, steps=2))
+    for w in cases:
+        for mode in (kmc.KMC_SEARCH_HALF, kmc.KMC_SEARCH_FULL):
+            _, exact = run_parity(kmc, w, 2, precision=precision, search_mode=mode)
+            assert exact
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_direct_search_forms(kmc, precision):
+    """Three cells to an axis (every cell a seam), a sphere, absorbing walls,
+    the planar mode, several boxes with empty ones between, kinds, velocity-only
+    collisions, the adaptive step, graph replay."""
+    box, s = I.uniform_box(400, ncell=3, D=0.3, ic_seed=5)
+    run_parity(kmc, I.Workload("seams", [box], s, 3), 3, precision=precision, use_graph=True)
+    run_parity(kmc, I.c3_sphere(n=20_000, steps=3), 3, precision=precision)
+    box, s = I.uniform_box(3000, periodic=False, ic_seed=6)
+    box.absorb = (True, False, True)
+    run_parity(kmc, I.Workload("absorb", [box], s, 4), 4, precision=precision)
+    run_parity(kmc, I.c1_planar(n=3001, steps=3), 3, precision=precision)
+    w = I.c4_batch(nboxes=5, n_lo=100, n_hi=3000, steps=3)
+    e = I.Box(n=0, lo=(0, 0, 0), hi=(1, 1, 1), ncell=(4, 4, 4), periodic=(True,) * 3, D2=0.01, dt=0.01)
+    w.boxes = [e] + w.boxes[:2] + [e] + w.boxes[2:] + [e]
+    w.kinematics = 1
+    run_parity(kmc, w, 3, precision=precision)
+    w = I.c6_mixture(n=4001, steps=3)
+    run_parity(kmc, w, 3, precision=precision, kinds=(w.species, w.radius, w.mass), use_graph=True)
+    w = I.ppc_sweep_case(n=5000, ppc=4.0)
+    run_parity(kmc, w, 3, precision=precision)
+
+
+@pytest.mark.parametrize("mode", ["half", "full"])
+@pytest.mark.parametrize("tile", [1, 2])
+def test_staged_screen_on_adversarial_pairs(kmc, tile, mode):
+    """The staged screens (a tile shape asked for) on near-boundary pairs, rows
+    hundreds of cells apart, particles outside the grid and scales outside the
+    screen's range, and their negative control."""
+    cfg = dict(tile=tile, search_mode=kmc.KMC_SEARCH_FULL if mode == "full" else kmc.KMC_SEARCH_HALF)
+    f32 = kmc.KMC_FP32_SCREEN
+    for variant in (dict(), dict(bulk=20.0), dict(origin=1000.0)):
+        mism, same, _ = S.gpu_vs_oracle(kmc, S.adversarial(seed=21, **variant), f32, **cfg)
+        assert mism == 0 and same
+    for spacing in (3, 60, 200, 1000):
+        mism, same, _ = S.gpu_vs_oracle(kmc, S.adversarial_sparse_row(seed=22, spacing=spacing), f32, **cfg)
+        assert mism == 0 and same
+    out = S.adversarial_outside(seed=23)
+    mism, same, stats = S.gpu_vs_oracle(kmc, out[0] if isinstance(out, tuple) else out, f32, steps=2, **cfg)
+    assert mism == 0 and same and stats["fallbacks"] > 0
+    mism, same, _ = S.gpu_vs_oracle(kmc, S.scaled(S.adversarial(seed=24), vel=2.0 ** 60), f32, **cfg)
+    assert mism == 0 and same
+    w = S.adversarial(seed=12, kinds=("radius", "tend", "tzero"))
+    mism, _, _ = S.gpu_vs_oracle(kmc, w, f32, guard_scale=-1.0, **cfg)
+    assert mism > 0
