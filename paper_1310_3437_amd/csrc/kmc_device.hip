@@ -422,9 +422,28 @@ __global__ void k_bin(Plan p)
 }
 
 // --------------------------------------------------------------------------
-// a2: exclusive prefix sum of the cell counts (reduce, scan of block sums,
-// down-sweep).  The down-sweep also clears the counts for the next step.
+// a2: exclusive prefix sum of the cell counts, which also clears the counts
+// for the next step: block sums, their scan, down-sweep.  Up to kSumBlocks
+// blocks the down-sweep adds up the sums before it itself, and up to
+// kOneScanCells cells one block does everything: in a small gas a launch costs
+// more than its work (about 4 us each; 2.7e4 cells: three launches 12 us, one
+// 7).
 // --------------------------------------------------------------------------
+constexpr uint32_t kSumBlocks = 1024;
+constexpr uint32_t kOneScanCells = 32768;
+
+// Start of a step's device-side bookkeeping (recheck list, split cells and
+// the FP32 screen's velocity bounds), by one block of the first kernel.
+__device__ __forceinline__ void begin_step(const Plan& p)
+{
+    if (threadIdx.x == 0) {
+        p.ctl->recheck_count = 0;
+        p.ctl->overflow = 0;
+        p.ctl->refined_count = 0;
+        p.ctl->pool_used = 0;
+    }
+    for (uint32_t b = threadIdx.x; b < p.nboxes; b += blockDim.x) p.box_vmax[b] = 0u;
+}
 
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* lds, uint32_t& total)
 {
@@ -477,11 +496,10 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_reduce(Plan p)
     uint32_t total;
     block_exclusive_scan(s, lds, total);
     if (threadIdx.x == 0) p.partial[blockIdx.x] = total;
+    if (blockIdx.x == 0) begin_step(p);
 }
 
-// One block of 1024 threads scans the block sums in place.  It also starts
-// the step's device-side bookkeeping (recheck list, overflow pair list and
-// the FP32 screen's per-box velocity bounds).
+// One block of 1024 threads scans the block sums in place.
 __global__ __launch_bounds__(1024) void k_scan_partials(Plan p)
 {
     __shared__ uint32_t lds[1024 / 64 + 1];
@@ -494,32 +512,11 @@ __global__ __launch_bounds__(1024) void k_scan_partials(Plan p)
         if (k < p.nblk_scan) p.partial[k] = carry + e;
         carry += total;
     }
-    if (threadIdx.x == 0) {
-        p.ctl->recheck_count = 0;
-        p.ctl->overflow = 0;
-        p.ctl->refined_count = 0;
-        p.ctl->pool_used = 0;
-    }
-    for (uint32_t b = threadIdx.x; b < p.nboxes; b += blockDim.x) p.box_vmax[b] = 0u;
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_scan_down(Plan p)
+// The starts st of the eight cells from base on written, their counts cleared.
+__device__ __forceinline__ void store_starts(const Plan& p, uint32_t base, const uint32_t st[kScanItems])
 {
-    __shared__ uint32_t lds[kScanBlock / 64 + 1];
-    const uint32_t base = blockIdx.x * (uint32_t)kScanTile + threadIdx.x * kScanItems;
-    uint32_t v[kScanItems];
-    load_counts(p, base, v);
-    uint32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) s += v[k];
-    uint32_t total;
-    uint32_t run = block_exclusive_scan(s, lds, total) + p.partial[blockIdx.x];
-    uint32_t st[kScanItems];
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        st[k] = run;
-        run += v[k];
-    }
     if (base + kScanItems <= p.C) {
         // 32-byte aligned runs of eight cells (the arrays are 256-byte aligned)
         uint4* sp = reinterpret_cast<uint4*>(p.start + base);
@@ -538,6 +535,87 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_down(Plan p)
             }
         }
     }
+}
+
+// The whole scan in one block: four tiles of eight cells per thread, all
+// loaded at once; the 64 wave totals are scanned by one wave.
+__global__ __launch_bounds__(1024) void k_scan_one(Plan p)
+{
+    constexpr uint32_t kTiles = kOneScanCells / (1024u * kScanItems);
+    static_assert(kTiles * 16u == 64u, "one wave total per lane");
+    __shared__ uint32_t wt[64];
+    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+    uint32_t v[kTiles][kScanItems], x[kTiles], sum[kTiles];
+#pragma unroll
+    for (uint32_t t = 0; t < kTiles; ++t) load_counts(p, (t * 1024u + threadIdx.x) * kScanItems, v[t]);
+#pragma unroll
+    for (uint32_t t = 0; t < kTiles; ++t) {
+        sum[t] = 0;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) sum[t] += v[t][k];
+        x[t] = sum[t];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(x[t], off, 64);
+            if (lane >= (uint32_t)off) x[t] += y;
+        }
+        if (lane == 63u) wt[t * 16u + wid] = x[t];
+    }
+    __syncthreads();
+    if (wid == 0) {
+        const uint32_t w = wt[lane];
+        uint32_t e = w;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(e, off, 64);
+            if (lane >= (uint32_t)off) e += y;
+        }
+        wt[lane] = e - w;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t t = 0; t < kTiles; ++t) {
+        uint32_t run = wt[t * 16u + wid] + x[t] - sum[t];
+        uint32_t st[kScanItems];
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            st[k] = run;
+            run += v[t][k];
+        }
+        store_starts(p, (t * 1024u + threadIdx.x) * kScanItems, st);
+    }
+    if (threadIdx.x == 0) p.start[p.C] = p.N;
+    begin_step(p);
+}
+
+// SUMS: the block sums are as k_scan_reduce left them (else scanned).
+template <bool SUMS>
+__global__ __launch_bounds__(kScanBlock) void k_scan_down(Plan p)
+{
+    __shared__ uint32_t lds[kScanBlock / 64 + 1];
+    uint32_t before = 0;
+    if (SUMS) {
+        uint32_t a = 0;
+        for (uint32_t k = threadIdx.x; k < blockIdx.x; k += blockDim.x) a += p.partial[k];
+        block_exclusive_scan(a, lds, before);
+    } else {
+        before = p.partial[blockIdx.x];
+    }
+    const uint32_t base = blockIdx.x * (uint32_t)kScanTile + threadIdx.x * kScanItems;
+    uint32_t v[kScanItems];
+    load_counts(p, base, v);
+    uint32_t s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) s += v[k];
+    uint32_t total;
+    uint32_t run = block_exclusive_scan(s, lds, total) + before;
+    uint32_t st[kScanItems];
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        st[k] = run;
+        run += v[k];
+    }
+    store_starts(p, base, st);
     if (blockIdx.x == 0 && threadIdx.x == 0) p.start[p.C] = p.N;
     if (p.adapt_L > 0) {
         // adaptive bins: this step's split level of every cell from its count;
@@ -801,7 +879,7 @@ __global__ void k_scatter(Plan p)
     __shared__ unsigned long long wv2[16];
     if (F32) {
         if (__ballot(outside) && (threadIdx.x & 63) == 0) atomicOr(&p.ctl->overflow, 1u);
-        // per-block maximum of |fl32(v_k)|; k_vmax_reduce folds the blocks of each box
+        // per-block maximum of |fl32(v_k)|; fold_partials takes those of each box
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) vm = fmaxf(vm, __shfl_xor(vm, off, 64));
         if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = vm;
@@ -810,7 +888,7 @@ __global__ void k_scatter(Plan p)
         // adaptive time step: max |v|^2 per box.  Non-negative doubles order
         // like their bit patterns, so the maximum is exact in any order.  The
         // block folds its particles that share the box of its first particle
-        // (k_adapt_dt reads the partial); any others go to their box directly.
+        // (fold_partials reads the partial); any others go to their box directly.
         const uint32_t first = blockIdx.x * blockDim.x;
         const uint32_t b0 = p.boxidx ? p.boxidx[first] : 0u;
         unsigned long long q = 0ull;
@@ -858,66 +936,61 @@ __device__ __forceinline__ double adaptive_dt(const Plan& p, const BoxDev& B, un
     return dt;
 }
 
-// This step's time step of every box (one block per box), from the maxima
-// k_scatter gathered: dt = min(cap, (C dx) / sqrt(max |v|^2)) under the
-// adaptive rule, the configured dt otherwise; also the simulated time.
-__global__ __launch_bounds__(256) void k_adapt_dt(Plan p)
+// Maxima of a box's scatter blocks k = first + part, first + part + stride, ...
+// (a block of 256 threads): |v|^2 over the blocks whose first particle lies in
+// the box, and |fl32(v_k)| over all blocks that touch it.  Thread 0 gets them.
+__device__ __forceinline__ void fold_partials(const Plan& p, const BoxDev& B, uint32_t part, uint32_t stride,
+                                              unsigned long long& v2, float& vm)
 {
-    __shared__ unsigned long long red[256];
-    const uint32_t b = blockIdx.x;
-    BoxDev& B = p.boxes[b];
-    unsigned long long m = 0ull;
-    if (p.dt_rule == KMC_DT_ADAPTIVE && B.n > 0) {
-        // the scatter blocks whose first particle lies in this box
-        const uint32_t blk = (uint32_t)p.block;
-        const uint32_t k0 = (B.poff + blk - 1) / blk, k1 = (B.poff + B.n - 1) / blk;
-        for (uint32_t k = k0 + threadIdx.x; k <= k1; k += blockDim.x) {
-            const unsigned long long v = p.v2_part[k];
-            m = v > m ? v : m;
-        }
-    }
-    red[threadIdx.x] = m;
-    __syncthreads();
-    for (uint32_t w = blockDim.x / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] = red[threadIdx.x + w] > red[threadIdx.x] ? red[threadIdx.x + w] : red[threadIdx.x];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        if (p.dt_rule == KMC_DT_ADAPTIVE) {
-            const unsigned long long o = p.box_v2[b];
-            const unsigned long long mm = o > red[0] ? o : red[0];
-            p.box_v2[b] = 0ull;
-            const double dt = adaptive_dt(p, B, mm);
-            B.dt = dt;
-            B.dt_32 = (float)dt;
-        }
-        B.time = B.time + B.dt;
-    }
-}
-
-// Per-box maximum of the scatter blocks' partials: kVmaxSplit blocks per
-// box, one atomic each (non-negative floats order like their bit patterns).
-constexpr uint32_t kVmaxSplit = 32;
-
-__global__ __launch_bounds__(256) void k_vmax_reduce(Plan p)
-{
-    __shared__ float red[256];
-    const uint32_t b = blockIdx.x / kVmaxSplit, part = blockIdx.x % kVmaxSplit;
-    const BoxDev& B = p.boxes[b];
-    float vm = 0.f;
+    __shared__ unsigned long long r2[4];
+    __shared__ float rv[4];
+    v2 = 0ull;
+    vm = 0.f;
     if (B.n > 0) {
         const uint32_t blk = (uint32_t)p.block;
-        const uint32_t first = B.poff / blk, last = (B.poff + B.n - 1) / blk;
-        for (uint32_t k = first + part * blockDim.x + threadIdx.x; k <= last; k += kVmaxSplit * blockDim.x)
-            vm = fmaxf(vm, p.vmax_part[k]);
+        const uint32_t first = B.poff / blk, last = (B.poff + B.n - 1) / blk, own = (B.poff + blk - 1) / blk;
+        for (uint32_t k = first + part; k <= last; k += stride) {
+            if (p.precision == KMC_FP32_SCREEN) vm = fmaxf(vm, p.vmax_part[k]);
+            if (p.dt_rule == KMC_DT_ADAPTIVE && k >= own) {
+                const unsigned long long v = p.v2_part[k];
+                v2 = v > v2 ? v : v2;
+            }
+        }
     }
-    red[threadIdx.x] = vm;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(v2, off, 64);
+        v2 = o > v2 ? o : v2;
+        vm = fmaxf(vm, __shfl_xor(vm, off, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        r2[threadIdx.x >> 6] = v2;
+        rv[threadIdx.x >> 6] = vm;
+    }
     __syncthreads();
-    for (uint32_t w = blockDim.x / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
-        __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < 4; ++w) {
+            v2 = r2[w] > v2 ? r2[w] : v2;
+            vm = fmaxf(vm, rv[w]);
+        }
+}
+
+// Boxes of many scatter blocks: kVmaxSplit blocks per box fold the partials
+// first, one atomic each (non-negative floats order like their bit patterns).
+// One block alone took 62 us for the 3.9e4 partials of 1e7 particles.
+constexpr uint32_t kVmaxSplit = 32;
+constexpr uint32_t kFoldAlone = 2048;   // scatter blocks of a step that need no help
+
+__global__ __launch_bounds__(256) void k_fold_partials(Plan p)
+{
+    const uint32_t b = blockIdx.x / kVmaxSplit, part = blockIdx.x % kVmaxSplit;
+    unsigned long long v2;
+    float vm;
+    fold_partials(p, p.boxes[b], part * blockDim.x + threadIdx.x, kVmaxSplit * blockDim.x, v2, vm);
+    if (threadIdx.x == 0) {
+        if (vm > 0.f) atomicMax(&p.box_vmax[b], __float_as_uint(vm));
+        if (v2) atomicMax(&p.box_v2[b], v2);
     }
-    if (threadIdx.x == 0 && red[0] > 0.f) atomicMax(&p.box_vmax[b], __float_as_uint(red[0]));
 }
 
 // --------------------------------------------------------------------------
@@ -1355,7 +1428,7 @@ struct PolF64 {
 //
 // The bounds depend on how far a group's neighbourhood reaches along x.  A
 // screened group of at most span_cells(c) cells uses the thresholds of class
-// c (k_screen_bounds computes each class per box), so dense rows keep tight
+// c (k_step_setup computes each class per box), so dense rows keep tight
 // bounds while the lanes of a sparse row (under one particle per cell),
 // hundreds of cells apart, share looser ones; the search splits rows wider
 // than the last class.
@@ -1545,13 +1618,36 @@ __device__ __forceinline__ bool screen_class(const Plan& p, const BoxDev& B, uin
     return __ballot(safe) == ~0ull;
 }
 
-// One block per box, one wave per span class.
-__global__ __launch_bounds__(64 * kSpanClasses) void k_screen_bounds(Plan p)
+// What a step needs to know of every box before its search (one block per
+// box, one wave per span class): the time step under the adaptive rule, dt =
+// min(cap, (C dx) / sqrt(max |v|^2)), and the FP32 screen's thresholds.
+// ALONE: the scatter blocks' partials are folded here (else by
+// k_fold_partials).
+template <bool ALONE>
+__global__ __launch_bounds__(64 * kSpanClasses) void k_step_setup(Plan p)
 {
+    static_assert(kSpanClasses == 4, "fold_partials works in four waves");
+    __shared__ float vmax;
     const uint32_t b = blockIdx.x;
-    const double V = (double)__uint_as_float(p.box_vmax[b]) * (1.0 + 3.0 * 0x1.0p-24);
+    BoxDev& B = p.boxes[b];
+    unsigned long long v2 = 0ull;
+    float vm = 0.f;
+    if (ALONE) fold_partials(p, B, threadIdx.x, blockDim.x, v2, vm);
+    if (threadIdx.x == 0) {
+        if (p.dt_rule == KMC_DT_ADAPTIVE) {
+            const unsigned long long o = p.box_v2[b];
+            p.box_v2[b] = 0ull;
+            const double dt = adaptive_dt(p, B, o > v2 ? o : v2);
+            B.dt = dt;
+            B.dt_32 = (float)dt;
+        }
+        vmax = ALONE ? vm : __uint_as_float(p.box_vmax[b]);
+    }
+    __syncthreads();   // (the box's dt, too)
+    if (p.precision != KMC_FP32_SCREEN) return;
+    const double V = (double)vmax * (1.0 + 3.0 * 0x1.0p-24);
     const int lane = threadIdx.x & 63;
-    const bool safe = screen_class(p, p.boxes[b], b, (int)(threadIdx.x >> 6), V, lane, true);
+    const bool safe = screen_class(p, B, b, (int)(threadIdx.x >> 6), V, lane, true);
     if (!safe && lane == 0) atomicOr(&p.ctl->overflow, 1u);
 }
 
@@ -1892,7 +1988,7 @@ void k_search_half(Plan p)
     // statistics: pairs the search kept, counted at both particles
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
-    if (lane == 0 && c) atomicAdd(&p.acc[blockIdx.x % kAccLanes].cand, 2ull * (unsigned long long)c);
+    if (lane == 0 && c) atomicAdd(&p.acc[blockIdx.x % p.acc_lanes].cand, 2ull * (unsigned long long)c);
 }
 
 // The FP64 search of one particle by a whole wave: lanes 0..26 look up one
@@ -2100,7 +2196,7 @@ __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, t
         uint64_t c = Pol::kScreen ? best.screened : best.accepted;
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
-        if (lane == 0 && c) atomicAdd(&p.acc[blockIdx.x % kAccLanes].cand, (unsigned long long)c);
+        if (lane == 0 && c) atomicAdd(&p.acc[blockIdx.x % p.acc_lanes].cand, (unsigned long long)c);
     }
     if constexpr (Pol::kScreen) {
         // particles with more deferred pairs than slots
@@ -2129,37 +2225,44 @@ void k_search_full(Plan p)
     }
 }
 
-// The re-search of single particles: its blocks of four waves, and the share
-// of the particles (one in kRecheckShare) above which the whole-step search is
+// The share of the particles to re-search (one in kRecheckShare) above which the whole-step search is
 // the faster way to the same partners (measured on 1e6 particles of one speed,
 // three per cell: 1.5 ns a particle re-searched, 0.24 ns a particle of the
 // whole step; the crossing is at one in six).
-constexpr uint32_t kRecheckBlocks = 1024;
 constexpr uint32_t kRecheckShare = 6;
+constexpr uint32_t kFallbackBlocks = 4096;
 
 // Whether this step's partners come from the whole-step search: its flag is
 // set, or the re-search has too many particles.
 __device__ __forceinline__ bool whole_step(const Plan& p)
 {
-    return p.ctl->overflow != 0u || p.ctl->recheck_count > p.N / kRecheckShare + 4u * kRecheckBlocks;
+    return p.ctl->overflow != 0u || p.ctl->recheck_count > p.N / kRecheckShare + kFallbackBlocks;
 }
 
 // Whole-step FP64 search, by the full-neighbourhood organisation, when the
 // recheck list overflowed or holds a large share of the particles or, under
 // the FP32 screen, a particle lies outside its box's grid or a box's scales
-// leave the screen's safe range.  A fixed grid of waves that exits at once
-// unless the step needs it, and otherwise takes the tiles in turn.
-constexpr uint32_t kFallbackBlocks = 4096;
+// leave the screen's safe range; otherwise the re-search of the listed
+// particles, one wave each.  A fixed grid of waves that exits at once when a
+// step needs neither.
 // Waves that walk the list of split cells (adaptive bins).
 constexpr uint32_t kAdaptPrepBlocks = 4096;
 
 template <class Pol>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Pol::kFullWaves)))
-void k_fallback_full(Plan p)
+void k_research(Plan p)
 {
     __shared__ typename Pol::Lds lds;
     __shared__ uint32_t lid[Pol::W];
-    if (!whole_step(p)) return;
+    if (!whole_step(p)) {
+        const uint32_t n = p.ctl->recheck_count;   // (at most recheck_cap here)
+        for (uint32_t k = blockIdx.x; k < n; k += gridDim.x) {
+            const uint32_t i = p.recheck[k];
+            const int32_t b = search_one64_wave(p, i);
+            if (threadIdx.x == 0) p.partner[i] = b;
+        }
+        return;
+    }
     const uint32_t ntiles = (p.N + 63u) / 64u;
     for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) search_full_tile<Pol, false>(p, t, lds, lid, nullptr);
 }
@@ -2506,7 +2609,7 @@ __device__ __forceinline__ void search_adapt_tile(const Plan& p, uint32_t tile, 
     if (STATS) {
 #pragma unroll
         for (int sft = 32; sft > 0; sft >>= 1) nstat += __shfl_xor(nstat, sft, 64);
-        if (lane == 0 && nstat) atomicAdd(&p.acc[blockIdx.x % kAccLanes].cand, (unsigned long long)nstat);
+        if (lane == 0 && nstat) atomicAdd(&p.acc[blockIdx.x % p.acc_lanes].cand, (unsigned long long)nstat);
     }
 }
 
@@ -2520,7 +2623,7 @@ void k_search_adapt(Plan p)
 }
 
 // The whole-step FP64 search of the particles k_search_adapt takes (see
-// k_fallback_full).
+// k_research).
 template <class Pol>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Pol::kFullWaves)))
 void k_fallback_adapt(Plan p)
@@ -2675,7 +2778,7 @@ __global__ __launch_bounds__(64) void k_search_direct(Plan p)
     if (i < p.N && u == 0) p.partner[i] = best.j;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
-    if (lane == 0 && c) atomicAdd(&p.acc[blockIdx.x % kAccLanes].cand, (unsigned long long)c);
+    if (lane == 0 && c) atomicAdd(&p.acc[blockIdx.x % p.acc_lanes].cand, (unsigned long long)c);
 }
 
 // Wave-aggregated append of this lane's particle to the FP64 recheck list
@@ -2724,22 +2827,6 @@ __global__ __launch_bounds__(256) void k_finish(Plan p)
     }
     push_recheck(p, i, cnt > (uint32_t)kSlots);
     if (valid) p.partner[i] = best;
-}
-
-// FP64 re-search of the particles whose candidate lists overflowed, one
-// wave per particle.
-__global__ void k_recheck64(Plan p)
-{
-    if (whole_step(p)) return;   // the whole-step FP64 search follows
-    const uint32_t cnt = p.ctl->recheck_count;
-    const uint32_t n = cnt < p.recheck_cap ? cnt : p.recheck_cap;
-    const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
-    for (uint32_t k = wave; k < n; k += nwaves) {
-        const uint32_t i = p.recheck[k];
-        const int32_t b = search_one64_wave(p, i);
-        if ((threadIdx.x & 63) == 0) p.partner[i] = b;
-    }
 }
 
 // --------------------------------------------------------------------------
@@ -2935,22 +3022,20 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(K ? 1 : 8)
     if ((threadIdx.x & 63) == 0 && lm) atomicAdd(&p.ctl->absorbed_total, (unsigned long long)__popcll(lm));
     block_sum2(my_np, my_dig, lds);
     if (threadIdx.x == 0 && my_np != 0) {
-        StepAcc& a = p.acc[blockIdx.x % kAccLanes];
+        StepAcc& a = p.acc[blockIdx.x % p.acc_lanes];
         atomicAdd(&a.np, (unsigned long long)my_np);
         atomicAdd(&a.dig, (unsigned long long)my_dig);
     }
 }
 
-// End of step (one block of kAdvanceThreads): fold this step's partial sums
-// into its history row and the running candidate count, clear them, and
-// advance the step counters.
-constexpr uint32_t kAdvanceThreads = 1024;
-
-__global__ __launch_bounds__(kAdvanceThreads) void k_advance(Plan p)
+// End of step (one block): fold this step's partial sums into its history row
+// and the running candidate count, clear them, and advance the boxes' time
+// and the step counters.
+__global__ __launch_bounds__(1024) void k_advance(Plan p)
 {
     __shared__ uint64_t lds[32];
     uint64_t np = 0, dig = 0, cand = 0, z = 0;
-    for (uint32_t k = threadIdx.x; k < (uint32_t)kAccLanes; k += blockDim.x) {
+    for (uint32_t k = threadIdx.x; k < p.acc_lanes; k += blockDim.x) {
         StepAcc& a = p.acc[k];
         np += a.np;
         dig += a.dig;
@@ -2959,6 +3044,7 @@ __global__ __launch_bounds__(kAdvanceThreads) void k_advance(Plan p)
         a.dig = 0;
         a.cand = 0;
     }
+    for (uint32_t b = threadIdx.x; b < p.nboxes; b += blockDim.x) p.boxes[b].time = p.boxes[b].time + p.boxes[b].dt;
     block_sum2(np, dig, lds);
     __syncthreads();
     block_sum2(cand, z, lds);
@@ -3060,9 +3146,17 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
     auto mark = [&](int k) { if (ev) (void)hipEventRecord(ev[k], s); };
     mark(KMC_PHASE_BIN);   // binning runs at the end of the previous step (k_resolve) or in kmc_init
     mark(KMC_PHASE_SCAN);
-    k_scan_reduce<<<p.nblk_scan, kScanBlock, 0, s>>>(p);
-    k_scan_partials<<<1, 1024, 0, s>>>(p);
-    k_scan_down<<<p.nblk_scan, kScanBlock, 0, s>>>(p);
+    if (p.C <= kOneScanCells && p.adapt_L == 0) {
+        k_scan_one<<<1, 1024, 0, s>>>(p);
+    } else {
+        k_scan_reduce<<<p.nblk_scan, kScanBlock, 0, s>>>(p);
+        if (p.nblk_scan <= kSumBlocks) {
+            k_scan_down<true><<<p.nblk_scan, kScanBlock, 0, s>>>(p);
+        } else {
+            k_scan_partials<<<1, 1024, 0, s>>>(p);
+            k_scan_down<false><<<p.nblk_scan, kScanBlock, 0, s>>>(p);
+        }
+    }
     if (p.adapt_L > 0 && p.N > 0) {
         // adaptive bins: split cells' leaf tables, then every particle's rank in its leaf
         k_refined_prep<<<kAdaptPrepBlocks, 64, 0, s>>>(p);
@@ -3074,13 +3168,16 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
         if (p.precision == KMC_FP32_SCREEN) k_scatter<true><<<gN, b, 0, s>>>(p);
         else k_scatter<false><<<gN, b, 0, s>>>(p);
     }
-    k_adapt_dt<<<p.nboxes, 256, 0, s>>>(p);
-    mark(KMC_PHASE_SEARCH);
     const uint32_t gW = blocks_for(p.N, 64);
-    if (p.precision == KMC_FP32_SCREEN) {
-        k_vmax_reduce<<<p.nboxes * kVmaxSplit, 256, 0, s>>>(p);
-        k_screen_bounds<<<p.nboxes, 64 * kSpanClasses, 0, s>>>(p);
+    if (p.precision == KMC_FP32_SCREEN || p.dt_rule == KMC_DT_ADAPTIVE) {
+        if (p.nblk_part <= kFoldAlone) {
+            k_step_setup<true><<<p.nboxes, 64 * kSpanClasses, 0, s>>>(p);
+        } else {
+            k_fold_partials<<<p.nboxes * kVmaxSplit, 256, 0, s>>>(p);
+            k_step_setup<false><<<p.nboxes, 64 * kSpanClasses, 0, s>>>(p);
+        }
     }
+    mark(KMC_PHASE_SEARCH);
     if (ev) (void)hipEventRecord(ev[KMC_PHASE_COUNT + 1], s);   // search kernel alone
     const int32_t dg = p.direct;
     const bool full = p.search_mode == KMC_SEARCH_FULL || dg > 0;
@@ -3112,11 +3209,12 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
         k_finish<<<blocks_for(p.N, 256), 256, 0, s>>>(p);
     }
     mark(KMC_PHASE_RECHECK);
-    if (p.N > 0 && !full) k_recheck64<<<kRecheckBlocks, 256, 0, s>>>(p);
-    // (the full search raises no overflow; the FP32 sorted copy may)
+    // (the full search lists nothing; the FP32 sorted copy may still ask for
+    // the whole-step search)
     if (p.N > 0 && dg == 0 && (!full || p.precision == KMC_FP32_SCREEN)) {
-        if (p.nspecies > 0) k_fallback_full<PolF64<true>><<<kFallbackBlocks, 64, 0, s>>>(p);
-        else k_fallback_full<PolF64<false>><<<kFallbackBlocks, 64, 0, s>>>(p);
+        const uint32_t g = gW < kFallbackBlocks ? gW : kFallbackBlocks;
+        if (p.nspecies > 0) k_research<PolF64<true>><<<g, 64, 0, s>>>(p);
+        else k_research<PolF64<false>><<<g, 64, 0, s>>>(p);
         if (p.adapt_L > 0) {
             if (p.nspecies > 0) k_fallback_adapt<PolF64<true>><<<kFallbackBlocks, 64, 0, s>>>(p);
             else k_fallback_adapt<PolF64<false>><<<kFallbackBlocks, 64, 0, s>>>(p);
@@ -3127,7 +3225,7 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
         if (p.nspecies > 0) k_resolve<true><<<gN, b, b * sizeof(P64), s>>>(p);
         else k_resolve<false><<<gN, b, b * sizeof(P64), s>>>(p);
     }
-    k_advance<<<1, kAdvanceThreads, 0, s>>>(p);
+    k_advance<<<1, p.acc_lanes, 0, s>>>(p);
     mark(KMC_PHASE_COUNT);
     return hipGetLastError();
 }

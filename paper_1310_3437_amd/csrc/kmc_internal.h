@@ -134,6 +134,7 @@ struct Plan {
     unsigned long long* box_v2;    // adaptive dt: per box, max |v|^2 of the other particles
     uint32_t N, C, nboxes, H;
     uint32_t nblk_scan;
+    uint32_t acc_lanes;            // accumulators in use (a multiple of 64, at most kAccLanes)
     uint32_t recheck_cap;
     uint64_t seed;
     int32_t precision, kinematics, block;
