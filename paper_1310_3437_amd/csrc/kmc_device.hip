@@ -7,6 +7,8 @@
 // floating-point expression that decides a result is written in the
 // definition's order so that results are bit-identical to any other
 // IEEE-754 binary64 implementation of the same definition.
+#include <type_traits>
+
 #include "kmc_internal.h"
 
 namespace kmc {
@@ -1111,12 +1113,35 @@ struct Found {
     uint32_t w;   // image shift of pair k in bits 6k..6k+5: (wx+1) | (wy+1) << 2 | (wz+1) << 4;
                   // bit 31: the lane lost a pair in the current chunk
     int n;
+    __device__ __forceinline__ void clear(Extra* e, uint32_t* slots)
+    {
+        extra = e;
+        sj = slots;
+        n = 0;
+        w = kNoImage * 0x41041u;   // no image in every slot
+    }
+    __device__ __forceinline__ void keep(uint32_t jj, uint32_t wcode)
+    {
+        sj[64 * n] = jj;
+        if (wcode != kNoImage) w ^= (wcode ^ kNoImage) << (6 * n);   // (the same for the whole wave)
+        ++n;
+    }
+    // Consecutive candidates j and j + 1, of which at least one is kept (the
+    // usual case, one of them with slots to spare, has no branches inside).
+    __device__ __forceinline__ void add2(bool k0, bool k1, uint32_t j, uint32_t wcode)
+    {
+        if (n + 1 < kReg) {
+            keep(k0 ? j : j + 1u, wcode);
+            if (k0 & k1) keep(j + 1u, wcode);
+        } else {
+            if (k0) add(j, wcode);
+            if (k1) add(j + 1u, wcode);
+        }
+    }
     __device__ __forceinline__ void add(uint32_t jj, uint32_t wcode)
     {
         if (n < kReg) {
-            sj[64 * n] = jj;
-            w |= wcode << (6 * n);
-            ++n;
+            keep(jj, wcode);
             return;
         }
         const uint32_t t = atomicAdd(&extra->n, 1u);
@@ -1338,14 +1363,14 @@ struct PolF64 {
         uint32_t row;   // K: kMaxKinds * own kind
     };
     using Group = NoGroup;
-    __device__ static void begin_group(const Plan&, const BoxDev&, Own&, Group&, int, int, int, int, int, uint32_t,
+    __device__ static void begin_group(const Lds&, const Plan&, const BoxDev&, Own&, Group&, int, int, int, int, int, uint32_t,
                                        bool) {}
     // per-group LDS tables, written before the group's first staging barrier
     __device__ static void group_lds(Lds& l, const Plan& p, uint32_t, int lane)
     {
         if (K) l.d2[lane] = p.sp_D2[lane];
     }
-    __device__ static void load_own(const Plan& p, uint32_t i, Own& o, double& x, double& y, double& z)
+    __device__ static void load_own(Lds&, const Plan& p, uint32_t i, Own& o, double& x, double& y, double& z)
     {
         o.me = p.B[i];
         o.row = K ? (uint32_t)p.spB[i] * (uint32_t)kMaxKinds : 0u;
@@ -1488,7 +1513,7 @@ __device__ __forceinline__ void screen_bound(double u, const double er[3], const
     const double s3 = 1.7320508075688774;     // >= sqrt(3)
     const double b0 = eg * (SRE + SE), b1 = kap * (SE + g3 * SRE);
     const double g0 = 3.0 * eg * eg, g1 = 2.0 * s3 * kap * eg, g2c = g3 * kap * kap;
-    const double Et = Err + u * D2 + u * (RR + D2);
+    const double Et = Err + u * D2 + 6.0 * u * (RR + D2);
     const double Tm = RR + D2 + Et;
     const double A2 = 2.0 * Rn * kap * b1 + b1 * b1 + u * RR * kap * kap * (1.0 + g3) * (1.0 + g3) + Tm * g2c +
                       Et * (1.0 + g2c) + 128.0 * u64 * (RR + D2) * kap * kap;
@@ -1510,7 +1535,7 @@ __device__ __forceinline__ void screen_bound(double u, const double er[3], const
 __device__ __forceinline__ float fold_kD2(double D2_32, double tc1, double RRb)
 {
     const double u = 0x1.0p-24;
-    return tc1 > 0.0 ? (float)((D2_32 + tc1 + 2.0 * u * (RRb + D2_32 + tc1)) * (1.0 + 2e-6)) : (float)D2_32;
+    return tc1 > 0.0 ? (float)((D2_32 + tc1 + 6.0 * u * (RRb + D2_32 + tc1)) * (1.0 + 2e-6)) : (float)D2_32;
 }
 
 // Returns the g2 slopes tt1 and tc1 and RRb (for fold_kD2 with other D2 values of the box).  With
@@ -1538,10 +1563,11 @@ __device__ __forceinline__ void screen_thresholds(const BoxDev& B, const double 
     g.tc0 = (float)t[4];
     // Folded constants, rounded up (the factor 1 + 2e-6 exceeds every rounding
     // here).  m2: -b - kdt g2 <= -b - (dt + tt1) g2 for kdt >= dt + tt1, and the
-    // screen's one rounding of the FMA is monotone.  m3: replacing the
-    // subtrahend D2 of the screen's fl(|r|^2 - D2) by kD2 lowers that value by
-    // at least kD2 - D2 - u (|fl(|r|^2) - kD2| + |fl(|r|^2) - D2|), which is >= tc1
-    // when kD2 (1 - u) >= D2 (1 + u) + tc1 + 2 u RRb with RRb >= fl(|r|^2).
+    // screen's one rounding of the FMA is monotone.  m3: the screen sums
+    // |r|^2 - D2 in three FMAs that start from -D2, each with an error of at most
+    // u (|r|^2 + D2); replacing D2 by kD2 lowers the sum by at least kD2 - D2 less
+    // the errors of both, which is >= tc1 when kD2 (1 - 3 u) >= D2 (1 + 3 u) +
+    // tc1 + 6 u RRb with RRb >= |r|^2.
     // Without bounds (guard 0) the constants are the criteria's own.
     const double dt32 = (double)B.dt_32;
     RRb = 0.0;
@@ -1560,12 +1586,23 @@ __device__ __forceinline__ void screen_thresholds(const BoxDev& B, const double 
     // certain to be acceptable when it passes the tests with the bounds on the
     // other side (kdm <= dt - tt1, g2 above its own error), and its key is
     // then at most |r|^2 + tc1 - (b^2 - tc0) / g2, which has to be below D2
-    // (taken from kD2: D2 >= (1 - 5e-6) kD2 - kc); the factor 1 + 1e-6 on
-    // |r|^2 exceeds the rounding of that expression (its terms are at most
-    // |r|^2, its other error tc1).  In the same way |r|^2 (1 - 1e-6) - (b^2 + tc0) / g2
-    // is no larger than the K at which the pair would fail the folded test.
-    g.kc = (float)((t[5] + 2.0 * u * (RRb + t[5])) * (1.0 + 4e-6));
-    g.tcu = (float)(2.0 * t[5]);
+    // (taken from kD2: D2 >= (1 - 5e-6) kD2 - kc).  The factor 1 + 1e-6 on |r|^2
+    // exceeds the rounding of the quotient (b^2 / g2 is at most |r|^2), and a
+    // second tc1 (tcu is twice tc1) that of |r|^2, which is summed as (|r|^2 -
+    // kD2) + kD2 with errors of at most 6 u (RRb + kD2).  In the same way
+    // |r|^2 (1 - 1e-6) - tcu - (b^2 + tc0) / g2 is no larger than the K at which the
+    // pair would fail the folded test.
+    g.kc = (float)((t[5] + 6.0 * u * (RRb + t[5])) * (1.0 + 4e-6));
+    g.tcu = (float)(2.0 * t[5] * (1.0 + 2e-6));
+    // The tests on b and m2 as one: -(g + kdt g2) <= b <= g + tb1 g2 with g the
+    // larger of tb0 and tt0 is |b + ka g2| <= g + kb g2 (ka, kb half the
+    // difference and half the sum); the factor 1 + 1e-6 on kb and g exceeds
+    // the rounding of both sides and makes the inequality strict, so that the
+    // sign bit of their difference decides.
+    g.ka = 0.5f * (g.kdt - g.tb1);
+    g.kb = 0.5f * (g.kdt + g.tb1) * 1.000001f;
+    g.kg = fmaxf(g.tb0, g.tt0) * 1.000001f;
+    g.tc = g.tc0 * 1.000001f;
     g.kdm = (float)((dt32 - t[3]) * (1.0 - 2e-6));
     g.gmin = t[7] < 0.5 ? (float)(2.0 * t[6] * (1.0 + 2e-6)) : __builtin_inff();
 }
@@ -1604,9 +1641,9 @@ __device__ __forceinline__ bool screen_class(const Plan& p, const BoxDev& B, uin
     ScreenBounds g;
     screen_thresholds(B, P, V, p.guard, g, tt1, tc1, RRb);
     if (store && lane == 0) p.box_sb[(size_t)b * kSpanClasses + c] = g;
-    const float th[9] = {g.tb0, g.tb1, g.tt0, (float)tt1, g.tc0, (float)tc1, g.kdt, g.kD2, g.kc};
+    const float th[11] = {g.tb0, g.tb1, g.tt0, (float)tt1, g.tc0, (float)tc1, g.kdt, g.kD2, g.kc, g.kb, g.kg};
 #pragma unroll
-    for (int k = 0; k < 9; ++k) safe = safe && isfinite(th[k]) && (double)fabsf(th[k]) * g2max < big;
+    for (int k = 0; k < 11; ++k) safe = safe && isfinite(th[k]) && (double)fabsf(th[k]) * g2max < big;
     if (p.nspecies > 0) {
         // the folded constant of each pair of kinds, from the pair's own D2
         // rounded to FP32 (entries of absent kinds are never read)
@@ -1653,39 +1690,59 @@ __global__ __launch_bounds__(64 * kSpanClasses) void k_step_setup(Plan p)
 
 // K: particles of several kinds (the screen's folded D2 constant of each
 // pair of kinds from a per-box table in LDS); otherwise the box's constant.
+// a < 0 and b < 0 (neither is NaN), by their sign bits: one comparison.  FP32
+// sums, products and logic on vector registers issue at twice the rate of
+// comparisons and of anything with a scalar operand here (measured 1.5 to 1.75
+// against 0.9 instructions per CU and cycle), so a test that costs one
+// comparison instead of three is worth the subtraction and the AND (with the
+// 24-byte records and the shorter path of a kept pair: full search of 256
+// boxes 1.53 -> 1.42 ms, of 1e7 particles of one speed 2.39 -> 2.30).
+__device__ __forceinline__ bool both_negative(float a, float b)
+{
+    return (int)(__float_as_uint(a) & __float_as_uint(b)) < 0;
+}
+
 template <bool K, class T = TileF32_0>
 struct PolF32 {
-    static constexpr int W = T::W;
+    static constexpr int W = K ? T::W * 3 / 4 : T::W;   // (with kinds, 24 waves would not fit a CU's LDS)
     static constexpr bool kScreen = true;
     static constexpr bool kKinds = K;
     static constexpr int kFlushBatch = 2;
     static constexpr bool kFlushSkipEmpty = true;
     static constexpr int kWaves = T::kWaves;
     static constexpr int kFullWaves = T::kFullWaves;
-    // A staged candidate is two 16-byte halves in two arrays: a = x, y, z
-    // relative to the group centre and vx; b = vy, vz, its kind (particle
-    // kinds only) and its sorted index (bit patterns).  With 16-byte strides
-    // consecutive records fall in distinct LDS banks (a 32-byte record would
-    // use only half of them).
+    // A staged candidate lies in two arrays: a = x, y, z relative to the group
+    // centre and vx; b = vy, vz; its kind (particles of several kinds) in a
+    // third.  Consecutive records fall in distinct LDS banks, and two of them
+    // are read by three instructions.
     struct Lds {
         float4 a[W];
-        float4 b[W];
+        float2 b[W];
+        uint8_t kind[K ? W : 1];
+        double own[3][K ? 64 : 1];
         float kd2[K ? kMaxKinds * kMaxKinds : 1];
     };
     struct Own {
         float x, y, z, vx, vy, vz;   // position relative to the current group's centre
         uint32_t row;                // K: kMaxKinds * own kind
-        double X, Y, Z;              // own FP64 position (kept: reloading it per group costs more)
+        double X, Y, Z;              // own FP64 position (kept: reloading it per group costs more;
+                                     // with kinds in LDS, where it would spill)
     };
     using Group = ScreenGroup;
     __device__ static P64 self64(const Plan& p, uint32_t i, const Own&) { return p.B[i]; }
-    __device__ static void load_own(const Plan& p, uint32_t i, Own& o, double& x, double& y, double& z)
+    __device__ static void load_own(Lds& l, const Plan& p, uint32_t i, Own& o, double& x, double& y, double& z)
     {
         const P64 m = p.B[i];
         o.vx = (float)m.vx; o.vy = (float)m.vy; o.vz = (float)m.vz;
         o.row = K ? (uint32_t)p.spB[i] * (uint32_t)kMaxKinds : 0u;
         x = m.x; y = m.y; z = m.z;
-        o.X = m.x; o.Y = m.y; o.Z = m.z;
+        if (K) {
+            l.own[0][threadIdx.x] = m.x;
+            l.own[1][threadIdx.x] = m.y;
+            l.own[2][threadIdx.x] = m.z;
+        } else {
+            o.X = m.x; o.Y = m.y; o.Z = m.z;
+        }
     }
     // per-group LDS tables, written before the group's first staging barrier
     // (sbi: the group's threshold set, box * kSpanClasses + span class)
@@ -1707,14 +1764,15 @@ struct PolF32 {
         }
         g.t = p.box_sb[sbi];
     }
-    __device__ static void begin_group(const Plan& p, const BoxDev& B, Own& o, Group& g, int cxf, int cxl,
+    __device__ static void begin_group(const Lds& l, const Plan& p, const BoxDev& B, Own& o, Group& g, int cxf, int cxl,
                                        int gcy, int gcz, int sbi, uint32_t i, bool in)
     {
         group_ctx(p, B, g, cxf, cxl, gcy, gcz, sbi);
         if (in) {
-            o.x = (float)(o.X - g.X0[0]);
-            o.y = (float)(o.Y - g.X0[1]);
-            o.z = (float)(o.Z - g.X0[2]);
+            const uint32_t t = K ? threadIdx.x : 0u;
+            o.x = (float)((K ? l.own[0][t] : o.X) - g.X0[0]);
+            o.y = (float)((K ? l.own[1][t] : o.Y) - g.X0[1]);
+            o.z = (float)((K ? l.own[2][t] : o.Z) - g.X0[2]);
         }
     }
     // FP32 copy of a candidate: image-shifted position relative to X0 and
@@ -1731,44 +1789,42 @@ struct PolF32 {
             z = z + (wz ? (double)wz * B.L[2] : 0.0);
         }
         l.a[t] = make_float4((float)(x - g.X0[0]), (float)(y - g.X0[1]), (float)(z - g.X0[2]), (float)q.vx);
-        l.b[t] = make_float4((float)q.vy, (float)q.vz, __uint_as_float(K ? (uint32_t)p.spB[j] : 0u),
-                             __uint_as_float(j));
+        l.b[t] = make_float2((float)q.vy, (float)q.vz);
+        if (K) l.kind[t] = p.spB[j];
     }
     template <bool SH>
     __device__ static void scan(const Plan& p, const Lds& l, uint32_t c0, uint32_t j0, uint32_t j1, uint32_t i,
                                 const Own& o, const BoxDev& B, const Group& g, int wx, int wy, int wz, int, int,
                                 Found& f)
     {
-        const float tb0 = g.t.tb0, tb1 = g.t.tb1, tt0 = g.t.tt0, kdt = g.t.kdt, tc0 = g.t.tc0, kD2 = g.t.kD2;
-        // the loop steps an LDS pointer only; the sorted index is read from
-        // the staged record for a kept pair alone
-        const float4* rp = l.a + (j0 - c0);
-        const float4* const re = rp + (j1 > j0 ? j1 - j0 : 0u);
-        auto test = [&](const float4& qa, const float4& qb) {
+        const float ka = g.t.ka, kb = g.t.kb, kg = g.t.kg, tc = g.t.tc, kD2 = g.t.kD2;
+        // the loop steps LDS pointers only; a kept pair's sorted index comes
+        // from the pointer
+        const float4* pa = l.a + (j0 - c0);
+        const float2* pb = l.b + (j0 - c0);
+        const float4* const pe = pa + (j1 > j0 ? j1 - j0 : 0u);
+        auto test = [&](const float4& qa, const float2& qb, uint32_t t) {
             const float rx = qa.x - o.x, ry = qa.y - o.y, rz = qa.z - o.z;
             const float gx = qa.w - o.vx, gy = qb.x - o.vy, gz = qb.y - o.vz;
+            const float kd = K ? l.kd2[o.row + l.kind[t]] : kD2;
             const float b = fmaf(rz, gz, fmaf(ry, gy, rx * gx));
             const float g2 = fmaf(gz, gz, fmaf(gy, gy, gx * gx));
-            const float rr = fmaf(rz, rz, fmaf(ry, ry, rx * rx));
-            const float kd = K ? l.kd2[o.row + __float_as_uint(qb.z)] : kD2;
-            const float mb = fmaf(-tb1, g2, b);
-            const float m2 = fmaf(-kdt, g2, -b);
-            const float m3 = fmaf(rr - kd, g2, -(b * b));
-            return (mb <= tb0) & (m2 <= tt0) & (m3 <= tc0);
+            const float rk = fmaf(rz, rz, fmaf(ry, ry, fmaf(rx, rx, -kd)));   // |r|^2 - kd
+            return both_negative(fabsf(fmaf(ka, g2, b)) - fmaf(kb, g2, kg), fmaf(rk, g2, fmaf(-b, b, -tc)));
         };
         // two records per iteration: one loop test and one branch on the
-        // kept pairs per two pair tests, and both LDS reads in flight
-        for (; rp + 1 < re; rp += 2) {
-            const float4 qa0 = rp[0], qb0 = rp[W], qa1 = rp[1], qb1 = rp[W + 1];
-            const bool k0 = test(qa0, qb0), k1 = test(qa1, qb1);
-            if (k0 | k1) {
-                if (k0) f.add(__float_as_uint(qb0.w), wcode(wx, wy, wz));
-                if (k1) f.add(__float_as_uint(qb1.w), wcode(wx, wy, wz));
-            }
+        // kept pairs per two pair tests, and all LDS reads in flight
+        for (; pa + 1 < pe; pa += 2, pb += 2) {
+            const float4 qa0 = pa[0], qa1 = pa[1];
+            const float2 qb0 = pb[0], qb1 = pb[1];
+            const uint32_t t = K ? (uint32_t)(pa - l.a) : 0u;
+            const bool k0 = test(qa0, qb0, t), k1 = test(qa1, qb1, t + 1u);
+            if (k0 | k1) f.add2(k0, k1, c0 + (uint32_t)(pa - l.a), wcode(wx, wy, wz));
         }
-        if (rp < re) {
-            const float4 qa = rp[0], qb = rp[W];
-            if (test(qa, qb)) f.add(__float_as_uint(qb.w), wcode(wx, wy, wz));
+        if (pa < pe) {
+            const float4 qa = pa[0];
+            const float2 qb = pb[0];
+            if (test(qa, qb, K ? (uint32_t)(pa - l.a) : 0u)) f.add(c0 + (uint32_t)(pa - l.a), wcode(wx, wy, wz));
         }
     }
     // full neighbourhood: every pair the screen cannot reject is decided in
@@ -1778,34 +1834,32 @@ struct PolF32 {
                                      uint32_t j1, uint32_t i, const Own& o, const BoxDev& B, const Group& g,
                                      int wx, int wy, int wz, int, int, Best& best, Deferred& d)
     {
-        const float tb0 = g.t.tb0, tb1 = g.t.tb1, tt0 = g.t.tt0, kdt = g.t.kdt, tc0 = g.t.tc0, kD2 = g.t.kD2;
+        const float ka = g.t.ka, kb = g.t.kb, kg = g.t.kg, tc = g.t.tc, kD2 = g.t.kD2;
         struct Q {
-            float b, g2, rr;
+            float b, g2, rk;   // rk: |r|^2 - kd
         };
-        auto test = [&](const float4& qa, const float4& qb, Q& q) {
+        auto test = [&](const float4& qa, const float2& qb, uint32_t t, Q& q) {
             const float rx = qa.x - o.x, ry = qa.y - o.y, rz = qa.z - o.z;
             const float gx = qa.w - o.vx, gy = qb.x - o.vy, gz = qb.y - o.vz;
+            const float kd = K ? l.kd2[o.row + l.kind[t]] : kD2;
             q.b = fmaf(rz, gz, fmaf(ry, gy, rx * gx));
             q.g2 = fmaf(gz, gz, fmaf(gy, gy, gx * gx));
-            q.rr = fmaf(rz, rz, fmaf(ry, ry, rx * rx));
-            const float kd = K ? l.kd2[o.row + __float_as_uint(qb.z)] : kD2;
-            const float mb = fmaf(-tb1, q.g2, q.b);
-            const float m2 = fmaf(-kdt, q.g2, -q.b);
-            const float m3 = fmaf(q.rr - kd, q.g2, -(q.b * q.b));
-            return (mb <= tb0) & (m2 <= tt0) & (m3 <= tc0);
+            q.rk = fmaf(rz, rz, fmaf(ry, ry, fmaf(rx, rx, -kd)));
+            return both_negative(fabsf(fmaf(ka, q.g2, q.b)) - fmaf(kb, q.g2, kg),
+                                 fmaf(q.rk, q.g2, fmaf(-q.b, q.b, -tc)));
         };
         // a kept pair: dropped if its key is certain to exceed the best so
         // far, else recorded for the end of the tile
-        auto take = [&](const float4& qb, const Q& q) {
-            const uint32_t j = __float_as_uint(qb.w);
+        auto take = [&](uint32_t j, const Q& q) {
             if (j == i) return;   // (the particle itself passes the tests)
             best.screened += 1u;
-            if (!(fmaf(q.rr - best.kcut, q.g2, -(q.b * q.b)) <= tc0)) return;
+            const float kd = K ? l.kd2[o.row + l.kind[j - c0]] : kD2;
+            const float bb = q.b * q.b;
+            if (!(fmaf(q.rk + (kd - best.kcut), q.g2, -bb) <= tc)) return;
             // certain to be acceptable: its key's upper bound prunes from here on
-            const float ig = __builtin_amdgcn_rcpf(q.g2), bb = q.b * q.b;
-            const float ku = fmaf(q.rr, 1.000001f, g.t.tcu) + (tc0 - bb) * ig;
-            const float kd = K ? l.kd2[o.row + __float_as_uint(qb.z)] : kD2;
-            if ((fmaf(tb1, q.g2, q.b) <= -tb0) & (fmaf(-g.t.kdm, q.g2, -q.b) <= -tt0) &
+            const float ig = __builtin_amdgcn_rcpf(q.g2), rr = q.rk + kd;
+            const float ku = fmaf(rr, 1.000001f, g.t.tcu) + (tc - bb) * ig;
+            if ((fmaf(g.t.tb1, q.g2, q.b) <= -g.t.tb0) & (fmaf(-g.t.kdm, q.g2, -q.b) <= -g.t.tt0) &
                 (ku < fmaf(kd, 0.999995f, -g.t.kc)) & (q.g2 > g.t.gmin))
                 best.kcut = fminf(best.kcut, fmaf(fmaxf(ku, 0.f), 1.000004f, g.t.kc));
             int k = d.n;
@@ -1821,23 +1875,28 @@ struct PolF32 {
                 }
             }
             d.l->j[k][threadIdx.x] = j;
-            d.l->lo[k][threadIdx.x] = fmaf(q.rr, 0.999999f, -(bb + tc0) * ig);
+            d.l->lo[k][threadIdx.x] = fmaf(rr, 0.999999f, -g.t.tcu) - (bb + tc) * ig;
             d.l->code[k][threadIdx.x] = (uint8_t)wcode(wx, wy, wz);
         };
-        const float4* rp = l.a + (j0 - c0);
-        const float4* const re = rp + (j1 > j0 ? j1 - j0 : 0u);
+        const float4* pa = l.a + (j0 - c0);
+        const float2* pb = l.b + (j0 - c0);
+        const float4* const pe = pa + (j1 > j0 ? j1 - j0 : 0u);
         Q q0, q1;
-        for (; rp + 1 < re; rp += 2) {   // two records per iteration, as in scan
-            const float4 qa0 = rp[0], qb0 = rp[W], qa1 = rp[1], qb1 = rp[W + 1];
-            const bool k0 = test(qa0, qb0, q0), k1 = test(qa1, qb1, q1);
+        for (; pa + 1 < pe; pa += 2, pb += 2) {   // two records per iteration, as in scan
+            const float4 qa0 = pa[0], qa1 = pa[1];
+            const float2 qb0 = pb[0], qb1 = pb[1];
+            const uint32_t t = K ? (uint32_t)(pa - l.a) : 0u;
+            const bool k0 = test(qa0, qb0, t, q0), k1 = test(qa1, qb1, t + 1u, q1);
             if (k0 | k1) {
-                if (k0) take(qb0, q0);
-                if (k1) take(qb1, q1);
+                const uint32_t j = c0 + (uint32_t)(pa - l.a);
+                if (k0) take(j, q0);
+                if (k1) take(j + 1u, q1);
             }
         }
-        if (rp < re) {
-            const float4 qa = rp[0], qb = rp[W];
-            if (test(qa, qb, q0)) take(qb, q0);
+        if (pa < pe) {
+            const float4 qa = pa[0];
+            const float2 qb = pb[0];
+            if (test(qa, qb, K ? (uint32_t)(pa - l.a) : 0u, q0)) take(c0 + (uint32_t)(pa - l.a), q0);
         }
     }
     // the deferred pairs of particle i, decided in FP64 with their image shifts
@@ -1863,6 +1922,16 @@ struct PolF32 {
     }
 };
 
+// A row of a search group's neighbourhood: its window of cells (the same for
+// the whole wave), the lane's part of it, and the row's image.
+struct RowRange {
+    uint32_t gs, ge;
+    uint32_t ls, le;
+    uint32_t row;
+    int wy, wz;
+    bool ok;
+};
+
 template <class Pol>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Pol::kWaves)))
 void k_search_half(Plan p)
@@ -1877,7 +1946,7 @@ void k_search_half(Plan p)
     typename Pol::Own own{};
     if (alive) {
         double x, y, z;
-        Pol::load_own(p, i, own, x, y, z);
+        Pol::load_own(lds, p, i, own, x, y, z);
         // (one box: its parameters are the same for every lane and come
         // through scalar loads, which keeps them out of the vector registers)
         auto locate = [&](const BoxDev& B) {
@@ -1897,10 +1966,7 @@ void k_search_half(Plan p)
     __shared__ Extra extra;
     if (lane == 0) extra.n = 0u;   // (a barrier follows before the first pair is tested)
     Found found;
-    found.extra = &extra;
-    found.sj = found_j + lane;
-    found.n = 0;
-    found.w = 0u;
+    found.clear(&extra, found_j + lane);
     uint64_t remaining = __ballot(alive);
     while (remaining) {
         const int lead = __ffsll((unsigned long long)remaining) - 1;
@@ -1921,62 +1987,71 @@ void k_search_half(Plan p)
         const int NX = B.nc[0], NY = B.nc[1], NZ = B.nc[2];
         typename Pol::Group gctx;
         const uint32_t sbi = gb * (uint32_t)kSpanClasses + span_class(cxl - cxf + 1);
-        Pol::begin_group(p, B, own, gctx, cxf, cxl, gcy, gcz, (int)sbi, i, in);
+        Pol::begin_group(lds, p, B, own, gctx, cxf, cxl, gcy, gcz, (int)sbi, i, in);
         Pol::group_lds(lds, p, sbi, lane);
-        // Cells [ca, cb] of a row seen with image shift (wx, wy, wz); each lane
-        // tests the sub-range [ls, le) of it (empty when ls >= le).
-        auto part = [&](uint32_t row, int ca, int cb, uint32_t ls, uint32_t le, int wx, int wy, int wz, int dy,
-                        int dz) {
-            const uint32_t gs = p.start[row + ca], ge = p.start[row + cb + 1];
+        // Sorted range [gs, ge) of a row seen with image shift (wx, wy, wz); each
+        // lane tests the sub-range [ls, le) of it (empty when ls >= le).
+        auto part = [&](uint32_t gs, uint32_t ge, uint32_t ls, uint32_t le, int wx, int wy, int wz) {
             const bool sh = (wx | wy | wz) != 0;
             for (uint32_t c0 = gs; c0 < ge; c0 += (uint32_t)Pol::W) {
                 const uint32_t n = min((uint32_t)Pol::W, ge - c0);
                 for (uint32_t t = (uint32_t)lane; t < n; t += 64u)
-                    Pol::stage(lds, t, p, c0 + t, B, gctx, wx, wy, wz, dy, dz);
+                    Pol::stage(lds, t, p, c0 + t, B, gctx, wx, wy, wz, 0, 0);
                 __syncthreads();
                 const uint32_t j0 = max(ls, c0), j1 = min(le, c0 + n);
                 // (the screen's records are staged with their image shift)
-                if (!Pol::kScreen && sh) Pol::template scan<true>(p, lds, c0, j0, j1, i, own, B, gctx, wx, wy, wz, dy, dz, found);
-                else Pol::template scan<false>(p, lds, c0, j0, j1, i, own, B, gctx, wx, wy, wz, dy, dz, found);
+                if (!Pol::kScreen && sh) Pol::template scan<true>(p, lds, c0, j0, j1, i, own, B, gctx, wx, wy, wz, 0, 0, found);
+                else Pol::template scan<false>(p, lds, c0, j0, j1, i, own, B, gctx, wx, wy, wz, 0, 0, found);
                 found.mark_lost(p, i, j0, j1);
                 __syncthreads();
             }
         };
-        // a wrapped end cell of a periodic x axis, used by lanes at that end
-        auto wrap_cell = [&](uint32_t row, int cell, bool use, int wx, int wy, int wz, int dy, int dz) {
-            part(row, cell, cell, use ? 0u : 1u, use ? 0xFFFFFFFFu : 0u, wx, wy, wz, dy, dz);
+        // Rows of the half neighbourhood: the own one (from the particle on,
+        // through cell cx+1), then (dy, dz) = (+1, 0), (-1, +1), (0, +1),
+        // (+1, +1) with the cells cx-1..cx+1.  The ranges of a row are loaded
+        // while the one before it is worked on (1e8 particles: 8.06 -> 7.82 ms,
+        // the shock tube 82 -> 79 us; the full search has no registers to spare
+        // for it: 1.42 -> 1.49 ms on 256 boxes).
+        auto fetch = [&](int r, RowRange& R) {
+            const int dy = r < 2 ? r : r - 3, dz = r < 2 ? 0 : 1;
+            int nz = gcz + dz, ny = gcy + dy;
+            R.wy = R.wz = 0;
+            R.ok = r < 5;
+            if (nz >= NZ) { R.ok = R.ok && B.periodic[2]; nz -= NZ; R.wz = 1; }
+            if (ny < 0) { R.ok = R.ok && B.periodic[1]; ny += NY; R.wy = -1; }
+            else if (ny >= NY) { R.ok = R.ok && B.periodic[1]; ny -= NY; R.wy = 1; }
+            R.row = B.coff + (uint32_t)NX * ((uint32_t)ny + (uint32_t)NY * (uint32_t)nz);
+            R.ls = R.le = 0;
+            if (!R.ok) return;
+            R.gs = p.start[R.row + (uint32_t)(r == 0 ? cxf : (cxf > 0 ? cxf - 1 : 0))];
+            R.ge = p.start[R.row + (uint32_t)(cxl + 1 < NX ? cxl + 1 : NX - 1) + 1u];
+            if (in) {
+                R.ls = r == 0 ? i + 1u : p.start[R.row + (uint32_t)(cx > 0 ? cx - 1 : 0)];
+                R.le = p.start[R.row + (uint32_t)(cx + 1 < NX ? cx + 1 : NX - 1) + 1u];
+            }
         };
-        // own row: the rest of the own cell after i, and cell cx+1
-        {
-            const uint32_t row = key;
-            const int cb = cxl + 1 >= NX ? NX - 1 : cxl + 1;
-            uint32_t ls = 0, le = 0;
-            if (in) {
-                ls = i + 1;
-                le = p.start[row + (cx + 1 >= NX ? NX - 1 : cx + 1) + 1];
+        RowRange R;
+        fetch(0, R);
+#pragma unroll 1
+        for (int r = 0; r < 5; ++r) {
+            RowRange next;
+            fetch(r + 1, next);
+            if (R.ok) {
+                part((uint32_t)__builtin_amdgcn_readfirstlane((int)R.gs), (uint32_t)__builtin_amdgcn_readfirstlane((int)R.ge),
+                     R.ls, R.le, 0, R.wy, R.wz);
+                if (B.periodic[0]) {
+                    // a wrapped end cell, used by lanes at that end (the own
+                    // row only looks ahead)
+                    for (int side = r == 0 ? 1 : 0; side < 2; ++side) {
+                        if (side == 0 ? cxf > 0 : cxl + 1 < NX) continue;
+                        const uint32_t cell = R.row + (side == 0 ? (uint32_t)(NX - 1) : 0u);
+                        const bool use = in && cx == (side == 0 ? 0 : NX - 1);
+                        part(p.start[cell], p.start[cell + 1u], use ? 0u : 1u, use ? 0xFFFFFFFFu : 0u, side == 0 ? -1 : 1, R.wy,
+                             R.wz);
+                    }
+                }
             }
-            part(row, cxf, cb, ls, le, 0, 0, 0, 0, 0);
-            if (B.periodic[0] && cxl + 1 >= NX) wrap_cell(row, 0, in && cx == NX - 1, 1, 0, 0, 0, 0);
-        }
-        // rows (dy, dz) = (+1, 0), (-1, +1), (0, +1), (+1, +1): cells cx-1..cx+1
-        for (int r = 0; r < 4; ++r) {
-            const int dy = r == 0 ? 1 : r - 2, dz = r == 0 ? 0 : 1;
-            int nz = gcz + dz, wz = 0;
-            if (nz >= NZ) { if (!B.periodic[2]) continue; nz -= NZ; wz = 1; }
-            int ny = gcy + dy, wy = 0;
-            if (ny < 0) { if (!B.periodic[1]) continue; ny += NY; wy = -1; }
-            else if (ny >= NY) { if (!B.periodic[1]) continue; ny -= NY; wy = 1; }
-            const uint32_t row = B.coff + (uint32_t)NX * ((uint32_t)ny + (uint32_t)NY * (uint32_t)nz);
-            uint32_t ls = 0, le = 0;
-            if (in) {
-                ls = p.start[row + (cx - 1 < 0 ? 0 : cx - 1)];
-                le = p.start[row + (cx + 1 >= NX ? NX - 1 : cx + 1) + 1];
-            }
-            part(row, cxf - 1 < 0 ? 0 : cxf - 1, cxl + 1 >= NX ? NX - 1 : cxl + 1, ls, le, 0, wy, wz, dy, dz);
-            if (B.periodic[0]) {
-                if (cxf - 1 < 0) wrap_cell(row, NX - 1, in && cx == 0, -1, wy, wz, dy, dz);
-                if (cxl + 1 >= NX) wrap_cell(row, 0, in && cx == NX - 1, 1, wy, wz, dy, dz);
-            }
+            R = next;
         }
     }
     uint32_t c = valid ? found.template flush<Pol::kFlushBatch, Pol::kFlushSkipEmpty, Pol::kKinds>(p, i, Pol::self64(p, i, own),
@@ -2106,7 +2181,7 @@ __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, t
         bidx = p.boxidx ? p.boxidx[i] : 0u;
         const BoxDev& B = p.boxes[bidx];
         double x, y, z;
-        Pol::load_own(p, i, own, x, y, z);
+        Pol::load_own(lds, p, i, own, x, y, z);
         cx = cell1(x, B.lo[0], B.inv_h[0], B.nc[0]);
         cy = cell1(y, B.lo[1], B.inv_h[1], B.nc[1]);
         cz = cell1(z, B.lo[2], B.inv_h[2], B.nc[2]);
@@ -2140,7 +2215,7 @@ __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, t
         const int NX = B.nc[0], NY = B.nc[1], NZ = B.nc[2];
         typename Pol::Group gctx;
         const uint32_t sbi = gb * (uint32_t)kSpanClasses + span_class(cxl - cxf + 1);
-        Pol::begin_group(p, B, own, gctx, cxf, cxl, gcy, gcz, (int)sbi, i, in);
+        Pol::begin_group(lds, p, B, own, gctx, cxf, cxl, gcy, gcz, (int)sbi, i, in);
         Pol::group_lds(lds, p, sbi, lane);
         auto part = [&](uint32_t row, int ca, int cb, uint32_t ls, uint32_t le, int wx, int wy, int wz, int dy,
                         int dz) {
@@ -2493,10 +2568,10 @@ __device__ __forceinline__ void search_adapt_tile(const Plan& p, uint32_t tile, 
         const uint32_t io = tile * 64u + (uint32_t)lead + (owner ? o : 0u);
         typename Pol::Own own{};
         double ox, oy, oz;
-        Pol::load_own(p, io, own, ox, oy, oz);
+        Pol::load_own(lds, p, io, own, ox, oy, oz);
         typename Pol::Group gctx;
         const uint32_t sbi = gb * (uint32_t)kSpanClasses;   // the neighbourhood spans 3 cells: class 0
-        Pol::begin_group(p, B, own, gctx, gc[0], gc[0], gc[1], gc[2], (int)sbi, io, owner);
+        Pol::begin_group(lds, p, B, own, gctx, gc[0], gc[0], gc[1], gc[2], (int)sbi, io, owner);
         Pol::group_lds(lds, p, sbi, lane);
         best.clear();
         // ranges of the touching leaves: lanes 0..26 take one neighbour cell each

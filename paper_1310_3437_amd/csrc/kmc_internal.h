@@ -98,7 +98,9 @@ struct Ctl {
 // The others serve the pruning by a particle's best key (full search).
 struct alignas(16) ScreenBounds {
     float tb0, tb1, tt0, kdt, tc0, kD2;
-    float kc, tcu, kdm, gmin, pad_[2];
+    float kc, tcu, kdm, gmin;
+    float ka, kb, kg, tc;   // the tests on b and m2 as one, and tc0, as the staged screens take them
+    float pad_[2];
 };
 
 // Device pointers carved out of the caller's workspace plus launch scalars.
