@@ -1106,6 +1106,43 @@ __device__ __forceinline__ uint32_t wcode(int wx, int wy, int wz)
 }
 constexpr uint32_t kNoImage = 0x15u;   // wcode(0, 0, 0)
 
+// The candidates of a row as a sequence f: their place in the sorted order and
+// their image.  Row is the usual one, f the place itself.
+struct Row {
+    int wx, wy, wz;
+    __device__ __forceinline__ uint32_t at(uint32_t f, int& x) const
+    {
+        x = wx;
+        return f;
+    }
+    __device__ __forceinline__ uint32_t at(uint32_t f, uint32_t& code) const
+    {
+        code = wcode(wx, wy, wz);
+        return f;
+    }
+};
+
+// A row with the wrapped end cells of a periodic x axis: first the nL
+// candidates of the one on the left (sorted from sL on), then the nM of the row
+// itself (from gs on), then those of the one on the right (from sR on).
+struct WrappedRow {
+    uint32_t gs, nM, nL, sL, sR;
+    int wy, wz;
+    __device__ __forceinline__ uint32_t at(uint32_t f, int& x) const
+    {
+        const bool l = f < nL, r = f >= nL + nM;
+        x = l ? -1 : r ? 1 : 0;
+        return f + (l ? sL : r ? sR - nL - nM : gs - nL);
+    }
+    __device__ __forceinline__ uint32_t at(uint32_t f, uint32_t& code) const
+    {
+        int x;
+        const uint32_t j = at(f, x);
+        code = wcode(x, wy, wz);
+        return j;
+    }
+};
+
 struct Found {
     Extra* extra; // the wave's extra pairs in LDS
     uint32_t* sj; // this lane's kept indices in LDS: pair k at sj[64 k] (one store per pair
@@ -1120,46 +1157,55 @@ struct Found {
         n = 0;
         w = kNoImage * 0x41041u;   // no image in every slot
     }
-    __device__ __forceinline__ void keep(uint32_t jj, uint32_t wcode)
+    template <class M>
+    __device__ __forceinline__ void keep(uint32_t f, const M& m)
     {
-        sj[64 * n] = jj;
-        if (wcode != kNoImage) w ^= (wcode ^ kNoImage) << (6 * n);   // (the same for the whole wave)
+        uint32_t code;
+        sj[64 * n] = m.at(f, code);
+        if (code != kNoImage) w ^= (code ^ kNoImage) << (6 * n);
         ++n;
     }
-    // Consecutive candidates j and j + 1, of which at least one is kept (the
+    // Consecutive candidates f and f + 1, of which at least one is kept (the
     // usual case, one of them with slots to spare, has no branches inside).
-    __device__ __forceinline__ void add2(bool k0, bool k1, uint32_t j, uint32_t wcode)
+    template <class M>
+    __device__ __forceinline__ void add2(bool k0, bool k1, uint32_t f, const M& m)
     {
         if (n + 1 < kReg) {
-            keep(k0 ? j : j + 1u, wcode);
-            if (k0 & k1) keep(j + 1u, wcode);
+            keep(k0 ? f : f + 1u, m);
+            if (k0 & k1) keep(f + 1u, m);
         } else {
-            if (k0) add(j, wcode);
-            if (k1) add(j + 1u, wcode);
+            if (k0) add(f, m);
+            if (k1) add(f + 1u, m);
         }
     }
-    __device__ __forceinline__ void add(uint32_t jj, uint32_t wcode)
+    template <class M>
+    __device__ __forceinline__ void add(uint32_t f, const M& m)
     {
         if (n < kReg) {
-            keep(jj, wcode);
+            keep(f, m);
             return;
         }
         const uint32_t t = atomicAdd(&extra->n, 1u);
         if (t < kExtra) {
-            extra->j[t] = jj;
+            uint32_t code;   // (the exact decision finds the image from the cells)
+            extra->j[t] = m.at(f, code);
             extra->lane[t] = (uint8_t)threadIdx.x;
         } else {
             w |= 0x80000000u;
         }
     }
     // After a chunk in which the lane lost pairs: particle i and its window
-    // [j0, j1) of the chunk go to the full re-search.
-    __device__ __forceinline__ void mark_lost(const Plan& p, uint32_t i, uint32_t j0, uint32_t j1)
+    // [f0, f1) of the chunk go to the full re-search.
+    template <class M>
+    __device__ __forceinline__ void mark_lost(const Plan& p, uint32_t i, uint32_t f0, uint32_t f1, const M& m)
     {
         if (!(w >> 31)) return;
         w &= 0x7FFFFFFFu;
         (void)atomicAdd(&p.sl_cnt[i], kMarked);
-        for (uint32_t j = j0; j < j1; ++j) (void)atomicAdd(&p.sl_cnt[j], kMarked);
+        for (uint32_t f = f0; f < f1; ++f) {
+            uint32_t code;
+            (void)atomicAdd(&p.sl_cnt[m.at(f, code)], kMarked);
+        }
     }
     // Decide the kept pairs exactly in FP64 (the FP32 screen keeps pairs it
     // could not reject), write i's best among them (its forward best) and
@@ -1383,12 +1429,11 @@ struct PolF64 {
         l.rec[t] = p.B[j];
         if (K) l.kind[t] = p.spB[j];
     }
-    template <bool SH>
-    __device__ static void scan(const Plan& p, const Lds& l, uint32_t c0, uint32_t j0, uint32_t j1, uint32_t i,
-                                const Own& o, const BoxDev& B, const Group&, int wx, int wy, int wz, int, int,
-                                Found& f)
+    template <bool SH, class M>
+    __device__ static void scan(const Lds& l, uint32_t c0, uint32_t j0, uint32_t j1, const Own& o, const BoxDev& B,
+                                const Group&, const M& m, Found& f)
     {
-        const double sx = (double)wx * B.L[0], sy = (double)wy * B.L[1], sz = (double)wz * B.L[2];
+        const double sx = (double)m.wx * B.L[0], sy = (double)m.wy * B.L[1], sz = (double)m.wz * B.L[2];
         const double D2 = B.D2, dt = B.dt;
         for (uint32_t j = j0; j < j1; ++j) {
             const P64 q = l.rec[j - c0];
@@ -1396,17 +1441,16 @@ struct PolF64 {
             if (SH) { rx = rx + sx; ry = ry + sy; rz = rz + sz; }
             const PairQ pq = pair_q(rx, ry, rz, q.vx - o.me.vx, q.vy - o.me.vy, q.vz - o.me.vz);
             const double d2 = K ? l.d2[o.row + l.kind[j - c0]] : D2;
-            if (accept(pq, d2, dt)) f.add(j, wcode(wx, wy, wz));
+            if (accept(pq, d2, dt)) f.add(j, m);
         }
     }
     // full neighbourhood: running (key, id) minimum over the acceptable pairs
     // (the particle itself has g2 = 0 and is never accepted)
-    template <bool SH>
-    __device__ static void scan_best(const Plan&, const Lds& l, const uint32_t* lid, uint32_t c0, uint32_t j0,
-                                     uint32_t j1, uint32_t, const Own& o, const BoxDev& B, const Group&, int wx,
-                                     int wy, int wz, int, int, Best& best, Deferred&)
+    template <bool SH, class M>
+    __device__ static void scan_best(const Lds& l, const uint32_t* lid, uint32_t c0, uint32_t j0, uint32_t j1, uint32_t,
+                                     const Own& o, const BoxDev& B, const Group&, const M& m, Best& best, Deferred&)
     {
-        const double sx = (double)wx * B.L[0], sy = (double)wy * B.L[1], sz = (double)wz * B.L[2];
+        const double sx = (double)m.wx * B.L[0], sy = (double)m.wy * B.L[1], sz = (double)m.wz * B.L[2];
         const double D2 = B.D2, dt = B.dt;
         for (uint32_t j = j0; j < j1; ++j) {
             const P64 q = l.rec[j - c0];
@@ -1792,10 +1836,9 @@ struct PolF32 {
         l.b[t] = make_float2((float)q.vy, (float)q.vz);
         if (K) l.kind[t] = p.spB[j];
     }
-    template <bool SH>
-    __device__ static void scan(const Plan& p, const Lds& l, uint32_t c0, uint32_t j0, uint32_t j1, uint32_t i,
-                                const Own& o, const BoxDev& B, const Group& g, int wx, int wy, int wz, int, int,
-                                Found& f)
+    template <bool SH, class M>
+    __device__ static void scan(const Lds& l, uint32_t c0, uint32_t j0, uint32_t j1, const Own& o, const BoxDev&,
+                                const Group& g, const M& m, Found& f)
     {
         const float ka = g.t.ka, kb = g.t.kb, kg = g.t.kg, tc = g.t.tc, kD2 = g.t.kD2;
         // the loop steps LDS pointers only; a kept pair's sorted index comes
@@ -1819,20 +1862,19 @@ struct PolF32 {
             const float2 qb0 = pb[0], qb1 = pb[1];
             const uint32_t t = K ? (uint32_t)(pa - l.a) : 0u;
             const bool k0 = test(qa0, qb0, t), k1 = test(qa1, qb1, t + 1u);
-            if (k0 | k1) f.add2(k0, k1, c0 + (uint32_t)(pa - l.a), wcode(wx, wy, wz));
+            if (k0 | k1) f.add2(k0, k1, c0 + (uint32_t)(pa - l.a), m);
         }
         if (pa < pe) {
             const float4 qa = pa[0];
             const float2 qb = pb[0];
-            if (test(qa, qb, K ? (uint32_t)(pa - l.a) : 0u)) f.add(c0 + (uint32_t)(pa - l.a), wcode(wx, wy, wz));
+            if (test(qa, qb, K ? (uint32_t)(pa - l.a) : 0u)) f.add(c0 + (uint32_t)(pa - l.a), m);
         }
     }
     // full neighbourhood: every pair the screen cannot reject is decided in
     // FP64 from the sorted records, with the image shift of its cell
-    template <bool SH>
-    __device__ static void scan_best(const Plan& p, const Lds& l, const uint32_t* lid, uint32_t c0, uint32_t j0,
-                                     uint32_t j1, uint32_t i, const Own& o, const BoxDev& B, const Group& g,
-                                     int wx, int wy, int wz, int, int, Best& best, Deferred& d)
+    template <bool SH, class M>
+    __device__ static void scan_best(const Lds& l, const uint32_t*, uint32_t c0, uint32_t j0, uint32_t j1, uint32_t i,
+                                     const Own& o, const BoxDev&, const Group& g, const M& m, Best& best, Deferred& d)
     {
         const float ka = g.t.ka, kb = g.t.kb, kg = g.t.kg, tc = g.t.tc, kD2 = g.t.kD2;
         struct Q {
@@ -1850,10 +1892,12 @@ struct PolF32 {
         };
         // a kept pair: dropped if its key is certain to exceed the best so
         // far, else recorded for the end of the tile
-        auto take = [&](uint32_t j, const Q& q) {
+        auto take = [&](uint32_t f, const Q& q) {
+            uint32_t code;
+            const uint32_t j = m.at(f, code);
             if (j == i) return;   // (the particle itself passes the tests)
             best.screened += 1u;
-            const float kd = K ? l.kd2[o.row + l.kind[j - c0]] : kD2;
+            const float kd = K ? l.kd2[o.row + l.kind[f - c0]] : kD2;
             const float bb = q.b * q.b;
             if (!(fmaf(q.rk + (kd - best.kcut), q.g2, -bb) <= tc)) return;
             // certain to be acceptable: its key's upper bound prunes from here on
@@ -1876,7 +1920,7 @@ struct PolF32 {
             }
             d.l->j[k][threadIdx.x] = j;
             d.l->lo[k][threadIdx.x] = fmaf(rr, 0.999999f, -g.t.tcu) - (bb + tc) * ig;
-            d.l->code[k][threadIdx.x] = (uint8_t)wcode(wx, wy, wz);
+            d.l->code[k][threadIdx.x] = (uint8_t)code;
         };
         const float4* pa = l.a + (j0 - c0);
         const float2* pb = l.b + (j0 - c0);
@@ -1931,6 +1975,63 @@ struct RowRange {
     int wy, wz;
     bool ok;
 };
+
+// A row's candidates, part by part: part(row, first f, end f, and the lane's
+// own [lf, le)).  On a periodic x axis the cells beyond the ends of the row are
+// the wrapped end cells, for the lanes at that end (back: the one before the
+// first cell as well).  Taken as parts of their own they cost a staging and two
+// barriers for one or two lanes' tests, and in a box of few cells along x most
+// groups have them.  So the screen, whose records are staged with their image,
+// takes them in one sequence with the row (256 uneven boxes in a context, 3 to
+// a bin: full search 1.42 -> 1.32 ms; 1e5 in a box of 32^3 bins: half search
+// 44.8 -> 40.6 us).  Other groups keep the plain sequence, in code of its own
+// (one code for both costs 3 to 5 % where nothing wraps), and so does FP64:
+// there the image enters each pair's arithmetic, once for the whole part.
+template <class Pol, class F>
+__device__ __forceinline__ void row_parts(const Plan& p, const BoxDev& B, const RowRange& R, bool back, bool in, int cx,
+                                          int cxf, int cxl, F&& part)
+{
+    const int NX = B.nc[0];
+    const uint32_t gs = (uint32_t)__builtin_amdgcn_readfirstlane((int)R.gs);
+    const uint32_t ge = (uint32_t)__builtin_amdgcn_readfirstlane((int)R.ge);
+    const bool left = B.periodic[0] && back && cxf == 0, right = B.periodic[0] && cxl == NX - 1;
+    const Row m{0, R.wy, R.wz};
+    if constexpr (Pol::kScreen) {
+        if (left || right) {
+            const uint32_t first = p.start[R.row], second = p.start[R.row + 1u];
+            const uint32_t last = p.start[R.row + (uint32_t)NX - 1u], end = p.start[R.row + (uint32_t)NX];
+            WrappedRow w;
+            w.gs = gs;
+            w.nM = ge - gs;
+            w.sL = (uint32_t)__builtin_amdgcn_readfirstlane((int)last);
+            w.nL = left ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(end - last)) : 0u;
+            w.sR = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+            const uint32_t nR = right ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(second - first)) : 0u;
+            w.wy = R.wy;
+            w.wz = R.wz;
+            const uint32_t total = w.nL + w.nM + nR;
+            uint32_t lf = 0u, le = 0u;
+            if (in) {
+                lf = left && cx == 0 ? 0u : R.ls - gs + w.nL;
+                le = right && cx == NX - 1 ? total : R.le - gs + w.nL;
+            }
+            part(w, 0u, total, lf, le);
+            return;
+        }
+        part(m, gs, ge, R.ls, R.le);
+    } else {
+        part(m, gs, ge, R.ls, R.le);
+        // k = 0: the wrapped cell to the left, k = 1: to the right
+        for (int k = 0; k < 2; ++k) {
+            if (!(k == 0 ? left : right)) continue;
+            const int wc = k == 0 ? NX - 1 : 0;
+            const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)p.start[R.row + (uint32_t)wc]);
+            const uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)p.start[R.row + (uint32_t)wc + 1u]);
+            const bool mine = in && cx == (k == 0 ? 0 : NX - 1);
+            part(Row{k == 0 ? -1 : 1, R.wy, R.wz}, s, e, mine ? s : 0u, mine ? e : 0u);
+        }
+    }
+}
 
 template <class Pol>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Pol::kWaves)))
@@ -1989,20 +2090,23 @@ void k_search_half(Plan p)
         const uint32_t sbi = gb * (uint32_t)kSpanClasses + span_class(cxl - cxf + 1);
         Pol::begin_group(lds, p, B, own, gctx, cxf, cxl, gcy, gcz, (int)sbi, i, in);
         Pol::group_lds(lds, p, sbi, lane);
-        // Sorted range [gs, ge) of a row seen with image shift (wx, wy, wz); each
-        // lane tests the sub-range [ls, le) of it (empty when ls >= le).
-        auto part = [&](uint32_t gs, uint32_t ge, uint32_t ls, uint32_t le, int wx, int wy, int wz) {
-            const bool sh = (wx | wy | wz) != 0;
-            for (uint32_t c0 = gs; c0 < ge; c0 += (uint32_t)Pol::W) {
-                const uint32_t n = min((uint32_t)Pol::W, ge - c0);
-                for (uint32_t t = (uint32_t)lane; t < n; t += 64u)
-                    Pol::stage(lds, t, p, c0 + t, B, gctx, wx, wy, wz, 0, 0);
+        // The candidates [fs, fe) of a row; each lane tests those in [lf, le).
+        auto part = [&](const auto& m, uint32_t fs, uint32_t fe, uint32_t lf, uint32_t le) {
+            for (uint32_t c0 = fs; c0 < fe; c0 += (uint32_t)Pol::W) {
+                const uint32_t n = min((uint32_t)Pol::W, fe - c0);
+                for (uint32_t t = (uint32_t)lane; t < n; t += 64u) {
+                    int wx;
+                    const uint32_t j = m.at(c0 + t, wx);
+                    Pol::stage(lds, t, p, j, B, gctx, wx, m.wy, m.wz, 0, 0);
+                }
                 __syncthreads();
-                const uint32_t j0 = max(ls, c0), j1 = min(le, c0 + n);
+                const uint32_t f0 = max(lf, c0), f1 = min(le, c0 + n);
                 // (the screen's records are staged with their image shift)
-                if (!Pol::kScreen && sh) Pol::template scan<true>(p, lds, c0, j0, j1, i, own, B, gctx, wx, wy, wz, 0, 0, found);
-                else Pol::template scan<false>(p, lds, c0, j0, j1, i, own, B, gctx, wx, wy, wz, 0, 0, found);
-                found.mark_lost(p, i, j0, j1);
+                bool shift = false;
+                if constexpr (!Pol::kScreen) shift = (m.wx | m.wy | m.wz) != 0;
+                if (shift) Pol::template scan<true>(lds, c0, f0, f1, own, B, gctx, m, found);
+                else Pol::template scan<false>(lds, c0, f0, f1, own, B, gctx, m, found);
+                found.mark_lost(p, i, f0, f1, m);
                 __syncthreads();
             }
         };
@@ -2036,21 +2140,7 @@ void k_search_half(Plan p)
         for (int r = 0; r < 5; ++r) {
             RowRange next;
             fetch(r + 1, next);
-            if (R.ok) {
-                part((uint32_t)__builtin_amdgcn_readfirstlane((int)R.gs), (uint32_t)__builtin_amdgcn_readfirstlane((int)R.ge),
-                     R.ls, R.le, 0, R.wy, R.wz);
-                if (B.periodic[0]) {
-                    // a wrapped end cell, used by lanes at that end (the own
-                    // row only looks ahead)
-                    for (int side = r == 0 ? 1 : 0; side < 2; ++side) {
-                        if (side == 0 ? cxf > 0 : cxl + 1 < NX) continue;
-                        const uint32_t cell = R.row + (side == 0 ? (uint32_t)(NX - 1) : 0u);
-                        const bool use = in && cx == (side == 0 ? 0 : NX - 1);
-                        part(p.start[cell], p.start[cell + 1u], use ? 0u : 1u, use ? 0xFFFFFFFFu : 0u, side == 0 ? -1 : 1, R.wy,
-                             R.wz);
-                    }
-                }
-            }
+            if (R.ok) row_parts<Pol>(p, B, R, r != 0, in, cx, cxf, cxl, part);
             R = next;
         }
     }
@@ -2217,49 +2307,43 @@ __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, t
         const uint32_t sbi = gb * (uint32_t)kSpanClasses + span_class(cxl - cxf + 1);
         Pol::begin_group(lds, p, B, own, gctx, cxf, cxl, gcy, gcz, (int)sbi, i, in);
         Pol::group_lds(lds, p, sbi, lane);
-        auto part = [&](uint32_t row, int ca, int cb, uint32_t ls, uint32_t le, int wx, int wy, int wz, int dy,
-                        int dz) {
-            const uint32_t gs = p.start[row + ca], ge = p.start[row + cb + 1];
-            const bool sh = (wx | wy | wz) != 0;
-            for (uint32_t c0 = gs; c0 < ge; c0 += (uint32_t)Pol::W) {
-                const uint32_t n = min((uint32_t)Pol::W, ge - c0);
+        auto part = [&](const auto& m, uint32_t fs, uint32_t fe, uint32_t lf, uint32_t le) {
+            for (uint32_t c0 = fs; c0 < fe; c0 += (uint32_t)Pol::W) {
+                const uint32_t n = min((uint32_t)Pol::W, fe - c0);
                 for (uint32_t t = (uint32_t)lane; t < n; t += 64u) {
-                    Pol::stage(lds, t, p, c0 + t, B, gctx, wx, wy, wz, dy, dz);
-                    if constexpr (!Pol::kScreen) lid[t] = p.idB[c0 + t];
+                    int wx;
+                    const uint32_t j = m.at(c0 + t, wx);
+                    Pol::stage(lds, t, p, j, B, gctx, wx, m.wy, m.wz, 0, 0);
+                    if constexpr (!Pol::kScreen) lid[t] = p.idB[j];
                 }
                 __syncthreads();
-                const uint32_t j0 = max(ls, c0), j1 = min(le, c0 + n);
-                if (!Pol::kScreen && sh)   // (the screen's records are staged with their image shift)
-                    Pol::template scan_best<true>(p, lds, lid, c0, j0, j1, i, own, B, gctx, wx, wy, wz, dy, dz, best,
-                                                  dfr);
+                const uint32_t f0 = max(lf, c0), f1 = min(le, c0 + n);
+                bool shift = false;   // (the screen's records are staged with their image)
+                if constexpr (!Pol::kScreen) shift = (m.wx | m.wy | m.wz) != 0;
+                if (shift)
+                    Pol::template scan_best<true>(lds, lid, c0, f0, f1, i, own, B, gctx, m, best, dfr);
                 else
-                    Pol::template scan_best<false>(p, lds, lid, c0, j0, j1, i, own, B, gctx, wx, wy, wz, dy, dz, best,
-                                                   dfr);
+                    Pol::template scan_best<false>(lds, lid, c0, f0, f1, i, own, B, gctx, m, best, dfr);
                 __syncthreads();
             }
         };
-        auto wrap_cell = [&](uint32_t row, int cell, bool use, int wx, int wy, int wz, int dy, int dz) {
-            part(row, cell, cell, use ? 0u : 1u, use ? 0xFFFFFFFFu : 0u, wx, wy, wz, dy, dz);
-        };
         for (int r = 0; r < 9; ++r) {
-            const int dy = r % 3 - 1, dz = r / 3 - 1;
-            int nz = gcz + dz, wz = 0;
-            if (nz < 0) { if (!B.periodic[2]) continue; nz += NZ; wz = -1; }
-            else if (nz >= NZ) { if (!B.periodic[2]) continue; nz -= NZ; wz = 1; }
-            int ny = gcy + dy, wy = 0;
-            if (ny < 0) { if (!B.periodic[1]) continue; ny += NY; wy = -1; }
-            else if (ny >= NY) { if (!B.periodic[1]) continue; ny -= NY; wy = 1; }
-            const uint32_t row = B.coff + (uint32_t)NX * ((uint32_t)ny + (uint32_t)NY * (uint32_t)nz);
-            uint32_t ls = 0, le = 0;
+            RowRange R;
+            int ny = gcy + r % 3 - 1, nz = gcz + r / 3 - 1;
+            R.wy = R.wz = 0;
+            if (nz < 0) { if (!B.periodic[2]) continue; nz += NZ; R.wz = -1; }
+            else if (nz >= NZ) { if (!B.periodic[2]) continue; nz -= NZ; R.wz = 1; }
+            if (ny < 0) { if (!B.periodic[1]) continue; ny += NY; R.wy = -1; }
+            else if (ny >= NY) { if (!B.periodic[1]) continue; ny -= NY; R.wy = 1; }
+            R.row = B.coff + (uint32_t)NX * ((uint32_t)ny + (uint32_t)NY * (uint32_t)nz);
+            R.gs = p.start[R.row + (uint32_t)(cxf > 0 ? cxf - 1 : 0)];
+            R.ge = p.start[R.row + (uint32_t)(cxl + 1 < NX ? cxl + 1 : NX - 1) + 1u];
+            R.ls = R.le = 0u;
             if (in) {
-                ls = p.start[row + (cx - 1 < 0 ? 0 : cx - 1)];
-                le = p.start[row + (cx + 1 >= NX ? NX - 1 : cx + 1) + 1];
+                R.ls = p.start[R.row + (uint32_t)(cx > 0 ? cx - 1 : 0)];
+                R.le = p.start[R.row + (uint32_t)(cx + 1 < NX ? cx + 1 : NX - 1) + 1u];
             }
-            part(row, cxf - 1 < 0 ? 0 : cxf - 1, cxl + 1 >= NX ? NX - 1 : cxl + 1, ls, le, 0, wy, wz, dy, dz);
-            if (B.periodic[0]) {
-                if (cxf - 1 < 0) wrap_cell(row, NX - 1, in && cx == 0, -1, wy, wz, dy, dz);
-                if (cxl + 1 >= NX) wrap_cell(row, 0, in && cx == NX - 1, 1, wy, wz, dy, dz);
-            }
+            row_parts<Pol>(p, B, R, true, in, cx, cxf, cxl, part);
         }
     }
     if constexpr (Pol::kScreen) {
