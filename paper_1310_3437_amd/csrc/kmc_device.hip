@@ -1461,31 +1461,6 @@ struct PolF64 {
             if (accept(pq, d2, dt)) best.take(pq, lid[j - c0], j);
         }
     }
-    // adaptive bins: the staged candidates t = u, u + kk, ... (< n) against
-    // owner io; candidate t is sorted particle lj[t] seen with the periodic
-    // image of code lw[t]
-    __device__ static void scan_adapt(const Plan&, const Lds& l, const uint32_t* lid, const uint32_t* lj,
-                                      const uint32_t* lw, uint32_t n, uint32_t u, uint32_t kk, uint32_t io,
-                                      const Own& o, const BoxDev& B, const Group&, Best& best)
-    {
-        const double D2 = B.D2, dt = B.dt;
-        for (uint32_t t = u; t < n; t += kk) {
-            const uint32_t j = lj[t];
-            if (j == io) continue;
-            const P64 q = l.rec[t];
-            double rx = q.x - o.me.x, ry = q.y - o.me.y, rz = q.z - o.me.z;
-            const uint32_t w = lw[t];
-            if (w != kNoImage) {
-                const int wx = (int)(w & 3u) - 1, wy = (int)((w >> 2) & 3u) - 1, wz = (int)((w >> 4) & 3u) - 1;
-                if (wx != 0) rx = rx + (double)wx * B.L[0];
-                if (wy != 0) ry = ry + (double)wy * B.L[1];
-                if (wz != 0) rz = rz + (double)wz * B.L[2];
-            }
-            const PairQ pq = pair_q(rx, ry, rz, q.vx - o.me.vx, q.vy - o.me.vy, q.vz - o.me.vz);
-            const double d2 = K ? l.d2[o.row + l.kind[t]] : D2;
-            if (accept(pq, d2, dt)) best.take(pq, lid[t], j);
-        }
-    }
 };
 
 // FP32 screen.  Positions are rounded to FP32 relative to the centre X0 of
@@ -2429,16 +2404,27 @@ void k_research(Plan p)
 // --------------------------------------------------------------------------
 // Density-adaptive bins: the search of particles in or next to a split cell.
 //
-// Particles of one leaf share their neighbourhood: the leaves that touch
-// theirs, all inside the 27 cells around their cell.  A wave takes 64
-// consecutive sorted particles; the lanes of one leaf form a group (they are
-// consecutive, the sort keeps leaves contiguous).  For each group the wave
-// lists the sorted ranges of the touching leaves, stages their particles
-// into LDS and tests every (owner, candidate) pair with all 64 lanes: each of
-// the group's g owners gets 64 / g' lanes (g' the next power of two), which
-// take every (64/g')-th staged candidate, and the owner's (key, id) minimum
-// is reduced over its lanes.  Each pair is tested from both sides (running
-// minimum, no lists).
+// A particle's candidates are those of the leaves that touch its own, all
+// inside the 27 cells around its cell.  A wave takes 64 consecutive sorted
+// particles; the sort keeps leaves contiguous, so they fall into a few dozen
+// leaves.  For up to kLeafBatch of these at a time kLeafLanes lanes list the
+// runs of touching leaves in LDS (a lane takes a neighbour cell, or some rows of
+// one where the leaf touches fewer cells than lanes), eight leaves side by
+// side.  Then kLeafLanes lanes share a particle and walk its leaf's runs as one
+// sequence, each testing every kLeafLanes-th candidate straight from the
+// sorted records, one loaded ahead, and their (key, id) minima are folded.
+// Each pair is tested from both sides (running minimum, no lists; the order of
+// the runs does not matter to the minimum).
+//
+// Leaves hold few particles (2.5 on average at threshold 8), so it is what a
+// wave does per leaf and per candidate besides the test that bounds this: with
+// the leaves taken in turn, each listed, staged through LDS and tested by the
+// whole wave, half of the instructions and most of the waiting were the listing
+// and its barriers.  1e7 particles in blobs, three levels, threshold 8: 4.51 ->
+// 2.95 ms; the listing by each particle's lanes for itself 3.57, 4 or 16 lanes
+// 3.2 and 3.8, without the load ahead 3.8, a list of a fixed size per leaf 3.25.
+// Now the L1 lookups of the gathered records and the control flow of the walk
+// take about equal parts with the FP64 tests.
 // --------------------------------------------------------------------------
 
 // The leaves of the neighbour cell (c + d) that touch the leaf [lo, hi]
@@ -2489,70 +2475,6 @@ __device__ __forceinline__ void neighbour_leaves(const Plan& p, const BoxDev& B,
         }
 }
 
-// The same ranges in two parts, for a wave that lists the neighbourhoods of
-// several leaves of one cell in turn: the neighbour cell's data (its index,
-// level, start and leaf-table offset, loaded together) kept across the
-// leaves, then per leaf the touching runs, which only load leaf-table
-// entries (and nothing at all when only counted).
-struct NbCell {
-    int32_t lvl;       // split level; -1: the neighbour cell does not exist
-    int32_t qw[3];     // its cell coordinates with the periodic image (q + w n)
-    uint32_t code;     // image and cell offset (as neighbour_leaves reports them)
-    uint32_t s0, s1;   // start[cell], start[cell + 1]
-    uint32_t pb;       // pool_base[cell] (split cells)
-};
-
-__device__ __forceinline__ void nb_cell_load(const Plan& p, const BoxDev& B, const int c[3], int dx, int dy, int dz,
-                                             NbCell& nc)
-{
-    const int d[3] = {dx, dy, dz};
-    int q[3], w[3];
-    nc.lvl = -1;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        q[a] = c[a] + d[a];
-        w[a] = 0;
-        if (q[a] < 0) { if (!B.periodic[a]) return; q[a] += B.nc[a]; w[a] = -1; }
-        else if (q[a] >= B.nc[a]) { if (!B.periodic[a]) return; q[a] -= B.nc[a]; w[a] = 1; }
-        nc.qw[a] = q[a] + w[a] * B.nc[a];
-    }
-    nc.code = wcode(w[0], w[1], w[2]) | ((uint32_t)wcode(dx, dy, dz) << 6);
-    const uint32_t cell = B.coff + (uint32_t)q[0] + (uint32_t)B.nc[0] * ((uint32_t)q[1] + (uint32_t)B.nc[1] * (uint32_t)q[2]);
-    nc.lvl = (int)p.level[cell];
-    nc.s0 = p.start[cell];
-    nc.s1 = p.start[cell + 1];
-    nc.pb = p.pool_base[cell];
-}
-
-// The leaves of a cached neighbour cell that touch the leaf [lo, hi]: their
-// index box jlo..jhi per axis, and the number of runs they form in the
-// cell's leaf order (one per (jy, jz) row of a split cell, one for an
-// unsplit cell, 0 when none touches).
-__device__ __forceinline__ uint32_t nb_leaf_box(const Plan& p, const NbCell& nc, const int lo[3], const int hi[3],
-                                                int jlo[3], int jhi[3])
-{
-    if (nc.lvl < 0) return 0u;
-    const int L = p.adapt_L;
-    const int sh = L - nc.lvl, r = 1 << nc.lvl;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        // the neighbour's lower face on the finest grid, with its image
-        const long long b0 = (long long)nc.qw[a] << L;
-        jlo[a] = (int)max(0ll, ((long long)lo[a] - b0 - 1) >> sh);
-        jhi[a] = (int)min((long long)(r - 1), ((long long)hi[a] + 1 - b0) >> sh);
-        if (jlo[a] > jhi[a]) return 0u;
-    }
-    if (nc.lvl == 0) return 1u;
-    return (uint32_t)(jhi[1] - jlo[1] + 1) * (uint32_t)(jhi[2] - jlo[2] + 1);
-}
-
-// One neighbour cell of a group as the wave's lanes read it when they list
-// the runs in parallel.
-struct NbBox {
-    int32_t jlo0, jhi0, jlo1, ny, jlo2, lvl;
-    uint32_t s0, s1, pb, code;
-};
-
 // A particle's cell (c) and leaf ([lo, hi] in finest indices) under adaptive
 // bins, from its position; returns the linear cell.
 __device__ __forceinline__ uint32_t leaf_of(const Plan& p, const BoxDev& B, double x, double y, double z, int c[3],
@@ -2579,219 +2501,239 @@ __device__ __forceinline__ uint32_t leaf_of(const Plan& p, const BoxDev& B, doub
     return cell;
 }
 
-constexpr int kRangeBatch = 128;
+constexpr int kLeafLanes = 8;    // lanes that share a leaf's listing, then a particle
+constexpr int kLeafBatch = 16;   // leaves listed at a time
+// Runs the lists of a batch hold.  One leaf has at most 237: an unsplit cell
+// (at most three split levels: 8 x 8 runs from each x face of its neighbours,
+// 8 from each y and z face and from the 8 edges along y and z, one from the
+// other edges, the corners and the cell itself).
+constexpr int kLeafRuns = 256;
+static_assert(kLeafRuns >= 237, "one leaf's runs fit");
+constexpr uint32_t kNoRun = 0xFFFFFFFFu;
 
-template <int W>
 struct AdaptLds {
-    NbBox nb[27];                    // the group's neighbour cells (runs of touching leaves)
-    uint32_t noff[27];               // exclusive prefix of their run counts
-    uint32_t rs[kRangeBatch];        // range starts (sorted index)
-    uint32_t rc[kRangeBatch];        // range codes (image, cell offset)
-    uint32_t rp[kRangeBatch + 1];    // exclusive prefix of the range sizes
-    uint32_t lid[W];                 // staged candidates' ids
-    uint32_t lj[W];                  // ... sorted indices
-    uint32_t lw[W];                  // ... image codes
+    int32_t c[64][3];       // per leaf of the wave: its cell,
+    uint32_t rl[64];        // ... its place in it (bytes 0 to 2: finest indices of its lower corner; 3: its width)
+    uint32_t box[64];
+    uint32_t head[kLeafBatch];   // first run of each of the batch's leaves
+    uint32_t used;               // runs listed (offered, if more than there is room for)
+    uint4 run[kLeafRuns + 1];    // first sorted index, length, image code, the leaf's next run; the last one ends every list
 };
 
-// Binary search: the range r of flat candidate index f (rp[r] <= f < rp[r+1]).
-__device__ __forceinline__ uint32_t range_of(const uint32_t* rp, uint32_t nr, uint32_t f)
+// Lists the runs of the leaves that touch leaf l of the wave as entry e of the
+// batch; lane u of kLeafLanes.
+__device__ __forceinline__ void list_leaf(const Plan& p, const BoxDev& B, AdaptLds& al, uint32_t l, uint32_t e, uint32_t u)
 {
-    uint32_t lo = 0, hi = nr - 1;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi + 1) >> 1;
-        if (rp[mid] <= f) lo = mid; else hi = mid - 1;
+    constexpr uint32_t G = (uint32_t)kLeafLanes;
+    const int L = p.adapt_L, m = (1 << L) - 1;
+    const uint32_t pk = al.rl[l];
+    // the range of neighbour cells the leaf touches: three per axis for an
+    // unsplit cell, else one or two
+    int rl[3], rh[3], d0[3], nd[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        rl[a] = (int)((pk >> (8 * a)) & 0xFFu);
+        rh[a] = rl[a] + (int)(pk >> 24) - 1;
+        d0[a] = rl[a] == 0 ? -1 : 0;
+        nd[a] = (rh[a] == m ? 2 : 1) - d0[a];
     }
-    return lo;
-}
-
-template <class Pol, bool STATS>
-__device__ __forceinline__ void search_adapt_tile(const Plan& p, uint32_t tile, typename Pol::Lds& lds,
-                                                  AdaptLds<Pol::W>& al)
-{
-    const int lane = threadIdx.x;
-    const uint32_t i = tile * 64u + (uint32_t)lane;
-    bool alive = i < p.N && !(p.idB[i] & kGone);
-    uint32_t bidx = 0, cell = 0xFFFFFFFFu, code = 0;
-    int c[3] = {0, 0, 0}, lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
-    if (alive) {
-        bidx = p.boxidx ? p.boxidx[i] : 0u;
-        const P64 me = p.B[i];
-        cell = leaf_of(p, p.boxes[bidx], me.x, me.y, me.z, c, lo, hi, code);
-        alive = p.mixed[cell] != 0;
+    const uint32_t total = (uint32_t)(nd[0] * nd[1] * nd[2]);
+    // (a product of ones and twos divides the lanes; 27 cells are taken in turn)
+    uint32_t k = u, row0 = 0u, rows = 1u;
+    if (total < G) {
+        k = u & (total - 1u);
+        row0 = u / total;
+        rows = G / total;
     }
-    Best best;
-    uint64_t nstat = 0;
-    uint64_t remaining = __ballot(alive);
-    // lanes 0..26: neighbour cell (lane % 3 - 1, lane / 3 % 3 - 1, lane / 9 - 1)
-    // of the cell of the current group, kept while the groups stay in it
-    const int ndx = lane % 3 - 1, ndy = (lane / 3) % 3 - 1, ndz = lane / 9 - 1;
-    NbCell nbc;
-    nbc.lvl = -1;
-    uint32_t nb_of = 0xFFFFFFFFu;
-    while (remaining) {
-        const int lead = __ffsll((unsigned long long)remaining) - 1;
-        const uint32_t gcell = (uint32_t)__builtin_amdgcn_readlane((int)cell, lead);
-        const uint32_t gcode = (uint32_t)__builtin_amdgcn_readlane((int)code, lead);
-        const uint64_t grp = __ballot(alive && cell == gcell && code == gcode) & remaining;
-        remaining &= ~grp;
-        const uint32_t g = (uint32_t)__popcll(grp);   // lanes lead .. lead + g - 1 (a leaf is contiguous)
-        const uint32_t gb = (uint32_t)__builtin_amdgcn_readlane((int)bidx, lead);
-        const BoxDev& B = p.boxes[gb];
-        int gc[3], glo[3], ghi[3];
+    // d / n for d < 27 and n of 1, 2, 3
+    auto div3 = [](uint32_t d, int n) { return n == 1 ? d : n == 2 ? d >> 1 : (d * 11u) >> 5; };
+    for (; k < total; k += G) {
+        const uint32_t kxy = div3(k, nd[0]), kz = div3(kxy, nd[1]);
+        const int d[3] = {d0[0] + (int)(k - kxy * (uint32_t)nd[0]), d0[1] + (int)(kxy - kz * (uint32_t)nd[1]),
+                          d0[2] + (int)kz};
+        int q[3], w[3];
+        bool ok = true;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            gc[a] = __builtin_amdgcn_readlane(c[a], lead);
-            glo[a] = __builtin_amdgcn_readlane(lo[a], lead);
-            ghi[a] = __builtin_amdgcn_readlane(hi[a], lead);
+            q[a] = al.c[l][a] + d[a];
+            w[a] = q[a] < 0 ? -1 : (q[a] >= B.nc[a] ? 1 : 0);
+            if (w[a] != 0) ok = ok && B.periodic[a];
+            q[a] -= w[a] * B.nc[a];
         }
-        // owners: 64 / g' lanes each (g' = g rounded up to a power of two)
-        uint32_t gp = 1;
-        while (gp < g) gp <<= 1;
-        const uint32_t kk = 64u / gp, o = (uint32_t)lane / kk, u = (uint32_t)lane % kk;
-        const bool owner = o < g;
-        const uint32_t io = tile * 64u + (uint32_t)lead + (owner ? o : 0u);
-        typename Pol::Own own{};
-        double ox, oy, oz;
-        Pol::load_own(lds, p, io, own, ox, oy, oz);
-        typename Pol::Group gctx;
-        const uint32_t sbi = gb * (uint32_t)kSpanClasses;   // the neighbourhood spans 3 cells: class 0
-        Pol::begin_group(lds, p, B, own, gctx, gc[0], gc[0], gc[1], gc[2], (int)sbi, io, owner);
-        Pol::group_lds(lds, p, sbi, lane);
-        best.clear();
-        // ranges of the touching leaves: lanes 0..26 take one neighbour cell each
-        if (gcell != nb_of) {
-            if (lane < 27) nb_cell_load(p, B, gc, ndx, ndy, ndz, nbc);
-            nb_of = gcell;
+        if (!ok) continue;
+        const uint32_t cell =
+            B.coff + (uint32_t)q[0] + (uint32_t)B.nc[0] * ((uint32_t)q[1] + (uint32_t)B.nc[1] * (uint32_t)q[2]);
+        const int lvl = (int)p.level[cell];
+        const uint32_t s0 = p.start[cell], s1 = p.start[cell + 1], pb = p.pool_base[cell];
+        auto list = [&](uint32_t a, uint32_t b) {
+            if (b <= a) return;
+            const uint32_t t = atomicAdd(&al.used, 1u);
+            if (t >= (uint32_t)kLeafRuns) return;
+            al.run[t] = uint4{a, b - a, wcode(w[0], w[1], w[2]), atomicExch(&al.head[e], t)};
+        };
+        if (lvl == 0) {
+            if (row0 == 0u) list(s0, s1);
+            continue;
         }
-        // per neighbour cell the box of touching leaves and its number of
-        // runs, published; then the lanes list the runs f = lane, lane + 64,
-        // ... of the flat sequence (cell by cell, rows jz-major) in parallel
-        int bjlo[3] = {0, 0, 0}, bjhi[3] = {0, 0, 0};
-        uint32_t nr = 0;
-        if (lane < 27) nr = nb_leaf_box(p, nbc, glo, ghi, bjlo, bjhi);
-        uint32_t off = nr;
+        // the cell's leaves jl .. jh per axis that touch; one run per (y, z)
+        const int sh = L - lvl, r = 1 << lvl;
+        int jl[3], jh[3];
 #pragma unroll
-        for (int sft = 1; sft < 64; sft <<= 1) {
-            const uint32_t y = __shfl_up(off, sft, 64);
-            if (lane >= sft) off += y;
+        for (int a = 0; a < 3; ++a) {
+            jl[a] = max(0, (rl[a] - (d[a] << L) - 1) >> sh);
+            jh[a] = min(r - 1, (rh[a] - (d[a] << L) + 1) >> sh);
         }
-        const uint32_t R = (uint32_t)__shfl((int)off, 63, 64);
-        off -= nr;
-        if (lane < 27) {
-            NbBox& nx = al.nb[lane];
-            nx.jlo0 = bjlo[0];
-            nx.jhi0 = bjhi[0];
-            nx.jlo1 = bjlo[1];
-            nx.ny = bjhi[1] - bjlo[1] + 1;
-            nx.jlo2 = bjlo[2];
-            nx.lvl = nbc.lvl;
-            nx.s0 = nbc.s0;
-            nx.s1 = nbc.s1;
-            nx.pb = nbc.pb;
-            nx.code = nbc.code;
-            al.noff[lane] = off;
+        const int ny = jh[1] - jl[1] + 1;
+        int jy = jl[1] + (int)row0, jz = jl[2];
+        for (;;) {
+            while (jy > jh[1]) {
+                jy -= ny;
+                ++jz;
+            }
+            if (jz > jh[2]) break;
+            const uint32_t* t = p.pool + pb + (uint32_t)r * ((uint32_t)jy + (uint32_t)r * (uint32_t)jz);
+            list(s0 + t[jl[0]], s0 + t[jh[0] + 1]);
+            jy += (int)rows;
         }
-        __syncthreads();
-        for (uint32_t rb = 0; rb < R; rb += (uint32_t)kRangeBatch) {
-            const uint32_t nb = min((uint32_t)kRangeBatch, R - rb);
-            for (uint32_t f = rb + (uint32_t)lane; f < rb + nb; f += 64u) {
-                // the neighbour cell d of run f: the last with noff[d] <= f
-                uint32_t d = 0;
-#pragma unroll
-                for (uint32_t step = 16; step > 0; step >>= 1)
-                    if (d + step < 27u && al.noff[d + step] <= f) d += step;
-                const NbBox& nx = al.nb[d];
-                const uint32_t k = f - al.noff[d];
-                uint32_t s0 = nx.s0, e0 = nx.s1;
-                if (nx.lvl > 0) {
-                    const uint32_t r = 1u << nx.lvl;
-                    const uint32_t jy = (uint32_t)nx.jlo1 + k % (uint32_t)nx.ny;
-                    const uint32_t jz = (uint32_t)nx.jlo2 + k / (uint32_t)nx.ny;
-                    const uint32_t* t = p.pool + nx.pb + r * (jy + r * jz);
-                    s0 = nx.s0 + t[nx.jlo0];
-                    e0 = nx.s0 + t[nx.jhi0 + 1];
-                }
-                al.rs[f - rb] = s0;
-                al.rc[f - rb] = nx.code;
-                al.rp[f - rb] = e0 - s0;   // size, turned into the prefix below
-            }
-            __syncthreads();
-            // exclusive prefix of the nb sizes: two per lane
-            const uint32_t e0 = 2u * (uint32_t)lane, e1 = e0 + 1u;
-            const uint32_t v0 = e0 < nb ? al.rp[e0] : 0u, v1 = e1 < nb ? al.rp[e1] : 0u;
-            uint32_t x = v0 + v1;
-#pragma unroll
-            for (int sft = 1; sft < 64; sft <<= 1) {
-                const uint32_t y = __shfl_up(x, sft, 64);
-                if (lane >= sft) x += y;
-            }
-            __syncthreads();
-            if (e0 < nb) al.rp[e0] = x - v0 - v1;
-            if (e1 < nb) al.rp[e1] = x - v1;
-            if (lane == 63) al.rp[nb] = x;
-            __syncthreads();
-            const uint32_t total = al.rp[nb];
-            for (uint32_t c0 = 0; c0 < total; c0 += (uint32_t)Pol::W) {
-                const uint32_t n = min((uint32_t)Pol::W, total - c0);
-                for (uint32_t t = (uint32_t)lane; t < n; t += 64u) {
-                    const uint32_t f = c0 + t;
-                    const uint32_t r = range_of(al.rp, nb, f);
-                    const uint32_t j = al.rs[r] + (f - al.rp[r]);
-                    const uint32_t cd = al.rc[r];
-                    const int wx = (int)(cd & 3u) - 1, wy = (int)((cd >> 2) & 3u) - 1, wz = (int)((cd >> 4) & 3u) - 1;
-                    const int dy = (int)((cd >> 8) & 3u) - 1, dz = (int)((cd >> 10) & 3u) - 1;
-                    Pol::stage(lds, t, p, j, B, gctx, wx, wy, wz, dy, dz);
-                    al.lid[t] = p.idB[j];
-                    al.lj[t] = j;
-                    al.lw[t] = cd & 0x3Fu;
-                }
-                __syncthreads();
-                if (owner) Pol::scan_adapt(p, lds, al.lid, al.lj, al.lw, n, u, kk, io, own, B, gctx, best);
-                __syncthreads();
-            }
-            __syncthreads();   // every read of this batch's ranges is done
-        }
-        // each owner's (key, id) minimum over its kk lanes
-        for (uint32_t sft = kk >> 1; sft > 0; sft >>= 1) {
-            const double k2 = __shfl_xor(best.key, (int)sft, 64);
-            const uint32_t id2 = (uint32_t)__shfl_xor((int)best.id, (int)sft, 64);
-            const int32_t j2 = __shfl_xor(best.j, (int)sft, 64);
-            if (k2 < best.key || (k2 == best.key && id2 < best.id)) {
-                best.key = k2;
-                best.id = id2;
-                best.j = j2;
-            }
-        }
-        if (owner && u == 0) p.partner[io] = best.j;
-        if (owner) nstat += Pol::kScreen ? best.screened : best.accepted;
-    }
-    if (STATS) {
-#pragma unroll
-        for (int sft = 32; sft > 0; sft >>= 1) nstat += __shfl_xor(nstat, sft, 64);
-        if (lane == 0 && nstat) atomicAdd(&p.acc[blockIdx.x % p.acc_lanes].cand, (unsigned long long)nstat);
     }
 }
 
-template <class Pol>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Pol::kFullWaves)))
-void k_search_adapt(Plan p)
+template <bool K>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) void k_search_adapt(Plan p)
 {
-    __shared__ typename Pol::Lds lds;
-    __shared__ AdaptLds<Pol::W> al;
-    search_adapt_tile<Pol, true>(p, xcd_tile(blockIdx.x, gridDim.x), lds, al);
-}
-
-// The whole-step FP64 search of the particles k_search_adapt takes (see
-// k_research).
-template <class Pol>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Pol::kFullWaves)))
-void k_fallback_adapt(Plan p)
-{
-    __shared__ typename Pol::Lds lds;
-    __shared__ AdaptLds<Pol::W> al;
-    if (!whole_step(p)) return;
-    const uint32_t ntiles = (p.N + 63u) / 64u;
-    for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) search_adapt_tile<Pol, false>(p, t, lds, al);
+    constexpr uint32_t G = (uint32_t)kLeafLanes;
+    __shared__ AdaptLds al;
+    const uint32_t lane = threadIdx.x;
+    const uint32_t i0 = xcd_tile(blockIdx.x, gridDim.x) * 64u;
+    // the wave's particles and their leaves (a leaf's particles are consecutive)
+    bool alive = i0 + lane < p.N && !(p.idB[i0 + lane] & kGone);
+    uint32_t cell = 0xFFFFFFFFu, code = 0u;
+    int c[3] = {0, 0, 0}, lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
+    uint32_t bidx = 0u;
+    if (alive) {
+        const P64 me = p.B[i0 + lane];
+        bidx = p.boxidx ? p.boxidx[i0 + lane] : 0u;
+        cell = leaf_of(p, p.boxes[bidx], me.x, me.y, me.z, c, lo, hi, code);
+        alive = p.mixed[cell] != 0;
+        if (!alive) cell = 0xFFFFFFFFu;
+    }
+    const uint32_t cell_l = __shfl_up(cell, 1, 64), code_l = __shfl_up(code, 1, 64);
+    const uint64_t lives = __ballot(alive);
+    if (lives == 0) return;
+    const uint64_t heads = __ballot(alive && (lane == 0u || cell != cell_l || code != code_l));
+    const uint32_t nleaves = (uint32_t)__popcll(heads);
+    if ((heads >> lane) & 1u) {
+        const uint32_t l = (uint32_t)__popcll(heads & ((1ull << lane) - 1ull));
+        const int L = p.adapt_L;
+        uint32_t pk = (uint32_t)(hi[0] - lo[0] + 1) << 24;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            al.c[l][a] = c[a];
+            pk |= (uint32_t)(lo[a] - (c[a] << L)) << (8 * a);
+        }
+        al.rl[l] = pk;
+        al.box[l] = bidx;
+    }
+    if (lane == 0u) al.run[kLeafRuns] = uint4{kNoRun, kNoRun, kNoImage, (uint32_t)kLeafRuns};
+    const uint32_t u = lane % G, o = lane / G;
+    uint32_t accepted = 0u;
+    auto search = [&](auto box) {
+        uint64_t left = heads;   // heads of the leaves not yet searched
+        uint32_t nl = (uint32_t)kLeafBatch;
+        for (uint32_t l0 = 0; l0 < nleaves; l0 += nl) {
+            nl = min(nl, nleaves - l0);
+            if (lane < (uint32_t)kLeafBatch) al.head[lane] = (uint32_t)kLeafRuns;
+            if (lane == 0u) al.used = 0u;
+            __syncthreads();
+            for (uint32_t e = o; e < nl; e += 64u / G) list_leaf(p, box(al.box[l0 + e]), al, l0 + e, e, u);
+            __syncthreads();
+            if (al.used > (uint32_t)kLeafRuns && nl > 1u) {   // (one leaf always fits)
+                __syncthreads();
+                nl >>= 1;
+                l0 -= nl;
+                continue;
+            }
+            // the particles of these leaves: lanes k0 .. k1 - 1 of the wave
+            const uint32_t k0 = (uint32_t)__ffsll((unsigned long long)left) - 1u;
+            for (uint32_t e = 0; e < nl; ++e) left &= left - 1ull;
+            const uint32_t k1 = left ? (uint32_t)__ffsll((unsigned long long)left) - 1u : 64u;
+            for (uint32_t kb = k0; kb < k1; kb += 64u / G) {
+                const uint32_t k = kb + o, i = i0 + k;
+                const bool on = k < k1 && ((lives >> k) & 1ull);
+                if (__ballot(on) == 0) continue;
+                Best best;
+                best.clear();
+                if (on) {
+                    const uint32_t l = (uint32_t)__popcll(heads & ((2ull << k) - 1ull)) - 1u, e = l - l0;
+                    const P64 me = p.B[i];
+                    const BoxDev& B = box(al.box[l]);
+                    const uint32_t row = K ? kind_row(p, i) : 0u;
+                    const double D2 = B.D2, dt = B.dt;
+                    auto test = [&](const P64& q, uint32_t j, uint32_t w) {
+                        // (the particle itself has g2 = 0 and is never accepted)
+                        double rx = q.x - me.x, ry = q.y - me.y, rz = q.z - me.z;
+                        if (w != kNoImage) {
+                            const int wx = (int)(w & 3u) - 1, wy = (int)((w >> 2) & 3u) - 1, wz = (int)((w >> 4) & 3u) - 1;
+                            if (wx != 0) rx = rx + (double)wx * B.L[0];
+                            if (wy != 0) ry = ry + (double)wy * B.L[1];
+                            if (wz != 0) rz = rz + (double)wz * B.L[2];
+                        }
+                        const PairQ pq = pair_q(rx, ry, rz, q.vx - me.vx, q.vy - me.vy, q.vz - me.vz);
+                        if (accept(pq, K ? pair_D2(p, B, row, j) : D2, dt)) best.take(pq, p.idB[j], j);
+                    };
+                    // the run that holds the lane's candidate f
+                    uint32_t f = u;
+                    uint4 R = al.run[al.head[e]];
+                    auto next = [&]() {
+                        while (f >= R.y) {
+                            f -= R.y;
+                            R = al.run[R.w];
+                        }
+                        return R.x != kNoRun;
+                    };
+                    if (next()) {
+                        P64 q = p.B[R.x + f];
+                        for (;;) {
+                            const uint32_t j = R.x + f, w = R.z;
+                            f += G;
+                            if (!next()) {
+                                test(q, j, w);
+                                break;
+                            }
+                            const P64 q2 = p.B[R.x + f];
+                            test(q, j, w);
+                            const uint32_t j2 = R.x + f, w2 = R.z;
+                            f += G;
+                            const bool more = next();
+                            if (more) q = p.B[R.x + f];
+                            test(q2, j2, w2);
+                            if (!more) break;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int off = kLeafLanes / 2; off > 0; off >>= 1) {
+                    const double k2 = __shfl_xor(best.key, off, 64);
+                    const uint32_t id2 = (uint32_t)__shfl_xor((int)best.id, off, 64);
+                    const int32_t j2 = __shfl_xor(best.j, off, 64);
+                    if (k2 < best.key || (k2 == best.key && id2 < best.id)) {
+                        best.key = k2;
+                        best.id = id2;
+                        best.j = j2;
+                    }
+                }
+                if (on && u == 0u) p.partner[i] = best.j;
+                accepted += best.accepted;
+            }
+            __syncthreads();
+        }
+    };
+    // (one box: its parameters come through scalar loads)
+    if (p.boxidx) search([&](uint32_t b) -> const BoxDev& { return p.boxes[b]; });
+    else search([&](uint32_t) -> const BoxDev& { return p.boxes[0]; });
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) accepted += __shfl_xor(accepted, off, 64);
+    if (lane == 0u && accepted) atomicAdd(&p.acc[blockIdx.x % p.acc_lanes].cand, (unsigned long long)accepted);
 }
 
 // --------------------------------------------------------------------------
@@ -3360,8 +3302,8 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
         // the particles next to split cells: plain FP64 in both precisions
         // (their groups are leaves of a few particles, where the screen's
         // conversions and FP64 decisions cost more than they save)
-        if (p.nspecies > 0) k_search_adapt<PolF64<true>><<<gW, 64, 0, s>>>(p);
-        else k_search_adapt<PolF64<false>><<<gW, 64, 0, s>>>(p);
+        if (p.nspecies > 0) k_search_adapt<true><<<gW, 64, 0, s>>>(p);
+        else k_search_adapt<false><<<gW, 64, 0, s>>>(p);
     }
     mark(KMC_PHASE_FINISH);
     if (p.N > 0 && !full) {
@@ -3374,10 +3316,6 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
         const uint32_t g = gW < kFallbackBlocks ? gW : kFallbackBlocks;
         if (p.nspecies > 0) k_research<PolF64<true>><<<g, 64, 0, s>>>(p);
         else k_research<PolF64<false>><<<g, 64, 0, s>>>(p);
-        if (p.adapt_L > 0) {
-            if (p.nspecies > 0) k_fallback_adapt<PolF64<true>><<<kFallbackBlocks, 64, 0, s>>>(p);
-            else k_fallback_adapt<PolF64<false>><<<kFallbackBlocks, 64, 0, s>>>(p);
-        }
     }
     mark(KMC_PHASE_RESOLVE);
     if (p.N > 0) {

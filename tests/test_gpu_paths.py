@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 from paper_1310_3437_amd import inputs as I
+from tests.test_gpu_adaptive import run_adaptive
 from tests.test_gpu_parity import run_parity
 from tests import test_gpu_screen as S
 from tests.test_gpu_screen import dense_gas
@@ -141,3 +142,23 @@ def test_staged_screen_on_adversarial_pairs(kmc, tile, mode):
     w = S.adversarial(seed=12, kinds=("radius", "tend", "tzero"))
     mism, _, _ = S.gpu_vs_oracle(kmc, w, f32, guard_scale=-1.0, **cfg)
     assert mism > 0
+
+
+@pytest.mark.parametrize("ncell", [3, 5])
+@pytest.mark.parametrize("thin", [1, 2, 9])
+def test_leaf_lists(kmc, ncell, thin):
+    """Unsplit cells and cells of large leaves alone among cells of the deepest
+    level: one leaf's list of touching runs is as long as it can be, and those of
+    a wave's leaves outgrow the room for them; three cells to an axis make every
+    cell a seam."""
+    rng = np.random.default_rng(100 * ncell + thin)
+    counts = np.full(ncell ** 3, 150)           # more than 2 * 8^2: level 3
+    counts[::5] = thin                          # level 0 (up to 2) or 1
+    cell = np.repeat(np.arange(ncell ** 3), counts)
+    at = np.stack([cell % ncell, cell // ncell % ncell, cell // ncell ** 2])
+    n = cell.size
+    box, s = I.uniform_box(n, ncell=ncell, D=0.9 / ncell, ic_seed=7, dt=0.02)
+    s[0:3] = np.minimum((at + rng.random((3, n))) / ncell, np.nextafter(1.0, 0.0))
+    w = I.Workload("leaves", [box], s[:, rng.permutation(n)].copy(), 2)
+    w.adapt_levels, w.adapt_threshold = 3, 2
+    run_adaptive(kmc, w, 2, "fp64")
