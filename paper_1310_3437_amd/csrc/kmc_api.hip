@@ -242,7 +242,8 @@ size_t layout(Plan& p, char* base, uint32_t nboxes, const kmc_config& cfg, const
     p.C = (uint32_t)C;
     p.nboxes = nboxes;
     p.H = H;
-    p.nblk_scan = nblk;
+    p.scan_block = C > kNarrowCells ? 1024u : (uint32_t)kScanBlock;
+    p.nblk_scan = (uint32_t)((C + p.scan_block * kScanItems - 1) / (p.scan_block * kScanItems));
     // folding 1024 accumulators takes a block 5 to 9 us, more than a small gas
     // gains by spreading its few atomics (64 of them: 3.4 us)
     p.acc_lanes = N <= (1u << 18) ? 64u : (N <= (1u << 21) ? 256u : (uint32_t)kAccLanes);

@@ -429,9 +429,10 @@ __global__ void k_bin(Plan p)
 // blocks the down-sweep adds up the sums before it itself, and up to
 // kOneScanCells cells one block does everything: in a small gas a launch costs
 // more than its work (about 4 us each; 2.7e4 cells: three launches 12 us, one
-// 7).
+// 7).  Above kNarrowCells the blocks have 1024 threads, so that there are few
+// sums (2e7 cells, a million particles: block sums, scan and down-sweep 64 us
+// with blocks of 256, 54 with 1024 and no launch between).
 // --------------------------------------------------------------------------
-constexpr uint32_t kSumBlocks = 1024;
 constexpr uint32_t kOneScanCells = 32768;
 
 // Start of a step's device-side bookkeeping (recheck list, split cells and
@@ -458,16 +459,17 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* l
     }
     if (lane == 63) lds[wid] = x;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t s = 0;
-        for (int w = 0; w < nw; ++w) { uint32_t t = lds[w]; lds[w] = s; s += t; }
-        lds[nw] = s;
+    // every wave scans the (at most 16) wave totals for itself
+    uint32_t t = lane < nw ? lds[lane] : 0u;
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) {
+        const uint32_t y = __shfl_up(t, off, 64);
+        if (lane >= off) t += y;
     }
+    total = __shfl(t, nw - 1, 64);
+    const uint32_t before = __shfl(t, wid > 0 ? wid - 1 : 0, 64);
     __syncthreads();
-    const uint32_t excl = lds[wid] + x - v;
-    total = lds[nw];
-    __syncthreads();
-    return excl;
+    return (wid > 0 ? before : 0u) + x - v;
 }
 
 // The eight counts of cells base..base+7 (zero beyond the last cell), with
@@ -486,10 +488,10 @@ __device__ __forceinline__ void load_counts(const Plan& p, uint32_t base, uint32
     }
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_scan_reduce(Plan p)
+__global__ __launch_bounds__(1024) void k_scan_reduce(Plan p)
 {
-    __shared__ uint32_t lds[kScanBlock / 64 + 1];
-    const uint32_t base = blockIdx.x * (uint32_t)kScanTile + threadIdx.x * kScanItems;
+    __shared__ uint32_t lds[16];
+    const uint32_t base = (blockIdx.x * blockDim.x + threadIdx.x) * kScanItems;
     uint32_t v[kScanItems];
     load_counts(p, base, v);
     uint32_t s = 0;
@@ -504,7 +506,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_reduce(Plan p)
 // One block of 1024 threads scans the block sums in place.
 __global__ __launch_bounds__(1024) void k_scan_partials(Plan p)
 {
-    __shared__ uint32_t lds[1024 / 64 + 1];
+    __shared__ uint32_t lds[16];
     uint32_t carry = 0;
     for (uint32_t base = 0; base < p.nblk_scan; base += blockDim.x) {
         const uint32_t k = base + threadIdx.x;
@@ -516,8 +518,11 @@ __global__ __launch_bounds__(1024) void k_scan_partials(Plan p)
     }
 }
 
-// The starts st of the eight cells from base on written, their counts cleared.
-__device__ __forceinline__ void store_starts(const Plan& p, uint32_t base, const uint32_t st[kScanItems])
+// The starts st of the eight cells from base on written, their counts v cleared
+// (where there is anything to clear: half of the fours are empty at one
+// particle in six cells).
+__device__ __forceinline__ void store_starts(const Plan& p, uint32_t base, const uint32_t st[kScanItems],
+                                             const uint32_t v[kScanItems])
 {
     if (base + kScanItems <= p.C) {
         // 32-byte aligned runs of eight cells (the arrays are 256-byte aligned)
@@ -525,8 +530,8 @@ __device__ __forceinline__ void store_starts(const Plan& p, uint32_t base, const
         uint4* cp = reinterpret_cast<uint4*>(p.count + base);
         sp[0] = make_uint4(st[0], st[1], st[2], st[3]);
         sp[1] = make_uint4(st[4], st[5], st[6], st[7]);
-        cp[0] = make_uint4(0u, 0u, 0u, 0u);
-        cp[1] = make_uint4(0u, 0u, 0u, 0u);
+        if ((v[0] | v[1] | v[2] | v[3]) != 0u) cp[0] = make_uint4(0u, 0u, 0u, 0u);
+        if ((v[4] | v[5] | v[6] | v[7]) != 0u) cp[1] = make_uint4(0u, 0u, 0u, 0u);
     } else {
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
@@ -584,7 +589,7 @@ __global__ __launch_bounds__(1024) void k_scan_one(Plan p)
             st[k] = run;
             run += v[t][k];
         }
-        store_starts(p, (t * 1024u + threadIdx.x) * kScanItems, st);
+        store_starts(p, (t * 1024u + threadIdx.x) * kScanItems, st, v[t]);
     }
     if (threadIdx.x == 0) p.start[p.C] = p.N;
     begin_step(p);
@@ -592,9 +597,9 @@ __global__ __launch_bounds__(1024) void k_scan_one(Plan p)
 
 // SUMS: the block sums are as k_scan_reduce left them (else scanned).
 template <bool SUMS>
-__global__ __launch_bounds__(kScanBlock) void k_scan_down(Plan p)
+__global__ __launch_bounds__(1024) void k_scan_down(Plan p)
 {
-    __shared__ uint32_t lds[kScanBlock / 64 + 1];
+    __shared__ uint32_t lds[16];
     uint32_t before = 0;
     if (SUMS) {
         uint32_t a = 0;
@@ -603,7 +608,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_down(Plan p)
     } else {
         before = p.partial[blockIdx.x];
     }
-    const uint32_t base = blockIdx.x * (uint32_t)kScanTile + threadIdx.x * kScanItems;
+    const uint32_t base = (blockIdx.x * blockDim.x + threadIdx.x) * kScanItems;
     uint32_t v[kScanItems];
     load_counts(p, base, v);
     uint32_t s = 0;
@@ -617,7 +622,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_down(Plan p)
         st[k] = run;
         run += v[k];
     }
-    store_starts(p, base, st);
+    store_starts(p, base, st, v);
     if (blockIdx.x == 0 && threadIdx.x == 0) p.start[p.C] = p.N;
     if (p.adapt_L > 0) {
         // adaptive bins: this step's split level of every cell from its count;
@@ -649,7 +654,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_down(Plan p)
                 xn += yn;
             }
         }
-        __shared__ uint32_t wsum[2][kScanBlock / 64];
+        __shared__ uint32_t wsum[2][16];
         const int wid = threadIdx.x >> 6, nw = (int)(blockDim.x >> 6);
         if (lane == 63) {
             wsum[0][wid] = xs;
@@ -3250,12 +3255,12 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
     if (p.C <= kOneScanCells && p.adapt_L == 0) {
         k_scan_one<<<1, 1024, 0, s>>>(p);
     } else {
-        k_scan_reduce<<<p.nblk_scan, kScanBlock, 0, s>>>(p);
+        k_scan_reduce<<<p.nblk_scan, p.scan_block, 0, s>>>(p);
         if (p.nblk_scan <= kSumBlocks) {
-            k_scan_down<true><<<p.nblk_scan, kScanBlock, 0, s>>>(p);
+            k_scan_down<true><<<p.nblk_scan, p.scan_block, 0, s>>>(p);
         } else {
             k_scan_partials<<<1, 1024, 0, s>>>(p);
-            k_scan_down<false><<<p.nblk_scan, kScanBlock, 0, s>>>(p);
+            k_scan_down<false><<<p.nblk_scan, p.scan_block, 0, s>>>(p);
         }
     }
     if (p.adapt_L > 0 && p.N > 0) {

@@ -13,6 +13,8 @@ namespace kmc {
 constexpr int kScanBlock = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanBlock * kScanItems;
+constexpr uint32_t kNarrowCells = 1u << 21;   // the scan's blocks: kScanBlock threads up to here, else 1024
+constexpr uint32_t kSumBlocks = 4096;          // ... its down-sweep adds up the block sums itself up to here
 // Per-step accumulators of the collision count, the digest and the recorded
 // candidates: one 128-byte line each, so the per-block atomics of the search
 // and the resolve spread over this many cache lines (k_advance folds them).
@@ -136,6 +138,7 @@ struct Plan {
     unsigned long long* box_v2;    // adaptive dt: per box, max |v|^2 of the other particles
     uint32_t N, C, nboxes, H;
     uint32_t nblk_scan;
+    uint32_t scan_block;
     uint32_t acc_lanes;            // accumulators in use (a multiple of 64, at most kAccLanes)
     uint32_t recheck_cap;
     uint64_t seed;

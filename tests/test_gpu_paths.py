@@ -162,3 +162,13 @@ def test_leaf_lists(kmc, ncell, thin):
     w = I.Workload("leaves", [box], s[:, rng.permutation(n)].copy(), 2)
     w.adapt_levels, w.adapt_threshold = 3, 2
     run_adaptive(kmc, w, 2, "fp64")
+
+
+@pytest.mark.parametrize("ncell", [128, 129, 322, 323])
+def test_scan_of_large_grids(kmc, ncell):
+    """2^21 cells and above (blocks of 1024 threads), 4096 of these blocks and
+    above (their sums scanned between); most cells empty."""
+    box, s = I.uniform_box(20_011, ncell=ncell, D=0.9 / ncell, ic_seed=ncell, dt=0.02)
+    s[0:3, :9000] = 0.5 + s[0:3, :9000] * 0.02
+    _, exact = run_parity(kmc, I.Workload("sparse", [box], s, 2), 2)
+    assert exact
