@@ -1712,8 +1712,6 @@ __global__ __launch_bounds__(64 * kSpanClasses) void k_step_setup(Plan p)
     if (!safe && lane == 0) atomicOr(&p.ctl->overflow, 1u);
 }
 
-// K: particles of several kinds (the screen's folded D2 constant of each
-// pair of kinds from a per-box table in LDS); otherwise the box's constant.
 // a < 0 and b < 0 (neither is NaN), by their sign bits: one comparison.  FP32
 // sums, products and logic on vector registers issue at twice the rate of
 // comparisons and of anything with a scalar operand here (measured 1.5 to 1.75
@@ -1726,6 +1724,8 @@ __device__ __forceinline__ bool both_negative(float a, float b)
     return (int)(__float_as_uint(a) & __float_as_uint(b)) < 0;
 }
 
+// K: particles of several kinds (the screen's folded D2 constant of each
+// pair of kinds from a per-box table in LDS); otherwise the box's constant.
 template <bool K, class T = TileF32_0>
 struct PolF32 {
     static constexpr int W = K ? T::W * 3 / 4 : T::W;   // (with kinds, 24 waves would not fit a CU's LDS)
