@@ -1321,7 +1321,9 @@ struct Best {
     __device__ __forceinline__ void clear()
     {
         key = __builtin_inf();
-        kcut = __builtin_inff();
+        // finite: its product with a g2 of zero (velocities equal in FP32 and not
+        // in FP64) is zero, and the pair stays
+        kcut = 0x1.fffffep127f;
         id = 0xFFFFFFFFu;
         j = -1;
         accepted = 0u;

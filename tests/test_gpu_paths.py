@@ -172,3 +172,52 @@ def test_scan_of_large_grids(kmc, ncell):
     s[0:3, :9000] = 0.5 + s[0:3, :9000] * 0.02
     _, exact = run_parity(kmc, I.Workload("sparse", [box], s, 2), 2)
     assert exact
+
+
+def side_by_side(kinds=False):
+    """Pairs on a lattice whose velocities are equal in FP32 and differ by one
+    part in 2^30 in FP64, side by side (r perpendicular to g, so closest now) or
+    at the same place; next to every third pair a particle that passes both at a
+    larger distance."""
+    rng = np.random.default_rng(31)
+    nc = 30
+    h = 1.0 / nc
+    D = 0.9 * h
+    pts = []
+    for k in range(1000):
+        ctr = (3 * np.array([k // 100, k // 10 % 10, k % 10]) + 1.5) * h
+        a, b = rng.permutation(3)[:2]
+        v, w = np.zeros(3), np.zeros(3)
+        v[a] = rng.uniform(0.5, 2.0)
+        w[a] = v[a] * (1.0 + 2.0 ** -30)
+        x, y = ctr.copy(), ctr.copy()
+        y[b] += 0.0 if k % 8 == 0 else D * rng.uniform(0.05, 0.6)
+        pts += [(x, v), (y, w)]
+        if k % 3 == 0:
+            c, g = 3 - a - b, rng.uniform(0.5, 2.0)
+            z, u = x.copy(), v.copy()
+            z[c] -= 0.8 * D
+            z[a] -= 0.005 * g
+            u[a] += g
+            pts.append((z, u))
+    s = np.array([np.concatenate(q) for q in pts]).T
+    s = s[:, rng.permutation(s.shape[1])].copy()
+    n = s.shape[1]
+    box = I.Box(n=n, lo=(0, 0, 0), hi=(1, 1, 1), ncell=(nc,) * 3, periodic=(True,) * 3, D2=D * D, dt=0.01)
+    if not kinds:
+        return I.Workload("side_by_side", [box], s, 1)
+    return I.Workload("side_by_side", [box], s, 1, species=rng.integers(0, 2, n).astype(np.uint8),
+                      radius=(0.5 * D, 0.45 * D), mass=(1.0, 3.0))
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("kinds", [False, True])
+def test_velocities_equal_in_fp32(kmc, kinds, tile):
+    """The screen's g2 is zero and FP64's is not: the pair is acceptable, and no
+    search may drop it."""
+    w = side_by_side(kinds)
+    kw = dict(kinds=(w.species, w.radius, w.mass)) if kinds else {}
+    for mode in (kmc.KMC_SEARCH_FULL, kmc.KMC_SEARCH_HALF):
+        for precision in ("fp32", "fp64"):
+            d, exact = run_parity(kmc, w, 1, precision=precision, search_mode=mode, tile=tile, **kw)
+            assert exact and d[0][0] > 500
