@@ -1586,7 +1586,12 @@ __device__ __forceinline__ void screen_thresholds(const BoxDev& B, const double 
     g.tb0 = (float)t[0];
     g.tb1 = (float)t[1];
     g.tt0 = (float)t[2];
-    g.tc0 = (float)t[4];
+    // The relative bounds do not see products that underflow: b^2 and the last
+    // product of the m3 test each lose up to 2^-150 (the errors that underflow
+    // leaves in b and g2 are a small fraction of the bounds for edges and speeds
+    // of at least 2^-40, where tc0 is 2^-180 or more).  2^-140 covers them, also
+    // in the pruning's use of tc.
+    g.tc0 = (float)t[4] + 0x1p-140f;
     // Folded constants, rounded up (the factor 1 + 2e-6 exceeds every rounding
     // here).  m2: -b - kdt g2 <= -b - (dt + tt1) g2 for kdt >= dt + tt1, and the
     // screen's one rounding of the FMA is monotone.  m3: the screen sums
@@ -1638,7 +1643,7 @@ __device__ __forceinline__ void screen_thresholds(const BoxDev& B, const double 
 // of kinds); true in every lane when the screen is safe to use.
 //
 // The bounds take FP32 arithmetic to neither overflow nor lose to underflow
-// more than a small fraction of them: cell edges in [2^-40, 2^40], the largest
+// more than a small fraction of them (beside what tc0 allows for): cell edges in [2^-40, 2^40], the largest
 // speed 0 or in [2^-40, 2^40], the pair test's largest products (|r|^2 g2 <=
 // 144 h^2 V^2 and the folded thresholds times g2 <= 12 V^2) below 2^120, every
 // threshold finite.  Outside that range this step's partners come from the

@@ -221,3 +221,18 @@ def test_velocities_equal_in_fp32(kmc, kinds, tile):
         for precision in ("fp32", "fp64"):
             d, exact = run_parity(kmc, w, 1, precision=precision, search_mode=mode, tile=tile, **kw)
             assert exact and d[0][0] > 500
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("pos,vel", [(25, 38), (30, 34), (34, 34), (35, 38)])
+def test_screen_of_small_scales(kmc, pos, vel, tile):
+    """Lengths of 2^-pos and speeds of 2^-vel, inside the screen's range of edges
+    and speeds, where the products of its test underflow in FP32: it stays on
+    and stays exact."""
+    for seed in (31, 32, 33):
+        w = S.scaled(S.adversarial(seed=seed), pos=2.0 ** -pos, vel=2.0 ** -vel)
+        for mode in (kmc.KMC_SEARCH_FULL, kmc.KMC_SEARCH_HALF):
+            for guard in (0.0, 1.0):
+                mism, same, stats = S.gpu_vs_oracle(kmc, w, kmc.KMC_FP32_SCREEN, search_mode=mode, tile=tile,
+                                                    guard_scale=guard)
+                assert mism == 0 and same and stats["fallbacks"] == 0
