@@ -167,7 +167,9 @@ typedef struct kmc_config {
                                   screen's undecided ones, and any particle with more
                                   candidates than the search records) before the whole
                                   step falls back to the full FP64 search;
-                                  0 = all particles (never falls back)                   */
+                                  0 = all particles.  Beyond n_total / 6 + 4096 of them
+                                  the whole step falls back in any case (it is then the
+                                  faster way to the same partners)                       */
     int32_t use_graph;         /* 1: each step is replayed from a captured hipGraph      */
     int32_t block_size;        /* threads per block, multiple of 64 in [64, 1024]; 0 = 256 */
     int32_t profile;           /* 1: time every phase with HIP events (disables graphs)  */
@@ -257,11 +259,11 @@ typedef struct kmc_stats {
     uint64_t rechecks;         /* particles listed for a full FP64 re-search (more list
                                   entries than slots, or next to a search wave that
                                   found more pairs than it holds), summed over steps;
-                                  in a step
-                                  that takes the whole-step FP64 search they are
-                                  covered by it                                         */
+                                  in a step that takes the whole-step FP64 search they
+                                  are covered by it                                     */
     uint64_t fallbacks;        /* steps that took the whole-step FP64 search (a list
-                                  overflowed, or the FP32 screen's assumptions failed)  */
+                                  overflowed, too many particles were listed, or the
+                                  FP32 screen's assumptions failed)                     */
     double ms[8];              /* accumulated milliseconds per phase (profile mode)      */
     uint64_t timed_steps;      /* steps that contributed to ms                          */
     double search_kernel_ms;   /* accumulated milliseconds of the search kernel alone   */

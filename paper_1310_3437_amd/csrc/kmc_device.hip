@@ -2379,7 +2379,8 @@ constexpr uint32_t kRecheckShare = 6;
 constexpr uint32_t kFallbackBlocks = 4096;
 
 // Whether this step's partners come from the whole-step search: its flag is
-// set, or the re-search has too many particles.
+// set, or the re-search has too many particles.  (The direct search lists none;
+// with the flag set it decides every pair in FP64 itself.)
 __device__ __forceinline__ bool whole_step(const Plan& p)
 {
     return p.ctl->overflow != 0u || p.ctl->recheck_count > p.N / kRecheckShare + kFallbackBlocks;
@@ -3167,7 +3168,7 @@ __global__ __launch_bounds__(1024) void k_advance(Plan p)
         p.hist_dig[done % p.H] = dig;
         p.ctl->candidates_total += cand;
         p.ctl->rechecks_total += p.ctl->recheck_count;
-        p.ctl->fallbacks_total += p.ctl->overflow ? 1ull : 0ull;
+        p.ctl->fallbacks_total += whole_step(p) ? 1ull : 0ull;
         p.ctl->steps_done = done + 1;
         p.ctl->step += 1;
     }

@@ -236,3 +236,16 @@ def test_screen_of_small_scales(kmc, pos, vel, tile):
                 mism, same, stats = S.gpu_vs_oracle(kmc, w, kmc.KMC_FP32_SCREEN, search_mode=mode, tile=tile,
                                                     guard_scale=guard)
                 assert mism == 0 and same and stats["fallbacks"] == 0
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_fallbacks_count_the_whole_step_searches(kmc, precision):
+    """Steps that list more than n / 6 + 4096 particles for the re-search take
+    the whole-step search, whatever the list's capacity, and are counted."""
+    prec = kmc.KMC_FP64 if precision == "fp64" else kmc.KMC_FP32_SCREEN
+    for D, dt, whole in ((0.1, 0.05, 2), (0.05, 0.02, 0)):
+        w = dense_gas(n=20_011, D=D, dt=dt)
+        mism, same, stats = S.gpu_vs_oracle(kmc, w, prec, steps=2)
+        assert mism == 0 and same
+        assert (stats["rechecks"] > 2 * (w.n // 6 + 4096)) == (whole > 0)
+        assert stats["fallbacks"] == whole
