@@ -249,3 +249,17 @@ def test_fallbacks_count_the_whole_step_searches(kmc, precision):
         assert mism == 0 and same
         assert (stats["rechecks"] > 2 * (w.n // 6 + 4096)) == (whole > 0)
         assert stats["fallbacks"] == whole
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("periodic", [True, False])
+def test_lost_pairs_in_short_rows(kmc, periodic, precision):
+    """Rows of three and five cells, every window of several cells and most of
+    them across the seam, many acceptable partners: whatever a wave's list of
+    extra pairs cannot hold is marked for the re-search, in the own row, the
+    other rows and the wrapped end cells."""
+    for n, ncell, tile, dt in ((2003, 3, 1, 0.007), (6007, 5, 2, 0.0062), (6007, 5, 1, 0.0068), (6007, 5, 1, 0.1)):
+        box, s = I.uniform_box(n, ncell=ncell, D=0.9 / ncell, periodic=periodic, ic_seed=n, dt=dt)
+        _, exact = run_parity(kmc, I.Workload("short_rows", [box], s, 2), 2, precision=precision, tile=tile)
+        assert exact
+        assert run_parity.last_stats["rechecks"] > 0
