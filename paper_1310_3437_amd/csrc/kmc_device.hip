@@ -1370,6 +1370,12 @@ struct Best {
 // overtaken pairs staying in them, took 18.9 ms on the blobs for the particles
 // searched again.
 constexpr int kDefer = 5;
+// Up to this many particles of a tile the wave searches again itself, one after
+// another (about 4 us each).  More of them, where velocities are equal in FP32
+// and no pair can be told from another (beams, a gas at rest), go to the step's
+// list (1e6 particles of one velocity: 1130 us a step by the waves themselves,
+// 660 by the list, which gives way to the whole-step search).
+constexpr int kAgainAlone = 16;
 struct DeferLds {
     uint32_t j[kDefer][64];      // sorted index
     float lo[kDefer][64];        // lower bound of the key
@@ -1908,6 +1914,7 @@ struct PolF32 {
                     if (d.l->lo[e][threadIdx.x] > best.kcut) k = e;
                 if (k < 0) {
                     d.n = kDefer + 1;
+                    best.kcut = -__builtin_inff();   // searched again: nothing more to record
                     return;
                 }
             }
@@ -2239,6 +2246,24 @@ __device__ int32_t search_one64_wave(const Plan& p, uint32_t i)
     return best;
 }
 
+// Wave-aggregated append of this lane's particle to the FP64 recheck list
+// (all lanes of the wave must call it).
+__device__ __forceinline__ void push_recheck(const Plan& p, uint32_t i, bool need)
+{
+    const uint64_t mask = __ballot(need);
+    if (!mask) return;
+    const int lane = threadIdx.x & 63;
+    const int leader = __ffsll((unsigned long long)mask) - 1;
+    uint32_t base = 0;
+    if (lane == leader) base = atomicAdd(&p.ctl->recheck_count, (unsigned int)__popcll(mask));
+    base = (uint32_t)__builtin_amdgcn_readlane((int)base, leader);
+    if (need) {
+        const uint32_t idx = base + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+        if (idx < p.recheck_cap) p.recheck[idx] = i;
+        else atomicOr(&p.ctl->overflow, 1u);
+    }
+}
+
 // Full-neighbourhood variant of the search (KMC_SEARCH_FULL): every
 // particle scans its own and all 26 neighbouring cells and keeps the running
 // (key, id) minimum in registers, writing its partner directly.  It tests
@@ -2353,6 +2378,10 @@ __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, t
     if constexpr (Pol::kScreen) {
         // particles with more deferred pairs than slots
         uint64_t again = __ballot(dfr.n > kDefer);
+        if (__popcll(again) > kAgainAlone) {
+            push_recheck(p, i, dfr.n > kDefer);
+            again = 0;
+        }
         while (again) {
             const int l = __ffsll((unsigned long long)again) - 1;
             again &= again - 1;
@@ -2901,24 +2930,6 @@ __global__ __launch_bounds__(64) void k_search_direct(Plan p)
     if (lane == 0 && c) atomicAdd(&p.acc[blockIdx.x % p.acc_lanes].cand, (unsigned long long)c);
 }
 
-// Wave-aggregated append of this lane's particle to the FP64 recheck list
-// (all lanes of the wave must call it).
-__device__ __forceinline__ void push_recheck(const Plan& p, uint32_t i, bool need)
-{
-    const uint64_t mask = __ballot(need);
-    if (!mask) return;
-    const int lane = threadIdx.x & 63;
-    const int leader = __ffsll((unsigned long long)mask) - 1;
-    uint32_t base = 0;
-    if (lane == leader) base = atomicAdd(&p.ctl->recheck_count, (unsigned int)__popcll(mask));
-    base = (uint32_t)__builtin_amdgcn_readlane((int)base, leader);
-    if (need) {
-        const uint32_t idx = base + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-        if (idx < p.recheck_cap) p.recheck[idx] = i;
-        else atomicOr(&p.ctl->overflow, 1u);
-    }
-}
-
 // Partner of every particle: the (key, id) minimum of its forward best (the
 // pairs its own search lane found) and the entries of its candidate list
 // (pairs found from the other side, or through the overflow list); keys are
@@ -3329,8 +3340,8 @@ hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev)
         k_finish<<<blocks_for(p.N, 256), 256, 0, s>>>(p);
     }
     mark(KMC_PHASE_RECHECK);
-    // (the full search lists nothing; the FP32 sorted copy may still ask for
-    // the whole-step search)
+    // (in FP64 the full search lists nothing; under the FP32 screen it may, and
+    // the sorted copy may ask for the whole-step search)
     if (p.N > 0 && dg == 0 && (!full || p.precision == KMC_FP32_SCREEN)) {
         const uint32_t g = gW < kFallbackBlocks ? gW : kFallbackBlocks;
         if (p.nspecies > 0) k_research<PolF64<true>><<<g, 64, 0, s>>>(p);

@@ -263,3 +263,19 @@ def test_lost_pairs_in_short_rows(kmc, periodic, precision):
         _, exact = run_parity(kmc, I.Workload("short_rows", [box], s, 2), 2, precision=precision, tile=tile)
         assert exact
         assert run_parity.last_stats["rechecks"] > 0
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("share,whole", [(1.0, 2), (0.2, 0)])
+def test_full_search_of_beams(kmc, share, whole, tile):
+    """Particles of one velocity (to 2^-30) in part of a gas: the screen tells
+    none of their pairs apart, and their waves list them for the re-search,
+    which the whole-step search replaces where it is the whole gas."""
+    w = dense_gas(n=20_011, D=0.05, dt=0.005)
+    beam = w.state[1] < share
+    v = np.array([1.0, 0.5, 0.25])[:, None]
+    w.state[3:6, beam] = v * (1.0 + 2.0 ** -30 * w.state[3:6, beam])
+    mism, same, stats = S.gpu_vs_oracle(kmc, w, kmc.KMC_FP32_SCREEN, steps=2, tile=tile,
+                                        search_mode=kmc.KMC_SEARCH_FULL)
+    assert mism == 0 and same
+    assert stats["rechecks"] > w.n / 6 and stats["fallbacks"] == whole
