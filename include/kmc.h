@@ -257,9 +257,9 @@ typedef struct kmc_stats {
     uint64_t n_total;          /* particles over all boxes                              */
     uint64_t cells_total;      /* cells over all boxes                                  */
     uint64_t rechecks;         /* particles listed for a full FP64 re-search (more list
-                                  entries than slots, next to a search wave that found
-                                  more pairs than it holds, or among many whose pairs
-                                  the FP32 screen cannot tell apart), summed over steps;
+                                  entries than slots, in a pair that a search wave had
+                                  no room for, or among many whose pairs the FP32
+                                  screen cannot tell apart), summed over steps;
                                   in a step that takes the whole-step FP64 search they
                                   are covered by it                                     */
     uint64_t fallbacks;        /* steps that took the whole-step FP64 search (a list

@@ -1087,8 +1087,9 @@ __device__ __forceinline__ bool exact_key(const Plan& p, const BoxDev& B, uint32
 // division inside the search loop would stall the whole wave).  A lane that
 // finds more than kReg appends the excess to the wave's list of extra pairs
 // in LDS, which the wave decides and posts together at its end.  When that
-// list is full the lane remembers that it lost pairs, and its particle and
-// those of its window are marked for the full FP64 re-search.
+// list is full, both particles of a further pair are marked for the full FP64
+// re-search.  (Marking a lane's whole window instead made re-searches of whole
+// clusters: 1.8e5 particles in four clusters 8.8 ms a step against 4.0.)
 // In a Maxwellian gas at three particles per cell (about three acceptable
 // partners each) 1.4% of the lanes find more than four; when each of these
 // pairs took an atomic on one step-wide counter the search waited on it
@@ -1153,12 +1154,14 @@ struct Found {
     uint32_t* sj; // this lane's kept indices in LDS: pair k at sj[64 k] (one store per pair
                   // instead of a select over register slots)
     uint32_t w;   // image shift of pair k in bits 6k..6k+5: (wx+1) | (wy+1) << 2 | (wz+1) << 4;
-                  // bit 31: the lane lost a pair in the current part of a row
+                  // bit 31: the lane lost a pair
     int n;
-    __device__ __forceinline__ void clear(Extra* e, uint32_t* slots)
+    uint32_t* lists;   // lengths of the candidate lists
+    __device__ __forceinline__ void clear(Extra* e, uint32_t* slots, uint32_t* l)
     {
         extra = e;
         sj = slots;
+        lists = l;
         n = 0;
         w = kNoImage * 0x41041u;   // no image in every slot
     }
@@ -1186,36 +1189,21 @@ struct Found {
     template <class M>
     __device__ __forceinline__ void add(uint32_t f, const M& m)
     {
-        if (n < kReg) {
+        if (__builtin_expect(n < kReg, 1)) {
             keep(f, m);
             return;
         }
         const uint32_t t = atomicAdd(&extra->n, 1u);
-        if (t < kExtra) {
-            uint32_t code;   // (the exact decision finds the image from the cells)
-            extra->j[t] = m.at(f, code);
+        uint32_t code;   // (the exact decision finds the image from the cells)
+        const uint32_t j = m.at(f, code);
+        if (__builtin_expect(t < kExtra, 1)) {
+            extra->j[t] = j;
             extra->lane[t] = (uint8_t)threadIdx.x;
         } else {
+            uint32_t k = j;
+            asm("" : "+v"(k));   // (keeps the address out of the pair loop)
             w |= 0x80000000u;
-        }
-    }
-    // After a part of a row in which lanes lost pairs: their particles and their
-    // windows [lf, le) go to the full re-search.  The wave marks the span of
-    // these windows, which begin and end in the order of the lanes, once: each
-    // lane marking its own made an atomic of every pair test (5e5 particles at
-    // 100 per cell, most of them acceptable partners: 30.0 -> 4.2 ms a step).
-    template <class M>
-    __device__ __forceinline__ void mark_lost(const Plan& p, uint32_t i, uint32_t lf, uint32_t le, const M& m)
-    {
-        const uint64_t lost = __ballot((int32_t)w < 0);
-        if (lost == 0) return;
-        if ((int32_t)w < 0) (void)atomicAdd(&p.sl_cnt[i], kMarked);
-        w &= 0x7FFFFFFFu;
-        const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)lf, __ffsll((unsigned long long)lost) - 1);
-        const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)le, 63 - __clzll((long long)lost));
-        for (uint32_t f = s + (threadIdx.x & 63u); f < e; f += 64u) {
-            uint32_t code;
-            (void)atomicAdd(&p.sl_cnt[m.at(f, code)], kMarked);
+            (void)atomicAdd(&lists[k], kMarked);
         }
     }
     // Decide the kept pairs exactly in FP64 (the FP32 screen keeps pairs it
@@ -1312,9 +1300,19 @@ struct Found {
     }
 };
 
-// Per-group context of the search (the FP64 search needs none).
-struct NoGroup {
+// Per-group context of the FP64 search: the criteria's constants, in scalar
+// registers (loaded per chunk they were waited for before its pair loop).
+struct Group64 {
+    double D2, dt;
 };
+
+__device__ __forceinline__ double uniform64(double x)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
 
 // Running (key, id) minimum of one lane in the full-neighbourhood search.
 struct Best {
@@ -1427,9 +1425,13 @@ struct PolF64 {
         P64 me;
         uint32_t row;   // K: kMaxKinds * own kind
     };
-    using Group = NoGroup;
-    __device__ static void begin_group(const Lds&, const Plan&, const BoxDev&, Own&, Group&, int, int, int, int, int, uint32_t,
-                                       bool) {}
+    using Group = Group64;
+    __device__ static void begin_group(const Lds&, const Plan&, const BoxDev& B, Own&, Group& g, int, int, int, int, int,
+                                       uint32_t, bool)
+    {
+        g.D2 = uniform64(B.D2);
+        g.dt = uniform64(B.dt);
+    }
     // per-group LDS tables, written before the group's first staging barrier
     __device__ static void group_lds(Lds& l, const Plan& p, uint32_t, int lane)
     {
@@ -1450,10 +1452,10 @@ struct PolF64 {
     }
     template <bool SH, class M>
     __device__ static void scan(const Lds& l, uint32_t c0, uint32_t j0, uint32_t j1, const Own& o, const BoxDev& B,
-                                const Group&, const M& m, Found& f)
+                                const Group& g, const M& m, Found& f)
     {
         const double sx = (double)m.wx * B.L[0], sy = (double)m.wy * B.L[1], sz = (double)m.wz * B.L[2];
-        const double D2 = B.D2, dt = B.dt;
+        const double D2 = g.D2, dt = g.dt;
         for (uint32_t j = j0; j < j1; ++j) {
             const P64 q = l.rec[j - c0];
             double rx = q.x - o.me.x, ry = q.y - o.me.y, rz = q.z - o.me.z;
@@ -1467,10 +1469,10 @@ struct PolF64 {
     // (the particle itself has g2 = 0 and is never accepted)
     template <bool SH, class M>
     __device__ static void scan_best(const Lds& l, const uint32_t* lid, uint32_t c0, uint32_t j0, uint32_t j1, uint32_t,
-                                     const Own& o, const BoxDev& B, const Group&, const M& m, Best& best, Deferred&)
+                                     const Own& o, const BoxDev& B, const Group& g, const M& m, Best& best, Deferred&)
     {
         const double sx = (double)m.wx * B.L[0], sy = (double)m.wy * B.L[1], sz = (double)m.wz * B.L[2];
-        const double D2 = B.D2, dt = B.dt;
+        const double D2 = g.D2, dt = g.dt;
         for (uint32_t j = j0; j < j1; ++j) {
             const P64 q = l.rec[j - c0];
             double rx = q.x - o.me.x, ry = q.y - o.me.y, rz = q.z - o.me.z;
@@ -2067,7 +2069,7 @@ void k_search_half(Plan p)
     __shared__ Extra extra;
     if (lane == 0) extra.n = 0u;   // (a barrier follows before the first pair is tested)
     Found found;
-    found.clear(&extra, found_j + lane);
+    found.clear(&extra, found_j + lane, p.sl_cnt);
     uint64_t remaining = __ballot(alive);
     while (remaining) {
         const int lead = __ffsll((unsigned long long)remaining) - 1;
@@ -2108,7 +2110,6 @@ void k_search_half(Plan p)
                 else Pol::template scan<false>(lds, c0, f0, f1, own, B, gctx, m, found);
                 __syncthreads();
             }
-            found.mark_lost(p, i, lf, le, m);
         };
         // Rows of the half neighbourhood: the own one (from the particle on,
         // through cell cx+1), then (dy, dz) = (+1, 0), (-1, +1), (0, +1),
@@ -2147,6 +2148,7 @@ void k_search_half(Plan p)
     uint32_t c = valid ? found.template flush<Pol::kFlushBatch, Pol::kFlushSkipEmpty, Pol::kKinds>(p, i, Pol::self64(p, i, own),
                                                                                        p.boxes[bidx])
                        : 0u;
+    if (found.w >> 31) (void)atomicAdd(&p.sl_cnt[i], kMarked);
     __syncthreads();   // every lane's extra pairs are in LDS
     if (lane == 0) c += extra.n;
     found.flush_extra(p, xcd_tile(blockIdx.x, gridDim.x) * 64u, (uint32_t)lane);
