@@ -301,6 +301,8 @@ void fill_box_dev(BoxDev& d, const kmc_box& b, uint32_t coff, uint32_t poff)
     d.dt_32 = (float)b.dt;
 }
 
+constexpr uint64_t kDirectAlways = 49152;
+
 // Lanes per particle of the direct search, or 0 for the staged searches.
 //
 // The direct search tests about twice the pairs without reusing a record, but
@@ -311,8 +313,9 @@ void fill_box_dev(BoxDev& d, const kmc_box& b, uint32_t coff, uint32_t poff)
 // against 114 at 1.2e5 (10 M tests), and loses from there on; thinner gases
 // keep the gain longer (0.03 per cell, 1e5 particles: 72 against 153) until
 // 2^18 particles, above which 0.05 per cell is as fast staged (3e5: 105
-// against 102).  Gases in dense blobs gain as well, although they test far
-// more pairs than their mean density says (2.5e5 in 64 blobs: 166 against 248).
+// against 102).  Clustered gases test far more pairs than their mean density
+// says; up to 49152 particles that leaves the chip idle all the same (4.9e4 in
+// two clusters, 1e9 tests: 1.9 to 2.1 ms against 3.2 to 9.8), above see direct_tests.
 // More lanes per particle shorten the chain of loads and leave more of them
 // without a candidate (16, 8 and 4 lanes: 52, 54, 61 us at 1e4 particles, 64,
 // 60, 65 at 3e4, 83, 75, 72 at 6e4).
@@ -327,7 +330,29 @@ int32_t direct_lanes(const kmc_box* boxes, uint32_t nboxes, const kmc_config& cf
         tests += (cfg.dims == 2 ? 9.0 : 27.0) * (double)boxes[b].n * (double)boxes[b].n / cells;
     }
     if (tests > 6e6) return 0;
-    return N <= 16384 ? 16 : (N <= 49152 ? 8 : 4);
+    return N <= 16384 ? 16 : (N <= kDirectAlways ? 8 : 4);
+}
+
+// Pair tests of the initial state up to which a gas of more than kDirectAlways
+// particles takes the direct search.  Its cost is in proportion to them; the
+// staged searches' is not, where one wave's cells hold most of them, and the
+// more particles there are the better these fill the chip, the FP32 screen's
+// half search first.  Gases in 2 to 512 clusters, direct against staged:
+//   FP64 half  6e4 particles, 3e8 tests 867 : 1038 us, 1.5e9 3.1 : 12.0 ms;
+//              1.3e5, 1.8e8 457 : 690 us, 5.4e8 1176 : 1003; 2.5e5, 2e8 517 : 390
+//   FP64 full  1.3e5, 1.4e9 2.9 : 3.3 ms; 2.5e5, 6.8e8 1.3 : 1.5, 2e9 3.6 : 3.3
+//   FP32 half  9e4, 8.8e7 269 : 302 us, 2.6e8 654 : 433; 1.3e5, 5.4e7 200 : 184;
+//              2.5e5, 2.6e7 159 : 171
+//   FP32 full  6e4, 1.2e8 369 : 410 us; 9e4, 2.6e8 653 : 546; 1.3e5, 5.4e7
+//              196 : 232; 1.8e5, 1e8 303 : 248
+// A gas that gathers into clusters later keeps the choice made for its initial
+// state.
+double direct_tests(const kmc_config& cfg, uint64_t N)
+{
+    const bool full = cfg.search_mode == KMC_SEARCH_FULL;
+    if (cfg.precision == KMC_FP32_SCREEN) return N <= 98304 ? (full ? 1.5e8 : 1e8) : (full ? 8e7 : 4e7);
+    if (N <= 98304 || (full && N <= 163840)) return INFINITY;
+    return full ? 1e9 : (N <= 163840 ? 3e8 : 6e7);
 }
 
 int dev_err(hipError_t e) { return e == hipSuccess ? KMC_OK : KMC_EDEVICE; }
@@ -463,7 +488,10 @@ int kmc_init(const kmc_box* boxes, uint32_t nboxes, const kmc_config* cfg, const
             e = hipMemcpyAsync((void*)c->plan.sp_mass, mtab.data(), sizeof(double) * mtab.size(), hipMemcpyHostToDevice, s);
     }
     if (e == hipSuccess) e = launch_init(c->plan, d_state, cfg->species ? cfg->species->d_kind : nullptr, s);
-    unsigned long long bad_kinds = 0;
+    const double max_tests = t.N > kDirectAlways ? direct_tests(*cfg, t.N) : INFINITY;
+    const bool counted = c->plan.direct > 0 && std::isfinite(max_tests);
+    if (e == hipSuccess && counted) e = launch_init_tests(c->plan, s);
+    unsigned long long bad_kinds = 0, tests = 0;
     if (e == hipSuccess) {
         // the step counter starts at step0 (k_init_ctl wrote 0); the kind
         // check counted its failures in the control block's scratch word
@@ -471,9 +499,12 @@ int kmc_init(const kmc_box* boxes, uint32_t nboxes, const kmc_config* cfg, const
         e = hipMemcpyAsync(&c->plan.ctl->step, &step0, sizeof(step0), hipMemcpyHostToDevice, s);
         if (e == hipSuccess)
             e = hipMemcpyAsync(&bad_kinds, &c->plan.ctl->scratch, sizeof(bad_kinds), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess && counted)
+            e = hipMemcpyAsync(&tests, &c->plan.ctl->tests_init, sizeof(tests), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);   // host buffers live on this stack frame
     }
     if (e != hipSuccess) { delete c; return KMC_EDEVICE; }
+    if ((double)tests > max_tests) c->plan.direct = 0;
     if (bad_kinds != 0) { delete c; return KMC_EINVAL; }
     *out = c;
     return KMC_OK;

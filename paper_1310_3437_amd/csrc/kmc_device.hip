@@ -301,6 +301,7 @@ __global__ void k_init_ctl(Plan p, unsigned long long step0)
         p.ctl->absorbed_total = 0;
         p.ctl->candidates_total = 0;
         p.ctl->scratch = 0;
+        p.ctl->tests_init = 0;
     }
     for (uint32_t k = t; k < (uint32_t)kAccLanes; k += blockDim.x) {
         p.acc[k].np = 0;
@@ -3224,6 +3225,39 @@ __global__ __launch_bounds__(256) void k_count_tests(Plan p, unsigned long long*
     if (threadIdx.x == 0) atomicAdd(out, (unsigned long long)t);
 }
 
+// Candidates of all particles of the initial state, from the cell counts of
+// its binning (before the first step's scan clears them).
+__global__ __launch_bounds__(256) void k_init_tests(Plan p)
+{
+    __shared__ uint64_t lds[32];
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    uint64_t t = 0, z = 0;
+    if (i < p.N) {
+        const BoxDev& B = box_of(p, i);
+        const P64 me = p.A[i];
+        const double xs[3] = {me.x, me.y, me.z};
+        int c[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) c[a] = cell1(xs[a], B.lo[a], B.inv_h[a], B.nc[a]);
+        for (int k = 0; k < 27; ++k) {
+            const int d[3] = {k % 3 - 1, (k / 3) % 3 - 1, k / 9 - 1};
+            int q[3];
+            bool ok = true;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                q[a] = c[a] + d[a];
+                if (q[a] < 0) { ok = ok && B.periodic[a]; q[a] += B.nc[a]; }
+                else if (q[a] >= B.nc[a]) { ok = ok && B.periodic[a]; q[a] -= B.nc[a]; }
+            }
+            if (ok)
+                t += p.count[B.coff + (uint32_t)q[0] +
+                             (uint32_t)B.nc[0] * ((uint32_t)q[1] + (uint32_t)B.nc[1] * (uint32_t)q[2])];
+        }
+    }
+    block_sum2(t, z, lds);
+    if (threadIdx.x == 0) atomicAdd(&p.ctl->tests_init, (unsigned long long)t);
+}
+
 inline uint32_t blocks_for(uint32_t n, uint32_t b) { return (n + b - 1) / b; }
 
 // The direct search with G lanes per particle.
@@ -3269,6 +3303,12 @@ hipError_t launch_init(const Plan& p, const double* d_state, const uint8_t* d_ki
     k_init_ctl<<<1, 64, 0, s>>>(p, 0);
     if (p.N > 0 && p.nspecies > 0) k_check_kinds<<<blocks_for(p.N, b), b, 0, s>>>(p, d_kind);
     if (p.N > 0) k_bin<<<blocks_for(p.N, b), b, 0, s>>>(p);
+    return hipGetLastError();
+}
+
+hipError_t launch_init_tests(const Plan& p, hipStream_t s)
+{
+    if (p.N > 0) k_init_tests<<<blocks_for(p.N, 256), 256, 0, s>>>(p);
     return hipGetLastError();
 }
 

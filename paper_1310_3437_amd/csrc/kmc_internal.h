@@ -88,7 +88,7 @@ struct Ctl {
     unsigned int overflow;              // this step's flag for the whole-step FP64 search
     unsigned int refined_count;         // adaptive bins: bins split this step
     unsigned int pool_used;             // adaptive bins: leaf-table entries claimed this step
-    unsigned int pad_[2];
+    unsigned long long tests_init;      // candidates of the initial state's particles (launch_init_tests)
 };
 
 // FP32 screen thresholds of one box for one step.  The bounds on the error
@@ -177,6 +177,9 @@ struct Plan {
 // KMC_PHASE_COUNT + 2 events recorded on `s`: ev[k] at the start of phase k,
 // ev[KMC_PHASE_COUNT] at the end of the step and ev[KMC_PHASE_COUNT + 1]
 // right before the search kernel itself (after the screen's bound kernels).
+// Counts the candidates of every particle of the state written by launch_init
+// into the control block.
+hipError_t launch_init_tests(const Plan& p, hipStream_t s);
 hipError_t launch_init(const Plan& p, const double* d_state, const uint8_t* d_kind, hipStream_t s);
 hipError_t launch_step(const Plan& p, hipStream_t s, hipEvent_t* ev);
 hipError_t launch_read_partners(const Plan& p, int32_t* out, hipStream_t s);

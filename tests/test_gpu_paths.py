@@ -279,3 +279,39 @@ def test_full_search_of_beams(kmc, share, whole, tile):
                                         search_mode=kmc.KMC_SEARCH_FULL)
     assert mism == 0 and same
     assert stats["rechecks"] > w.n / 6 and stats["fallbacks"] == whole
+
+
+def clusters(n, width, periodic=True):
+    """Three Gaussian clusters of a cell's width or more, one across the seams, in
+    a box of 100^3 cells, and few particles elsewhere."""
+    rng = np.random.default_rng(17)
+    c = np.array([[0.0, 0.5, 0.004], [0.31, 0.3, 0.7], [0.8, 0.99, 0.5]])[rng.integers(0, 3, n)].T
+    s = np.empty((6, n))
+    s[0:3] = c + width * rng.standard_normal((3, n))
+    s[0:3, ::50] = rng.random((3, (n + 49) // 50))
+    s[0:3] = np.minimum(np.mod(s[0:3], 1.0), np.nextafter(1.0, 0.0))
+    s[3:6] = rng.standard_normal((3, n))
+    box = I.Box(n=n, lo=(0, 0, 0), hi=(1, 1, 1), ncell=(100,) * 3, periodic=(periodic,) * 3, D2=0.0015 ** 2, dt=0.002)
+    return I.Workload("clusters", [box], s, 1)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,width,staged", [(49_152, 0.009, False), (100_000, 0.016, True)])
+def test_clustered_gases(kmc, n, width, staged, precision):
+    """A large gas whose clusters make far more pair tests than its mean density
+    takes the staged searches (of which the half search lists particles for the
+    re-search here), one of up to 49152 particles the direct one, also as one of
+    two boxes; a thin gas of that size takes the direct one."""
+    w = clusters(n, width, periodic=staged)
+    for mode in (kmc.KMC_SEARCH_HALF, kmc.KMC_SEARCH_FULL):
+        _, exact = run_parity(kmc, w, 1, precision=precision, search_mode=mode)
+        assert exact
+        if mode == kmc.KMC_SEARCH_HALF:
+            assert (run_parity.last_stats["rechecks"] > 0) == staged
+    thin = I.uniform_box(n, ncell=100, D=0.009, ic_seed=3, dt=0.05)
+    run_parity(kmc, I.Workload("thin", [thin[0]], thin[1], 1), 1, precision=precision)
+    assert run_parity.last_stats["rechecks"] == 0
+    a, b = clusters(n - 200, width), I.uniform_box(200, ncell=10, D=0.05, ic_seed=4)
+    two = I.Workload("two", [b[0], a.boxes[0]], np.concatenate([b[1], a.state], axis=1), 1)
+    run_parity(kmc, two, 1, precision=precision)
+    assert (run_parity.last_stats["rechecks"] > 0) == staged
