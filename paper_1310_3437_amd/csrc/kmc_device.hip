@@ -2421,7 +2421,7 @@ constexpr uint32_t kFallbackBlocks = 4096;
 // with the flag set it decides every pair in FP64 itself.)
 __device__ __forceinline__ bool whole_step(const Plan& p)
 {
-    return p.ctl->overflow != 0u || p.ctl->recheck_count > p.N / kRecheckShare + kFallbackBlocks;
+    return (p.ctl->overflow != 0u) | (p.ctl->recheck_count > p.N / kRecheckShare + kFallbackBlocks);
 }
 
 // Whole-step FP64 search, by the full-neighbourhood organisation, when the
@@ -3169,6 +3169,7 @@ __global__ __launch_bounds__(1024) void k_advance(Plan p)
 {
     __shared__ uint64_t lds[32];
     uint64_t np = 0, dig = 0, cand = 0, z = 0;
+    const bool whole = whole_step(p);   // (loaded here, under the sums)
     for (uint32_t k = threadIdx.x; k < p.acc_lanes; k += blockDim.x) {
         StepAcc& a = p.acc[k];
         np += a.np;
@@ -3188,7 +3189,7 @@ __global__ __launch_bounds__(1024) void k_advance(Plan p)
         p.hist_dig[done % p.H] = dig;
         p.ctl->candidates_total += cand;
         p.ctl->rechecks_total += p.ctl->recheck_count;
-        p.ctl->fallbacks_total += whole_step(p) ? 1ull : 0ull;
+        p.ctl->fallbacks_total += whole ? 1ull : 0ull;
         p.ctl->steps_done = done + 1;
         p.ctl->step += 1;
     }
