@@ -315,3 +315,37 @@ def test_clustered_gases(kmc, n, width, staged, precision):
     two = I.Workload("two", [b[0], a.boxes[0]], np.concatenate([b[1], a.state], axis=1), 1)
     run_parity(kmc, two, 1, precision=precision)
     assert (run_parity.last_stats["rechecks"] > 0) == staged
+
+
+def rings(m, ncell):
+    """60 resting particles, each with m partners that pass it along +x at the
+    same distance of closest approach, exactly or up to some ulp."""
+    rng = np.random.default_rng(8)
+    s = np.zeros((6, 60 * (m + 1)))
+    k = 0
+    for c in range(60):
+        ctr = 0.15 + 0.18 * np.array([c % 5, c // 5 % 4, c // 20])
+        s[0:3, k] = ctr
+        k += 1
+        for e in range(m):
+            a = 2 * np.pi * rng.random()
+            r = 0.04 if e % 3 else 0.04 * (1.0 + 2.0 ** -52 * e)
+            s[0:3, k] = ctr[0] - rng.uniform(0.01, 0.03), ctr[1] + r * np.cos(a), ctr[2] + r * np.sin(a)
+            s[3, k] = 1.0 + 0.2 * rng.random()
+            k += 1
+    box = I.Box(n=k, lo=(0, 0, 0), hi=(1, 1, 1), ncell=(ncell,) * 3, periodic=(True,) * 3, D2=0.09 ** 2, dt=0.05)
+    return I.Workload("rings", [box], s[:, rng.permutation(k)].copy(), 1)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("tile,m,ncell", [(1, 39, 10), (2, 39, 10), (1, 99, 10), (2, 99, 10), (0, 99, 5)])
+def test_staged_searches_of_equal_and_near_equal_keys(kmc, tile, m, ncell, precision):
+    """More partners than a particle has slots, whose keys the screen cannot tell
+    apart: the wave searches such a particle again, or lists it where its cell
+    holds more than 64."""
+    w = rings(m, ncell)
+    for mode in (kmc.KMC_SEARCH_FULL, kmc.KMC_SEARCH_HALF):
+        _, exact = run_parity(kmc, w, 1, precision=precision, search_mode=mode, tile=tile)
+        assert exact
+        if precision == "fp32" and mode == kmc.KMC_SEARCH_FULL:
+            assert (run_parity.last_stats["rechecks"] > 0) == (m == 99)
