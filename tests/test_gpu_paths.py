@@ -5,7 +5,8 @@ import pytest
 
 from paper_1310_3437_amd import inputs as I
 from tests.test_gpu_adaptive import run_adaptive
-from tests.test_gpu_parity import run_parity
+from tests.test_gpu_kinds import adversarial_kinds, run_kinds
+from tests.test_gpu_parity import _adaptive, run_parity
 from tests import test_gpu_screen as S
 from tests.test_gpu_screen import dense_gas
 
@@ -349,3 +350,112 @@ def test_staged_searches_of_equal_and_near_equal_keys(kmc, tile, m, ncell, preci
         assert exact
         if precision == "fp32" and mode == kmc.KMC_SEARCH_FULL:
             assert (run_parity.last_stats["rechecks"] > 0) == (m == 99)
+
+
+STAGED = [("half", 1), ("half", 2), ("full", 1), ("full", 2)]
+
+
+@pytest.mark.parametrize("mode,tile", STAGED)
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_staged_forms(kmc, precision, mode, tile):
+    """The forms of a small gas in the staged searches (a tile shape asked for;
+    the default takes the direct one): absorbing faces, periodic and not, the
+    planar mode with the fixed and the adaptive step, positions on cell faces,
+    empty boxes between others, velocity-only collisions, a sphere, rows of three
+    cells, one particle, kinds."""
+    kw = dict(precision=precision, tile=tile,
+              search_mode=kmc.KMC_SEARCH_FULL if mode == "full" else kmc.KMC_SEARCH_HALF)
+    w = I.c2_shock(n=10_000, steps=8)
+    w.boxes[0].absorb = (True, False, False)
+    run_parity(kmc, w, 8, **kw)
+    assert run_parity.last_stats["absorbed"] > 0
+    w = _adaptive(I.c1_small(steps=6), 1.0, 10.0)
+    w.boxes[0].periodic, w.boxes[0].absorb = (False, True, True), (True, False, False)
+    run_parity(kmc, w, 6, use_graph=True, **kw)
+    assert run_parity.last_stats["absorbed"] > 0
+    run_parity(kmc, I.c1_planar(steps=4), 4, **kw)
+    st = run_parity.last_state
+    assert np.all(st[2] == 0.5) and np.all(st[5] == 0.0)
+    run_parity(kmc, _adaptive(I.c1_planar(n=20_011, D=0.004, steps=3), 0.5, 10.0), 3, use_graph=True, **kw)
+    n = 8009
+    box, s = I.uniform_box(n, ncell=20, D=0.045, ic_seed=3, dt=0.01)
+    box.periodic = (True, False, True)
+    s[0:3] = np.floor(s[0:3] * 20) / 20 + (np.random.default_rng(3).random((3, n)) < 0.5) * (s[0:3] % 0.05)
+    run_parity(kmc, I.Workload("faces", [box], s, 3), 3, **kw)
+    e = I.Box(n=0, lo=(0, 0, 0), hi=(1, 1, 1), ncell=(4, 4, 4), periodic=(True,) * 3, D2=0.01, dt=0.01)
+    w = I.c4_batch(nboxes=4, n_lo=100, n_hi=2000, steps=3)
+    w.boxes = [e] + w.boxes[:2] + [e] + w.boxes[2:] + [e]
+    w.kinematics = 1
+    run_parity(kmc, w, 3, **kw)
+    run_parity(kmc, I.c3_sphere(n=8000, steps=3), 3, **kw)
+    for n in (1, 400):
+        box, s = I.uniform_box(n, ncell=3, D=0.3, ic_seed=5)
+        run_parity(kmc, I.Workload("seams", [box], s, 3), 3, **kw)
+    w = I.c6_mixture(n=4001, steps=3)
+    run_parity(kmc, w, 3, kinds=(w.species, w.radius, w.mass), use_graph=True, **kw)
+
+
+@pytest.mark.parametrize("mode,tile", STAGED)
+@pytest.mark.parametrize("bulk", [0.0, 20.0])
+def test_staged_screen_on_adversarial_kinds(kmc, bulk, mode, tile):
+    w = adversarial_kinds(seed=22, bulk=bulk)
+    kw = dict(tile=tile, search_mode=kmc.KMC_SEARCH_FULL if mode == "full" else kmc.KMC_SEARCH_HALF)
+    _, s64 = run_kinds(kmc, w, 2, "fp64", **kw)
+    _, s32 = run_kinds(kmc, w, 2, "fp32", **kw)
+    assert s32["candidates"] >= s64["candidates"]
+
+
+def many(make, count):
+    """`count` boxes of make(seed), the workloads of four seeds in turn."""
+    ws = [make(seed) for seed in range(41, 45)]
+    ws = [ws[k % 4] for k in range(count)]
+    w = I.Workload("many", [w.boxes[0] for w in ws], np.concatenate([w.state for w in ws], axis=1), 1)
+    if ws[0].species is not None:
+        w.species, w.radius, w.mass = np.concatenate([w.species for w in ws]), ws[0].radius, ws[0].mass
+    return w
+
+
+@pytest.mark.parametrize("mode", ["half", "full"])
+def test_default_tile_above_the_direct_search(kmc, mode):
+    """Gases of more than 2^18 particles: the default tile shape on near-boundary
+    pairs of one and three kinds, particles outside their grids, absorbing faces
+    and the planar mode."""
+    sm = kmc.KMC_SEARCH_FULL if mode == "full" else kmc.KMC_SEARCH_HALF
+    w = many(lambda seed: S.adversarial(seed=seed), 120)
+    assert w.n > 2 ** 18
+    mism, same, stats = S.gpu_vs_oracle(kmc, w, kmc.KMC_FP32_SCREEN, search_mode=sm)
+    assert mism == 0 and same and stats["fallbacks"] == 0
+    w = many(lambda seed: S.adversarial_outside(seed=seed)[0], 136)
+    assert w.n > 2 ** 18
+    mism, same, stats = S.gpu_vs_oracle(kmc, w, kmc.KMC_FP32_SCREEN, search_mode=sm)
+    assert mism == 0 and same and stats["fallbacks"] == 1
+    w = many(lambda seed: adversarial_kinds(seed=seed), 136)
+    assert w.n > 2 ** 18
+    run_kinds(kmc, w, 1, "fp32", search_mode=sm)
+    for precision in ("fp64", "fp32"):
+        w = I.c2_shock(n=300_000, steps=4)
+        w.boxes[0].absorb = (True, False, False)
+        run_parity(kmc, w, 4, check_every=4, precision=precision, search_mode=sm)
+        assert run_parity.last_stats["absorbed"] > 0
+        run_parity(kmc, I.c1_planar(n=300_000, D=0.002, steps=2), 2, check_every=2, precision=precision, search_mode=sm)
+
+
+@pytest.mark.parametrize("ncell", [(7, 31, 151), (32, 32, 32), (33, 33, 33)])
+def test_scan_in_one_block_and_two_launches(kmc, ncell):
+    """32768 cells with the one for absorbed particles (one block) and more."""
+    n = 5003
+    box, s = I.uniform_box(n, ncell=4, D=0.005, ic_seed=9, dt=0.01)
+    box.ncell = ncell
+    for kw in (dict(), dict(tile=1, search_mode=kmc.KMC_SEARCH_FULL)):
+        _, exact = run_parity(kmc, I.Workload("scan", [box], s, 3), 3, precision="fp32", **kw)
+        assert exact
+
+
+@pytest.mark.parametrize("n,ncell,D", [(2 ** 18, 120, 0.008), (2 ** 18 + 1, 120, 0.008),
+                                       (60_000, 25, 0.01), (60_000, 26, 0.01)])
+def test_limits_of_the_direct_search(kmc, n, ncell, D):
+    """2^18 particles and one more, 6.2e6 and 5.5e6 expected pair tests."""
+    box, s = I.uniform_box(n, ncell=ncell, D=D, ic_seed=n, dt=0.2 / ncell)
+    for precision in ("fp64", "fp32"):
+        _, exact = run_parity(kmc, I.Workload("limits", [box], s, 2), 2, check_every=2, precision=precision)
+        assert exact
