@@ -204,9 +204,7 @@ size_t layout(Plan& p, char* base, uint32_t nboxes, const kmc_config& cfg, const
     p.start = (uint32_t*)take(4 * (C + 1));
     p.partial = (uint32_t*)take(4 * (size_t)(nblk ? nblk : 1));
     p.recheck = (uint32_t*)take(4 * (size_t)(cap ? cap : 1));
-    // (16 bytes per particle, four of them used: the workspace keeps its size,
-    // and with it the largest gas that kmc_init_scratch takes)
-    p.place = (uint32_t*)take(16 * (N ? N : 1));
+    p.place = (uint32_t*)take(4 * (N ? N : 1));
     p.adapt_L = cfg.adapt_levels;
     p.adapt_T = cfg.adapt_threshold;
     if (cfg.adapt_levels > 0) {

@@ -269,3 +269,15 @@ def test_adaptive_bins_validation():
     n0 = _ws([_good()], search_mode=kmc.KMC_SEARCH_FULL)[1]
     n1 = _ws([_good()], **ok)[1]
     assert n1 >= n0 + 4 * (8 * 100 // 8 + 100 + 1) + 4 * 100 + 10 * 64
+
+
+def test_workspace_bytes_per_particle():
+    """Two records, ids, slot, partner, list length, eight list entries, forward
+    best, re-search list, read-out index: 264 bytes, and 12 per scatter block."""
+    n = 1 << 20
+    sizes = []
+    for m in (1, 3):
+        b = _good()
+        b.n = m * n
+        sizes.append(_ws([b])[1])
+    assert abs((sizes[1] - sizes[0]) - 2 * n * (264 + 12 / 256)) < 4096
