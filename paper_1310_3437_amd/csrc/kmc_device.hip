@@ -1369,15 +1369,18 @@ struct Best {
 // overtaken pairs staying in them, took 18.9 ms on the blobs for the particles
 // searched again.
 constexpr int kDefer = 5;
-// Up to this many particles of a tile, in cells of up to this many, the wave
-// searches again itself, one after another (about 4 us each at three per cell).
-// More of them, where velocities are equal in FP32 and no pair can be told from
-// another (beams, a gas at rest), go to the step's list (1e6 particles of one
-// velocity: 1130 us a step by the waves themselves, 660 by the list, which gives
-// way to the whole-step search), and so do those of dense cells, with their
-// thousands of candidates (1.8e5 in two clusters: 18.1 -> 11.7 ms).
+// Up to this many particles of a tile the wave searches again itself, one after
+// another (about 4 us each at three per cell).  More of them, where velocities
+// are equal in FP32 and no pair can be told from another (beams, a gas at rest),
+// go to the step's list (1e6 particles of one velocity: 1130 us a step by the
+// waves themselves, 660 by the list, which gives way to the whole-step search).
+// So do those of dense cells, with their thousands of candidates, in a gas of
+// one round of waves, where each wave's time shows (1.8e5 in two clusters: 18.1
+// -> 11.7 ms); in a larger gas other waves run beside it, and the list's few
+// long searches would come after (1e7 in blobs: 180 to 410 us a step).
 constexpr int kAgainAlone = 16;
 constexpr uint32_t kAgainCell = 64;
+constexpr uint32_t kAgainRound = 64u * 6u * 4u * 256u;   // six waves on each SIMD
 struct DeferLds {
     uint32_t j[kDefer][64];      // sorted index
     float lo[kDefer][64];        // lower bound of the key
@@ -1920,7 +1923,6 @@ struct PolF32 {
                     if (d.l->lo[e][threadIdx.x] > best.kcut) k = e;
                 if (k < 0) {
                     d.n = kDefer + 1;
-                    best.kcut = -__builtin_inff();   // searched again: nothing more to record
                     return;
                 }
             }
@@ -2350,6 +2352,9 @@ __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, t
                     Pol::template scan_best<false>(lds, lid, c0, f0, f1, i, own, B, gctx, m, best, dfr);
                 __syncthreads();
             }
+            // (a particle beyond its slots is searched again: it records nothing
+            // more; set in the pair loop this took four registers and with them a wave)
+            if (Pol::kScreen && dfr.n > kDefer) best.kcut = -__builtin_inff();
         };
         for (int r = 0; r < 9; ++r) {
             RowRange R;
@@ -2386,7 +2391,11 @@ __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, t
         uint64_t again = __ballot(dfr.n > kDefer);
         if (again) {
             uint32_t own = 0;   // particles in the cell
-            if (dfr.n > kDefer) own = p.start[rowkey + (uint32_t)cx + 1u] - p.start[rowkey + (uint32_t)cx];
+            if (dfr.n > kDefer && p.N <= kAgainRound) {
+                const P64 me = p.B[i];
+                const uint32_t c = cell_of(box_of(p, i), me.x, me.y, me.z, false);
+                own = p.start[c + 1u] - p.start[c];
+            }
             if (__popcll(again) > kAgainAlone || __ballot(own > kAgainCell)) {
                 push_recheck(p, i, dfr.n > kDefer);
                 again = 0;
