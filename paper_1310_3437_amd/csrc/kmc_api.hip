@@ -218,11 +218,9 @@ size_t layout(Plan& p, char* base, uint32_t nboxes, const kmc_config& cfg, const
         p.refined = (uint32_t*)take(4 * (C ? C : 1));
         p.pool = (uint32_t*)take(4 * cap);
         p.leaf_slot = (uint32_t*)take(4 * (N ? N : 1));
-        p.pool_cap = (uint32_t)std::min<size_t>(cap, 0xFFFFFFFFu);
     } else {
         p.level = p.mixed = nullptr;
         p.pool_base = p.refined = p.pool = p.leaf_slot = nullptr;
-        p.pool_cap = 0;
     }
     p.nspecies = cfg.species ? (int32_t)cfg.species->count : 0;
     if (cfg.species) {

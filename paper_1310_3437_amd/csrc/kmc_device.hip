@@ -1451,8 +1451,8 @@ struct PolF64 {
         x = o.me.x; y = o.me.y; z = o.me.z;
     }
     __device__ static P64 self64(const Plan&, uint32_t, const Own& o) { return o.me; }
-    __device__ static void stage(Lds& l, uint32_t t, const Plan& p, uint32_t j, const BoxDev&, const Group&,
-                                 int, int, int, int, int)
+    __device__ static void stage(Lds& l, uint32_t t, const Plan& p, uint32_t j, const BoxDev&, const Group&, int, int,
+                                 int)
     {
         l.rec[t] = p.B[j];
         if (K) l.kind[t] = p.spB[j];
@@ -1831,7 +1831,7 @@ struct PolF32 {
     // velocity, each rounded once.  Rows without an image (almost all) skip
     // the shift (the row's shift is the same for the whole wave).
     __device__ static void stage(Lds& l, uint32_t t, const Plan& p, uint32_t j, const BoxDev& B, const Group& g,
-                                 int wx, int wy, int wz, int, int)
+                                 int wx, int wy, int wz)
     {
         const P64 q = p.B[j];
         double x = q.x, y = q.y, z = q.z;
@@ -2105,7 +2105,7 @@ void k_search_half(Plan p)
                 for (uint32_t t = (uint32_t)lane; t < n; t += 64u) {
                     int wx;
                     const uint32_t j = m.at(c0 + t, wx);
-                    Pol::stage(lds, t, p, j, B, gctx, wx, m.wy, m.wz, 0, 0);
+                    Pol::stage(lds, t, p, j, B, gctx, wx, m.wy, m.wz);
                 }
                 __syncthreads();
                 const uint32_t f0 = max(lf, c0), f1 = min(le, c0 + n);
@@ -2339,7 +2339,7 @@ __device__ __forceinline__ void search_full_tile(const Plan& p, uint32_t tile, t
                 for (uint32_t t = (uint32_t)lane; t < n; t += 64u) {
                     int wx;
                     const uint32_t j = m.at(c0 + t, wx);
-                    Pol::stage(lds, t, p, j, B, gctx, wx, m.wy, m.wz, 0, 0);
+                    Pol::stage(lds, t, p, j, B, gctx, wx, m.wy, m.wz);
                     if constexpr (!Pol::kScreen) lid[t] = p.idB[j];
                 }
                 __syncthreads();
@@ -2446,9 +2446,6 @@ __device__ __forceinline__ bool whole_step(const Plan& p)
 // leave the screen's safe range; otherwise the re-search of the listed
 // particles, one wave each.  A fixed grid of waves that exits at once when a
 // step needs neither.
-// Waves that walk the list of split cells (adaptive bins).
-constexpr uint32_t kAdaptPrepBlocks = 4096;
-
 template <class Pol>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Pol::kFullWaves)))
 void k_research(Plan p)
@@ -2496,10 +2493,10 @@ void k_research(Plan p)
 
 // The leaves of the neighbour cell (c + d) that touch the leaf [lo, hi]
 // (finest indices per axis) of a particle in cell c, as ranges of the sorted
-// arrays: f(s, e, code) once per run of touching leaves that is contiguous
-// in the cell's leaf order (one range for an unsplit cell); code packs the
-// periodic image (wcode) and the cell offset d.  Nothing when the neighbour
-// cell does not exist or no leaf of it touches.
+// arrays: f(s, e) once per run of touching leaves that is contiguous in the
+// cell's leaf order (one range for an unsplit cell).  Nothing when the neighbour
+// cell does not exist or no leaf of it touches.  For the pair-test counter; the
+// search lists a leaf's runs by several lanes (list_leaf).
 template <class F>
 __device__ __forceinline__ void neighbour_leaves(const Plan& p, const BoxDev& B, const int c[3], const int lo[3],
                                                  const int hi[3], int dx, int dy, int dz, F&& f)
@@ -2528,17 +2525,16 @@ __device__ __forceinline__ void neighbour_leaves(const Plan& p, const BoxDev& B,
         jhi[a] = (int)min((long long)(r - 1), ((long long)hi[a] + 1 - b0) >> sh);
         if (jlo[a] > jhi[a]) return;
     }
-    const uint32_t code = wcode(w[0], w[1], w[2]) | ((uint32_t)wcode(dx, dy, dz) << 6);
     const uint32_t s0 = p.start[cell];
     if (lvl == 0) {
-        f(s0, p.start[cell + 1], code);
+        f(s0, p.start[cell + 1]);
         return;
     }
     const uint32_t* t = p.pool + p.pool_base[cell];
     for (int jz = jlo[2]; jz <= jhi[2]; ++jz)
         for (int jy = jlo[1]; jy <= jhi[1]; ++jy) {
             const uint32_t row = (uint32_t)r * ((uint32_t)jy + (uint32_t)r * (uint32_t)jz);
-            f(s0 + t[row + (uint32_t)jlo[0]], s0 + t[row + (uint32_t)jhi[0] + 1u], code);
+            f(s0 + t[row + (uint32_t)jlo[0]], s0 + t[row + (uint32_t)jhi[0] + 1u]);
         }
 }
 
@@ -2951,7 +2947,7 @@ __global__ __launch_bounds__(64) void k_search_direct(Plan p)
 
 // Partner of every particle: the (key, id) minimum of its forward best (the
 // pairs its own search lane found) and the entries of its candidate list
-// (pairs found from the other side, or through the overflow list); keys are
+// (pairs found from the other side, and its own extra pairs); keys are
 // exact FP64, ids are read only to break equal keys.  A particle with more
 // list entries than slots is searched again in full.
 __global__ __launch_bounds__(256) void k_finish(Plan p)
@@ -3232,7 +3228,7 @@ __global__ __launch_bounds__(256) void k_count_tests(Plan p, unsigned long long*
             leaf_of(p, B, me.x, me.y, me.z, c, lo, hi, code);
             for (int k = 0; k < 27; ++k)
                 neighbour_leaves(p, B, c, lo, hi, k % 3 - 1, (k / 3) % 3 - 1, k / 9 - 1,
-                                 [&](uint32_t s, uint32_t e, uint32_t) { t += e - s; });
+                                 [&](uint32_t s, uint32_t e) { t += e - s; });
         } else {
             for_each_range(B, cx, cy, cz, p.start, [&](uint32_t s, uint32_t e, int, int, int) { t += e - s; });
         }
@@ -3274,6 +3270,9 @@ __global__ __launch_bounds__(256) void k_init_tests(Plan p)
     block_sum2(t, z, lds);
     if (threadIdx.x == 0) atomicAdd(&p.ctl->tests_init, (unsigned long long)t);
 }
+
+// Waves that walk the list of split cells (adaptive bins).
+constexpr uint32_t kAdaptPrepBlocks = 4096;
 
 inline uint32_t blocks_for(uint32_t n, uint32_t b) { return (n + b - 1) / b; }
 

@@ -159,7 +159,6 @@ struct Plan {
     uint32_t* pool;                // leaf tables: per split cell 8^level counts, then their
                                    // exclusive prefix (leaf starts relative to the cell's
                                    // start) and the cell's count
-    uint32_t pool_cap;             // entries of pool
     uint32_t* leaf_slot;           // per particle in A order: its rank in its leaf
     int32_t dims;                  // 3, or 2 for the planar mode
     double dt_factor;              // adaptive dt: C in dt = min(cap, C dx / v_max)
