@@ -459,3 +459,14 @@ def test_limits_of_the_direct_search(kmc, n, ncell, D):
     for precision in ("fp64", "fp32"):
         _, exact = run_parity(kmc, I.Workload("limits", [box], s, 2), 2, check_every=2, precision=precision)
         assert exact
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2])
+def test_speeds_that_vanish_in_fp32(kmc, tile):
+    """Speeds of 2^-160 are zero in FP32, and so is the screen's largest speed;
+    pairs side by side are acceptable all the same."""
+    w = side_by_side()
+    w.state[3:6] *= 2.0 ** -160
+    for mode in (kmc.KMC_SEARCH_FULL, kmc.KMC_SEARCH_HALF):
+        d, exact = run_parity(kmc, w, 1, precision="fp32", search_mode=mode, tile=tile)
+        assert exact and d[0][0] > 500
