@@ -873,7 +873,8 @@ __global__ void k_scatter(Plan p)
         if (id & kGone) vx = vy = vz = 0.0;   // not in the gas: no part in the adaptive step
         if (F32) {
             vm = fmaxf(fabsf((float)r.vx), fmaxf(fabsf((float)r.vy), fabsf((float)r.vz)));
-
+            // (a box's largest speed is 0 only where every particle rests)
+            if (vm == 0.f && ((r.vx != 0.0) | (r.vy != 0.0) | (r.vz != 0.0))) vm = 0x1p-126f;
             if (!(id & kGone)) {
                 outside = outside_grid(B, r);
             }
@@ -1655,6 +1656,9 @@ __device__ __forceinline__ void screen_thresholds(const BoxDev& B, const double 
     g.kb = 0.5f * (g.kdt + g.tb1) * 1.000001f;
     g.kg = fmaxf(g.tb0, g.tt0) * 1.000001f;
     g.tc = g.tc0 * 1.000001f;
+    // Nothing is acceptable in a gas at rest, and no pair passes (with b = g2 = 0
+    // every one would, and end in the re-search).
+    if (V == 0.0) g.tb0 = g.kg = -1.0f;
     g.kdm = (float)((dt32 - t[3]) * (1.0 - 2e-6));
     g.gmin = t[7] < 0.5 ? (float)(2.0 * t[6] * (1.0 + 2e-6)) : __builtin_inff();
 }

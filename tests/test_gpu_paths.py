@@ -470,3 +470,17 @@ def test_speeds_that_vanish_in_fp32(kmc, tile):
     for mode in (kmc.KMC_SEARCH_FULL, kmc.KMC_SEARCH_HALF):
         d, exact = run_parity(kmc, w, 1, precision="fp32", search_mode=mode, tile=tile)
         assert exact and d[0][0] > 500
+
+
+@pytest.mark.parametrize("n,tile", [(2000, 0), (20_011, 0), (20_011, 1), (20_011, 2)])
+def test_gas_at_rest(kmc, n, tile):
+    """Nothing is acceptable at rest, and the screen keeps nothing; one particle
+    that moves too slowly for FP32 hands the step to the FP64 search."""
+    w = dense_gas(n=n)
+    w.state[3:6] = 0.0
+    for v, fallbacks in ((0.0, 0), (2.0 ** -160, 1)):
+        w.state[4, 7] = v
+        for mode in (kmc.KMC_SEARCH_FULL, kmc.KMC_SEARCH_HALF):
+            mism, same, stats = S.gpu_vs_oracle(kmc, w, kmc.KMC_FP32_SCREEN, tile=tile, search_mode=mode)
+            assert mism == 0 and same and stats["fallbacks"] == fallbacks
+            assert v != 0.0 or (stats["candidates"] == 0 and stats["rechecks"] == 0)
