@@ -2493,7 +2493,7 @@ void k_research(Plan p)
 // 3.2 and 3.8, without the load ahead 3.8, a list of a fixed size per leaf 3.25.
 // Against the leaves in turn it gains 1.3 to 1.45 times at a threshold of 8 and
 // three levels, 1.1 to 1.25 at leaves of 100, and nothing from about 400 on
-// (1.0 to 0.91: LDS would serve their many owners better than L1 does).
+// (1.0 to 0.89: LDS would serve their many owners better than L1 does).
 // Now the L1 lookups of the gathered records and the control flow of the walk
 // take about equal parts with the FP64 tests.
 // --------------------------------------------------------------------------
